@@ -188,7 +188,7 @@ __device__ __forceinline__ float bf16_hi(uint32_t packed) {
   return __uint_as_float(packed & 0xffff0000u);
 }
 
-// 2^x for x up to a few units (softmax weights): the hardware instruction as it is.  Results
+// 2^x for x <= 0 (softmax weights): the hardware instruction as it is.  Results
 // below the normal range come out as 0, which is what a weight of 2^-127 is worth.
 __device__ __forceinline__ float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 
