@@ -1,5 +1,6 @@
-"""Dense attention: values near the end of the range."""
+"""Dense attention: values near the end of the range, infinite elements in the last row of a sequence."""
 
+import numpy as np
 import pytest
 import torch
 
@@ -39,3 +40,22 @@ def test_values_near_the_end_of_the_range(G):
         ref = torch.softmax(K[h // G].double() @ q[0, h].double() / d ** 0.5, 0) @ V[h // G].double()
         # weights and sums in fp32, 300 tokens: below 310 roundings of 2^-24 each
         assert float(((out[0, h] - ref) / ref).abs().max()) < 310 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("G", [1, 5, 8])
+@pytest.mark.parametrize("d", [64, 128, 192])
+def test_an_infinite_element_in_the_last_row(G, d):
+    gen = torch.Generator().manual_seed(G + d)
+    lens, Hkv = [1, 33, 200, 64, 127], 2
+    starts = [0] + list(np.cumsum(lens)[:-1])
+    K, V = (torch.randn(Hkv, sum(lens), d, generator=gen).bfloat16() for _ in range(2))
+    q = torch.randn(len(lens), Hkv * G, d, generator=gen).bfloat16()
+    inf = float("inf")
+    for s, L in zip(starts, lens):
+        V[0, s + L - 1, 3] = inf
+        V[1, s + L - 1, 8] = -inf
+    out = full_attention(q, K, V, starts, lens)
+    assert torch.all(out[:, :G, 3] == inf) and torch.all(out[:, G:, 8] == -inf)
+    fine = torch.ones_like(out, dtype=torch.bool)
+    fine[:, :G, 3] = fine[:, G:, 8] = False
+    assert torch.isfinite(out[fine]).all()
