@@ -233,7 +233,8 @@ Thresholds scaled(const adamas_config* c, const float* thr) {
   t.transform = (c->variant & ADAMAS_VARIANT_NO_HADAMARD) ? 0 : 1;
   const double root = t.transform ? std::sqrt((double)c->head_dim) : 1.0;
   const int n_thr = (1 << code_bits(c)) - 1;
-  for (int i = 0; i < n_thr; ++i) t.tau[i] = (double)thr[i] * root;
+  // (+ 0.0: a threshold of -0 is 0; the single-precision attempt reads the sign of tau - y)
+  for (int i = 0; i < n_thr; ++i) t.tau[i] = (double)thr[i] * root + 0.0;
   // single-precision copies for the bulk encode's certified attempt
   t.fast = 1;
   double worst = 0.0;
