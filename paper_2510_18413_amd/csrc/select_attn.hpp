@@ -201,7 +201,7 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
     const int i0 = b0 + grp;
     // Row slots are filled in order, so one that the wave's first group does not use
     // ends the batch (wave-uniform: the rows of a small selection take one or
-    // two slots, and unused pairs cost nothing).
+    // two slots, and unused ones cost nothing).
     const int used = min((n - b0 - wave_grp + kGroups - 1) / kGroups, U);
     uint4 kv[U], vv[U];
     bool ok[U];
@@ -221,57 +221,70 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
     }
     // Two rows at a time: their chains of additions run side by side (all four at once take
     // 89 registers, and a sixth workgroup no longer fits a compute unit: 61.9 -> 66.2 us for 48 sequences).
+    // A last slot without a partner is computed alone (one slot, D = 64, 128 heads of 256 rows: 7.2 us, in a pair 7.5, with
+    // a maximum per row 7.0; three slots, D = 128, 768 heads of 700 rows: 50.0, 51.8, 50.7).
     double sc[U];
     float mn = m;
+    auto scores = [&](int u0, auto rows_) {
+#pragma clang fp contract(off)
+      constexpr int kRows = decltype(rows_)::value;
+      double s[kRows];
 #pragma unroll
-    for (int u0 = 0; u0 < U; u0 += 2) {
-      sc[u0] = sc[u0 + 1] = (double)kNegBig;
-      if (u0 < used) {
-        if (u0 == 0 && b0 == 0) trace.stamp(kSelRowsFirst);
-        double s[2];
-#pragma unroll
-        for (int v = 0; v < 2; ++v) {
-          const uint4 k4 = kv[u0 + v];
-          // two chains of four: the additions of a chain wait for each other
-          double s1 = qf[0] * (double)bf16_lo(k4.x), s2 = qf[1] * (double)bf16_hi(k4.x);
-          s1 = fma(qf[2], (double)bf16_lo(k4.y), s1);
-          s2 = fma(qf[3], (double)bf16_hi(k4.y), s2);
-          s1 = fma(qf[4], (double)bf16_lo(k4.z), s1);
-          s2 = fma(qf[5], (double)bf16_hi(k4.z), s2);
-          s1 = fma(qf[6], (double)bf16_lo(k4.w), s1);
-          s2 = fma(qf[7], (double)bf16_hi(k4.w), s2);
-          s[v] = s1 + s2;
-        }
-#pragma unroll
-        for (int v = 0; v < 2; ++v) {
-          // summed over the row's aligned group of 8, 16 or 32 lanes
-          s[v] = lanes_sum_f64<LPR>(s[v]) * scale_log2e;
-          if (ok[u0 + v]) sc[u0 + v] = s[v];
-          mn = fmaxf(mn, (float)sc[u0 + v]);
-        }
+      for (int v = 0; v < kRows; ++v) {
+        const uint4 k4 = kv[u0 + v];
+        // two chains of four: the additions of a chain wait for each other
+        double s1 = qf[0] * (double)bf16_lo(k4.x), s2 = qf[1] * (double)bf16_hi(k4.x);
+        s1 = fma(qf[2], (double)bf16_lo(k4.y), s1);
+        s2 = fma(qf[3], (double)bf16_hi(k4.y), s2);
+        s1 = fma(qf[4], (double)bf16_lo(k4.z), s1);
+        s2 = fma(qf[5], (double)bf16_hi(k4.z), s2);
+        s1 = fma(qf[6], (double)bf16_lo(k4.w), s1);
+        s2 = fma(qf[7], (double)bf16_hi(k4.w), s2);
+        s[v] = s1 + s2;
       }
+#pragma unroll
+      for (int v = 0; v < kRows; ++v) {
+        // summed over the row's aligned group of 8, 16 or 32 lanes
+        s[v] = lanes_sum_f64<LPR>(s[v]) * scale_log2e;
+        if (ok[u0 + v]) sc[u0 + v] = s[v];
+        mn = fmaxf(mn, (float)sc[u0 + v]);
+      }
+    };
+    auto weigh = [&](int u) {
+#pragma clang fp contract(off)
+      const float pw = ok[u] ? exp2_neg((float)(sc[u] - (double)mn)) : 0.f;
+      l += pw;
+      acc[0] = fmaf(pw, bf16_lo(vv[u].x), acc[0]);
+      acc[1] = fmaf(pw, bf16_hi(vv[u].x), acc[1]);
+      acc[2] = fmaf(pw, bf16_lo(vv[u].y), acc[2]);
+      acc[3] = fmaf(pw, bf16_hi(vv[u].y), acc[3]);
+      acc[4] = fmaf(pw, bf16_lo(vv[u].z), acc[4]);
+      acc[5] = fmaf(pw, bf16_hi(vv[u].z), acc[5]);
+      acc[6] = fmaf(pw, bf16_lo(vv[u].w), acc[6]);
+      acc[7] = fmaf(pw, bf16_hi(vv[u].w), acc[7]);
+    };
+    constexpr std::integral_constant<int, 1> kOne{};
+    constexpr std::integral_constant<int, 2> kTwo{};
+    if (b0 == 0) trace.stamp(kSelRowsFirst);
+#pragma unroll
+    for (int u = 0; u < U; ++u) sc[u] = (double)kNegBig;
+    if (used >= 2) scores(0, kTwo);
+    else scores(0, kOne);
+    if (used > 2) {
+      if (used > 3) scores(2, kTwo);
+      else scores(2, kOne);
     }
     const float corr = exp2_neg(m - mn);
     m = mn;
     l *= corr;
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] *= corr;
-#pragma unroll
-    for (int u0 = 0; u0 < U; u0 += 2) {
-      if (u0 < used) {
-#pragma unroll
-        for (int u = u0; u < u0 + 2; ++u) {
-          const float pw = ok[u] ? exp2_neg((float)(sc[u] - (double)mn)) : 0.f;
-          l += pw;
-          acc[0] = fmaf(pw, bf16_lo(vv[u].x), acc[0]);
-          acc[1] = fmaf(pw, bf16_hi(vv[u].x), acc[1]);
-          acc[2] = fmaf(pw, bf16_lo(vv[u].y), acc[2]);
-          acc[3] = fmaf(pw, bf16_hi(vv[u].y), acc[3]);
-          acc[4] = fmaf(pw, bf16_lo(vv[u].z), acc[4]);
-          acc[5] = fmaf(pw, bf16_hi(vv[u].z), acc[5]);
-          acc[6] = fmaf(pw, bf16_lo(vv[u].w), acc[6]);
-          acc[7] = fmaf(pw, bf16_hi(vv[u].w), acc[7]);
-        }
+    weigh(0);
+    if (used >= 2) {
+      weigh(1);
+      if (used > 2) {
+        weigh(2);
+        if (used > 3) weigh(3);
       }
     }
   }
