@@ -1,5 +1,5 @@
-"""Stand-alone sparse attention where the number of workgroups per head changes: one per head (no merge), up to four
-per compute unit, one per 32 rows; lists with padding in them."""
+"""Stand-alone sparse attention where the number of workgroups per head changes: one per head (no merge), one per 32
+rows, at most eight or sixteen; lists with padding in them."""
 
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("B,Hq,Hkv,k", [(8, 32, 8, 256), (8, 32, 8, 257), (8, 31, 31, 256), (16, 32, 8, 40),
                                         (33, 32, 4, 33), (2, 32, 8, 512), (1, 8, 8, 700), (40, 32, 32, 1), (17, 32, 8, 513),
-                                        (32, 32, 32, 896)])
+                                        (32, 32, 32, 896), (3, 32, 8, 900), (10, 32, 8, 400), (10, 32, 8, 257)])
 def test_sparse_attention_over_lists_of_every_plan(B, Hq, Hkv, k):
     import paper_2510_18413_amd as A
     L, d, G = 900, 128, Hq // Hkv
