@@ -69,11 +69,11 @@ struct Plan {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// ceil(2^32 / group), 0 for a group of one (kv_head_of in the kernels)
-uint32_t group_magic_of(const adamas_config* c) {
-  const uint64_t g = (uint64_t)(c->num_q_heads / c->num_kv_heads);
-  return g == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + g - 1) / g);
-}
+// ceil(2^32 / d), 0 for d = 1
+uint32_t magic_of(uint64_t d) { return d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+
+// of the query group (kv_head_of in the kernels)
+uint32_t group_magic_of(const adamas_config* c) { return magic_of(c->num_q_heads / c->num_kv_heads); }
 
 int log2_of(int64_t pow2) {
   int s = 0;
@@ -290,27 +290,27 @@ void launch_scan(const adamas_config* c, bool fused, const Plan& pl, int batch, 
 }
 
 struct FullPlan {
-  int n_splits, chunk;
+  int n_splits;
   size_t total;
 };
 
-// Two workgroups per compute unit, which run at the same time (the kernel keeps
-// 16 KiB per wavefront in flight), for up to half as many planes as compute units;
-// four beyond, where a plane's few splits are long and unequal sequences would
-// leave compute units idle.  A split covers a multiple of 256 tokens.  At 2 / 4
-// (/ 8) per unit, us: 8 planes of 131072 tokens 95.9 / 101.8 / 109.0; 128 ragged
-// planes of up to 16384 138.5 / 150.1 / 145.9; 224 of up to 10594 163.0 / 139.4 /
-// 136.3; 384 of up to 6001 153.8 / 158.2 / 148.9.
+// Workgroups for two per compute unit, where up to half as many planes as compute units share them; for four beyond, where a
+// plane's few splits are long and unequal sequences would leave compute units idle.  At 2 / 4 / 8 per unit, us:
+//   d = 128, group of four: 8 planes of 131072 tokens 96.8 / 101.8 / 109.8; 128 ragged planes of up to 8192 78.2 / 84.5 /
+//     80.0; 160 of up to 10000 114.4 / 112.1 / 106.2; 224 of up to 10594 174.4 / 162.0 / 153.0; 384 of up to 6001
+//     164.6 / 167.7 / 167.6; 800 planes of 3000 239.1 / 231.9 / 227.9
+//   d = 256, group of eight (one workgroup fits a compute unit): 8 of 131072 187.9 / 200.1 / 224.0; 160 ragged 236.0 /
+//     232.9 / 239.1; 192 of up to 6001 166.0 / 168.3 / 173.3; 400 of 3000 255.9 / 234.7 / 253.0
+// (eight would gain up to 6 % at d = 128 beyond 128 planes and lose up to 8 % at d = 256).
 FullPlan make_full_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len) {
   FullPlan fp{};
   const int64_t planes = (int64_t)batch * c->num_kv_heads;
   const int per_unit = planes > kTargetWorkgroups / 2 ? 4 : 2;
   int64_t want = (per_unit * kTargetWorkgroups + planes - 1) / planes;
   if (want > kFullMaxSplits) want = kFullMaxSplits;
-  int64_t chunk = (max_seq_len + want - 1) / want;
-  chunk = (chunk + 255) / 256 * 256;
-  fp.chunk = (int)chunk;
-  fp.n_splits = (int)((max_seq_len + chunk - 1) / chunk);
+  const int64_t granules = (max_seq_len + kFullGranule - 1) / kFullGranule;
+  const int64_t per = (granules + want - 1) / want;
+  fp.n_splits = (int)((granules + per - 1) / per);
   fp.total = align256((size_t)batch * c->num_q_heads * fp.n_splits * partial_stride(c->head_dim) * sizeof(float));
   return fp;
 }
@@ -768,7 +768,7 @@ int adamas_full_attn(const adamas_config* cfg, const void* q, const void* K, con
   fp.Hq = cfg->num_q_heads;
   fp.Hkv = cfg->num_kv_heads;
   fp.n_splits = pl.n_splits;
-  fp.chunk = pl.chunk;
+  fp.splits_magic = magic_of((uint32_t)pl.n_splits);
   fp.scale_log2e = (float)scale_log2e(cfg);
   const dim3 grid(pl.n_splits, cfg->num_kv_heads, batch);
   dim_set_of(cfg).full_attn(cfg->num_q_heads / cfg->num_kv_heads, grid, st, fp);

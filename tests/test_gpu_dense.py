@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 LENS = [1, 2, 15, 16, 17, 31, 32, 33, 63, 65, 127, 128, 129, 255, 256, 257, 513, 0]
 
 
-def run(G, d, lens, seed, spoil=None):
+def run(G, d, lens, seed, spoil=None, bound=None):
     """(library's output, the same in float64) for Hkv = 2; sequences packed back to back."""
     import paper_2510_18413_amd as A
     rng = np.random.default_rng(seed)
@@ -24,9 +24,9 @@ def run(G, d, lens, seed, spoil=None):
         spoil(K, V, q, starts)
     cfg = A.Config.make(Hkv * G, Hkv, pool, head_dim=d)
     out = torch.full((B, Hkv * G, d), -7.0, device="cuda")
-    ws = torch.full((A.adamas_full_attn_workspace_bytes(cfg, B, max(lens)),), 0xA5, dtype=torch.uint8, device="cuda")
+    ws = torch.full((A.adamas_full_attn_workspace_bytes(cfg, B, bound or max(lens)),), 0xA5, dtype=torch.uint8, device="cuda")
     A.adamas_full_attn(cfg, q.cuda(), K.cuda(), V.cuda(), torch.from_numpy(starts).cuda(),
-                       torch.tensor(lens, dtype=torch.int32).cuda(), out, max(lens), ws)
+                       torch.tensor(lens, dtype=torch.int32).cuda(), out, bound or max(lens), ws)
     ref = torch.zeros(B, Hkv * G, d, dtype=torch.float64)
     for b, L in enumerate(lens):
         for h in range(Hkv * G if L else 0):
@@ -43,7 +43,7 @@ def test_dense_attention_at_the_edges_of_its_steps(G, d):
     # A score is a sum of d products with |k| about 3: it is off by at most (d + 1) * 2^-23 * sum |q k| (each
     # of its additions and the alignment inside the matrix instruction lose less than 2^-23 of what they add),
     # about 3 * 0.64 * d * 2^-23 * (d + 1); divided by sqrt(d) that is the relative error of a weight, which
-    # moves the output by at most that times the largest |V| (below 6).  At d = 256: 0.0023 * 6.
+    # moves the output by at most that times the largest |V| (below 6).  At d = 256: 0.00094 * 6.
     bound = 6 * 1.92 * d * (d + 1) / d ** 0.5 * 2.0 ** -23
     assert float((out - ref).abs().max()) <= bound
     assert float((out - ref).norm() / ref.norm()) <= 4e-6    # typical: 1e-6, as with fp32 sums in any order
@@ -66,3 +66,12 @@ def test_dense_attention_with_elements_that_are_not_finite(G):
     fine[0, :G, 3] = fine[1, G:, 9] = fine[2, :G, 0] = False
     assert torch.isfinite(out[fine]).all()
     assert float((out - ref)[fine].abs().max()) < 1e-3
+
+
+@pytest.mark.parametrize("bound", [513, 768, 5000, 65536, 100001, 1 << 20])
+def test_dense_attention_of_lengths_far_below_the_bound(bound):
+    """The splits follow each sequence's own length, whatever max_seq_len allows for."""
+    out, ref = run(4, 128, LENS, 7, bound=bound)
+    assert float((out - ref).abs().max()) <= 6 * 1.92 * 128 * 129 / 128 ** 0.5 * 2.0 ** -23      # as above
+    assert float((out - ref).norm() / ref.norm()) <= 4e-6
+    assert torch.all(out[LENS.index(0)] == 0)
