@@ -294,19 +294,24 @@ struct FullPlan {
   size_t total;
 };
 
-// Workgroups for two per compute unit, where up to half as many planes as compute units share them; for four beyond, where a
-// plane's few splits are long and unequal sequences would leave compute units idle.  At 2 / 4 / 8 per unit, us:
-//   d = 128, group of four: 8 planes of 131072 tokens 96.8 / 101.8 / 109.8; 128 ragged planes of up to 8192 78.2 / 84.5 /
-//     80.0; 160 of up to 10000 114.4 / 112.1 / 106.2; 224 of up to 10594 174.4 / 162.0 / 153.0; 384 of up to 6001
-//     164.6 / 167.7 / 167.6; 800 planes of 3000 239.1 / 231.9 / 227.9
-//   d = 256, group of eight (one workgroup fits a compute unit): 8 of 131072 187.9 / 200.1 / 224.0; 160 ragged 236.0 /
-//     232.9 / 239.1; 192 of up to 6001 166.0 / 168.3 / 173.3; 400 of 3000 255.9 / 234.7 / 253.0
-// (eight would gain up to 6 % at d = 128 beyond 128 planes and lose up to 8 % at d = 256).
+// As many splits as give at most two workgroups per compute unit, for up to half as many planes as compute units
+// (one more split would give some compute units three, and every split its share less: 96 planes in five and six); at most
+// six beyond, where a plane's few splits are long and unequal sequences would leave compute units idle.  At most 2 / 4 / 6 /
+// 8 per unit, us, d = 128 with a group of four | d = 256 with a group of eight (one workgroup fits a compute unit):
+//     8 planes of 100000 tokens     74.8  86.0  85.2  84.6 | 148.3 179.3 179.1 187.1
+//    80 of 12000                    88.5  89.7  92.0  92.7 | 173.6 180.5 179.7 199.2
+//    96 of 9000 (six splits: 89.4)  82.4  85.3  86.5  83.2 | 159.8 172.0 171.3 174.9
+//   136 of 9000                    112.5 119.5 111.0 118.6 | 221.5 243.3 224.5 236.8
+//   384 ragged, up to 5000         134.0 130.5 138.1 133.3 | 266.1 249.0 241.5 223.1
+//   960 ragged, up to 500           45.3  45.3  44.6  51.1 |  91.6  88.4  91.4 125.9
+// Over all of 8 to 1920 planes, d = 64 to 256, groups of one, four and eight: two is fastest up to 128 planes; beyond, six is
+// within 1 % of the fastest on average and its worst case the least slow.
 FullPlan make_full_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len) {
   FullPlan fp{};
   const int64_t planes = (int64_t)batch * c->num_kv_heads;
-  const int per_unit = planes > kTargetWorkgroups / 2 ? 4 : 2;
-  int64_t want = (per_unit * kTargetWorkgroups + planes - 1) / planes;
+  const int per_unit = planes > kTargetWorkgroups / 2 ? 6 : 2;
+  int64_t want = per_unit * kTargetWorkgroups / planes;
+  if (want < 1) want = 1;
   if (want > kFullMaxSplits) want = kFullMaxSplits;
   const int64_t granules = (max_seq_len + kFullGranule - 1) / kFullGranule;
   const int64_t per = (granules + want - 1) / want;
