@@ -197,6 +197,10 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
   constexpr int U = 4;
   const int wave_grp = __builtin_amdgcn_readfirstlane(wave) * (kWave / LPR);  // first lane group of the wave
   n = __builtin_amdgcn_readfirstlane(n);
+  // Nothing that the rows' registers could wait for is left in flight (vmcnt = 0).  Said here, because the compiler would
+  // otherwise put that wait between the requests of a batch where it comes too late: a round trip in every batch
+  // (paged, 240 heads of 1160 rows: 81 us a step instead of 74).
+  __builtin_amdgcn_s_waitcnt(0x0f70);
   for (int b0 = 0; b0 + wave_grp < n; b0 += kGroups * U) {
     const int i0 = b0 + grp;
     // Row slots are filled in order, so one that the wave's first group does not use
@@ -231,7 +235,10 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
       double s[kRows];
 #pragma unroll
       for (int v = 0; v < kRows; ++v) {
-        const uint4 k4 = kv[u0 + v];
+        uint4 k4 = kv[u0 + v];
+        // (opaque in the path of a single row, or the compiler moves what it shares with the path of two
+        // in front of the branch and the chains of the two rows run one after the other)
+        if constexpr (kRows == 1) asm("" : "+v"(k4.x), "+v"(k4.y), "+v"(k4.z), "+v"(k4.w));
         // two chains of four: the additions of a chain wait for each other
         double s1 = qf[0] * (double)bf16_lo(k4.x), s2 = qf[1] * (double)bf16_hi(k4.x);
         s1 = fma(qf[2], (double)bf16_lo(k4.y), s1);
@@ -246,22 +253,26 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
       for (int v = 0; v < kRows; ++v) {
         // summed over the row's aligned group of 8, 16 or 32 lanes
         s[v] = lanes_sum_f64<LPR>(s[v]) * scale_log2e;
+        if constexpr (kRows == 1) asm("" : "+v"(s[v]));
         if (ok[u0 + v]) sc[u0 + v] = s[v];
         mn = fmaxf(mn, (float)sc[u0 + v]);
       }
     };
-    auto weigh = [&](int u) {
+    auto weigh = [&](int u0, auto rows_) {
 #pragma clang fp contract(off)
-      const float pw = ok[u] ? exp2_neg((float)(sc[u] - (double)mn)) : 0.f;
-      l += pw;
-      acc[0] = fmaf(pw, bf16_lo(vv[u].x), acc[0]);
-      acc[1] = fmaf(pw, bf16_hi(vv[u].x), acc[1]);
-      acc[2] = fmaf(pw, bf16_lo(vv[u].y), acc[2]);
-      acc[3] = fmaf(pw, bf16_hi(vv[u].y), acc[3]);
-      acc[4] = fmaf(pw, bf16_lo(vv[u].z), acc[4]);
-      acc[5] = fmaf(pw, bf16_hi(vv[u].z), acc[5]);
-      acc[6] = fmaf(pw, bf16_lo(vv[u].w), acc[6]);
-      acc[7] = fmaf(pw, bf16_hi(vv[u].w), acc[7]);
+#pragma unroll
+      for (int u = u0; u < u0 + decltype(rows_)::value; ++u) {
+        const float pw = ok[u] ? exp2_neg((float)(sc[u] - (double)mn)) : 0.f;
+        l += pw;
+        acc[0] = fmaf(pw, bf16_lo(vv[u].x), acc[0]);
+        acc[1] = fmaf(pw, bf16_hi(vv[u].x), acc[1]);
+        acc[2] = fmaf(pw, bf16_lo(vv[u].y), acc[2]);
+        acc[3] = fmaf(pw, bf16_hi(vv[u].y), acc[3]);
+        acc[4] = fmaf(pw, bf16_lo(vv[u].z), acc[4]);
+        acc[5] = fmaf(pw, bf16_hi(vv[u].z), acc[5]);
+        acc[6] = fmaf(pw, bf16_lo(vv[u].w), acc[6]);
+        acc[7] = fmaf(pw, bf16_hi(vv[u].w), acc[7]);
+      }
     };
     constexpr std::integral_constant<int, 1> kOne{};
     constexpr std::integral_constant<int, 2> kTwo{};
@@ -279,14 +290,8 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
     l *= corr;
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] *= corr;
-    weigh(0);
-    if (used >= 2) {
-      weigh(1);
-      if (used > 2) {
-        weigh(2);
-        if (used > 3) weigh(3);
-      }
-    }
+    weigh(0, kTwo);
+    if (used > 2) weigh(2, kTwo);
   }
   trace.stamp(kSelAttended);
 
