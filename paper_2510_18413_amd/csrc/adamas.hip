@@ -526,25 +526,25 @@ int adamas_sparse_attn(const adamas_config* cfg, const void* q, const void* K, c
   ap.Hkv = cfg->num_kv_heads;
   ap.k = k;
   ap.group_magic = group_magic_of(cfg);
-  // About 32 rows per workgroup, at most kMaxParts workgroups per head; half as many where there are as many heads
-  // as compute units (and up to eight times as many rows as heads).  One workgroup per head, which needs no merge launch,
-  // where there are at least as many heads as compute units and as rows, up to 512 rows.  Powers of two: with 11 or 6
-  // workgroups per head, 96 and 192 heads of 2048 rows take 22.9 and 37.8 us instead of 17.4 and 30.3 (d = 128).
-  // us at 1 / 4 / 8 / 16 workgroups per head, d = 64, 128, 256 (chosen: * of those measured):
-  //   192 heads, 2048 rows   27.3  20.9  16.9  19.2*   54.3  33.3  28.8  30.3*   107.2  60.9  55.3  57.3*
+  // About 32 rows per workgroup, at most kMaxParts workgroups per head; half as many from half as many heads as
+  // compute units on.  One workgroup per head, which needs no merge launch, where there are at least as many heads as
+  // compute units and as rows, up to 512 rows.  Powers of two: with 11 or 6 workgroups per head, 96 and 192 heads of 2048
+  // rows take 22.9 and 37.8 us instead of 17.4 and 30.3 (d = 128).
+  // us at 1 / 4 / 8 / 16 workgroups per head, d = 64, 128, 256 (chosen: *):
+  //    96 heads, 2048 rows   26.1  14.5  12.1  12.5*   51.5  22.1  18.0  17.4*   101.6  35.2  28.0  29.2*
+  //   128 heads,  512 rows    9.0   8.5   8.2*  9.9    14.5  11.6  11.4* 11.7     25.1  16.7  16.4* 16.7
+  //   128 heads, 1024 rows   15.2  11.5  11.2* 12.0    27.2  16.5  15.8* 15.3     49.8  25.2  24.1* 24.3
+  //   192 heads, 2048 rows   27.3  20.9  16.9* 19.2    54.3  33.3  28.8* 30.3    107.2  60.9  55.3* 57.3
   //   256 heads,  256 rows    6.5*  8.6  10.2  13.7    10.4* 11.9  12.2  13.6     16.1* 17.1  17.2  18.3
-  //   256 heads, 2048 rows   28.1  25.6  21.3* 22.9    58.0  44.8  40.0* 39.9    109.7  81.8  73.9* 76.4
-  //   256 heads, 4000 rows   54.5  37.4  30.6  30.0*  106.5  73.0  62.9  60.7*   203.0 133.3 111.3 113.6*
+  //   256 heads, 4000 rows   54.5  37.4  30.6* 30.0   106.5  73.0  62.9* 60.7    203.0 133.3 111.3* 113.6
   //   512 heads,  512 rows   15.5* 17.4  17.8  23.5    24.4* 26.8  26.5  28.4     48.1* 52.7  53.5  54.0
   //   512 heads, 1500 rows   36.4  33.8  32.4* 35.2    69.3  69.4  62.2* 63.9    121.5 119.9 114.9* 117.4
   //  1024 heads, 2048 rows   84.9  79.0  74.5* 82.2   164.6 155.9 141.0* 146.1   319.1 291.3 270.0* 277.5
   const int64_t n_heads = (int64_t)batch * cfg->num_q_heads;
+  const int most = n_heads >= kTargetWorkgroups / 2 ? kMaxParts / 2 : kMaxParts;
   int parts = (k + 31) / 32;
-  if (parts > kMaxParts) parts = kMaxParts;
-  if (n_heads >= kTargetWorkgroups) {
-    if (n_heads >= k && k <= 512) parts = 1;
-    else if (8 * n_heads >= k && parts > kMaxParts / 2) parts = kMaxParts / 2;
-  }
+  if (parts > most) parts = most;
+  if (n_heads >= kTargetWorkgroups && n_heads >= k && k <= 512) parts = 1;
   ap.chunk = (k + parts - 1) / parts;
   ap.n_parts = (k + ap.chunk - 1) / ap.chunk;
   ap.scale_log2e = scale_log2e(cfg);
