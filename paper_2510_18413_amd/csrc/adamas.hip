@@ -290,31 +290,37 @@ void launch_scan(const adamas_config* c, bool fused, const Plan& pl, int batch, 
 }
 
 struct FullPlan {
-  int n_splits;
+  int n_splits, chunk;
+  int64_t short_len;  // sequences up to this long are cut by their own length (FullAttnParams)
   size_t total;
 };
 
 // As many splits as give at most two workgroups per compute unit, for up to half as many planes as compute units
-// (one more split would give some compute units three, and every split its share less: 96 planes in five and six); at most
-// six beyond, where a plane's few splits are long and unequal sequences would leave compute units idle.  At most 2 / 4 / 6 /
-// 8 per unit, us, d = 128 with a group of four | d = 256 with a group of eight (one workgroup fits a compute unit):
-//     8 planes of 100000 tokens     74.8  86.0  85.2  84.6 | 148.3 179.3 179.1 187.1
-//    80 of 12000                    88.5  89.7  92.0  92.7 | 173.6 180.5 179.7 199.2
-//    96 of 9000 (six splits: 89.4)  82.4  85.3  86.5  83.2 | 159.8 172.0 171.3 174.9
-//   136 of 9000                    112.5 119.5 111.0 118.6 | 221.5 243.3 224.5 236.8
-//   384 ragged, up to 5000         134.0 130.5 138.1 133.3 | 266.1 249.0 241.5 223.1
-//   960 ragged, up to 500           45.3  45.3  44.6  51.1 |  91.6  88.4  91.4 125.9
-// Over all of 8 to 1920 planes, d = 64 to 256, groups of one, four and eight: two is fastest up to 128 planes; beyond, six is
-// within 1 % of the fastest on average and its worst case the least slow.
+// (one more split would give some compute units three, and every split its share less: 96 planes in five and six); about
+// four beyond, where a plane's few splits are long and unequal sequences would leave compute units idle.  A split covers
+// a multiple of 256 tokens, two of them at least where there is a plane for every compute unit.  At 2 / 4 / 8 per unit, us:
+//                               d = 128, group of four | d = 256, group of eight (one workgroup fits a compute unit)
+//     8 planes of 100000 tokens     74.8  86.0  84.6   | 148.3 179.3 187.1
+//    80 of 12000 (seven: 100.2)     88.5  89.7  92.7   | 173.6 180.5 199.2
+//    96 of 9000 (six: 89.4)         82.4  85.3  83.2   | 159.8 172.0 174.9
+//   192 ragged, up to 8000         123.8 109.4 110.4   | 182.1 189.7 192.3
+//   320 of 6000                    176.2 169.4 175.5   |
+//   512 of 4000                    175.3 180.7 187.0   |
+//   640 ragged, up to 3000         140.7 136.5 127.6   | 262.0 263.9 255.7
+//   960 ragged, up to 500           45.4  50.5  51.1   |  92.8 123.2 125.9   (256 tokens each at 4 and 8)
 FullPlan make_full_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len) {
   FullPlan fp{};
   const int64_t planes = (int64_t)batch * c->num_kv_heads;
-  const int per_unit = planes > kTargetWorkgroups / 2 ? 6 : 2;
-  int64_t want = per_unit * kTargetWorkgroups / planes;
-  if (want < 1) want = 1;
+  int64_t want = planes > kTargetWorkgroups / 2 ? (4 * kTargetWorkgroups + planes - 1) / planes : 2 * kTargetWorkgroups / planes;
   if (want > kFullMaxSplits) want = kFullMaxSplits;
   const int64_t granules = (max_seq_len + kFullGranule - 1) / kFullGranule;
-  const int64_t per = (granules + want - 1) / want;
+  int64_t per = (granules + want - 1) / want;
+  if (per < 2 && planes >= kTargetWorkgroups) per = 2;
+  fp.chunk = (int)per * kFullGranule;
+  // Where the splits do not come out at two per compute unit, every sequence fills all of them (96 planes ragged, up to 9000, d =
+  // 256, group of one: 102.0 us, 126.7 if only those below a third do).  Otherwise see full_attn_kernel.
+  const bool even = planes > kTargetWorkgroups / 2 || 2 * kTargetWorkgroups % planes == 0;
+  fp.short_len = even ? max_seq_len / 3 : max_seq_len;
   fp.n_splits = (int)((granules + per - 1) / per);
   fp.total = align256((size_t)batch * c->num_q_heads * fp.n_splits * partial_stride(c->head_dim) * sizeof(float));
   return fp;
@@ -773,6 +779,8 @@ int adamas_full_attn(const adamas_config* cfg, const void* q, const void* K, con
   fp.Hq = cfg->num_q_heads;
   fp.Hkv = cfg->num_kv_heads;
   fp.n_splits = pl.n_splits;
+  fp.chunk = pl.chunk;
+  fp.short_len = (int)pl.short_len;
   fp.splits_magic = magic_of((uint32_t)pl.n_splits);
   fp.scale_log2e = (float)scale_log2e(cfg);
   const dim3 grid(pl.n_splits, cfg->num_kv_heads, batch);
