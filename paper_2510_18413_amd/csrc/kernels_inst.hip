@@ -66,12 +66,15 @@ void launch_select(bool attn, bool paged, dim3 grid, hipStream_t st, const Selec
 // does not instantiate their kernels either.
 // Whether a bulk encode with the transform goes to encode_rows_matrix_kernel.  Lane groups / matrix cores, us, for
 // 8000, 40000, 160000 and 640000 vectors of two-bit codes with symmetric thresholds:
-//   D =  64   3.1 / 2.8   3.8 / 3.5   6.5 / 6.6   18.8 / 16.8   (unsymmetric at 160000 7.1 / 7.4)
+//   D =  64   3.1 / 2.8   3.8 / 3.5   6.5 / 6.6   18.8 / 16.8
 //   D =  96   4.0 / 5.1   6.0 / 6.9  13.1 / 12.7  45.5 / 33.3   (operands to LDS first: 1 us)
 //   D = 128   3.5 / 3.5   5.5 / 5.1  11.6 / 10.8  37.2 / 35.6   and 56.9 / 58.3 for 1 Mi
-//   D = 160   6.6 / 10.2 10.7 / 13.0 27.4 / 28.7  90.7 / 74.6
-//   D = 192   5.2 / 7.2  11.1 / 10.6 33.3 / 23.4 114.4 / 67.7
+//   D = 160   6.6 / 10.2 10.7 / 13.0 27.4 / 28.7  90.7 / 71.9
+//   D = 192   5.2 / 7.2  11.1 / 10.6 33.3 / 23.4 114.4 / 64.5
 //   D = 256   4.9 / 6.0   8.9 / 9.0  24.3 / 21.8  86.0 / 71.2
+// At the limits below, one-bit codes and unsymmetric thresholds (other caches, so not comparable with the rows above):
+//   one bit      D =  64  32768: 4.5 / 4.3   96 196608: 17.6 / 14.5  160 393216: 55.2 / 43.8  192 65536: 14.8 / 12.2  256 196608: 29.2 / 26.5
+//   unsymmetric  D =  64 393216: 17.8 / 18.4 96 196608: 19.9 / 17.8  160 393216: 69.3 / 57.6  192 65536: 17.6 / 15.6  256 196608: 39.4 / 36.1
 // Three-bit codes (seven masks) and codes without the transform are slower there.
 template <int BITS_>
 constexpr bool has_matrix_encode() { return BITS_ <= 2 && D != 128; }
@@ -81,6 +84,21 @@ inline bool matrix_encode_pays(const Thresholds& thr, int64_t n_vec) {
   return n_vec >= (D == 192 ? 64 : D == 160 ? 384 : 192) * 1024;
 }
 
+// Workgroups of its grid.  Where they put operands in LDS first, as many as run at once: later ones would start a round of
+// their own and build the operands again.  Per compute unit, from the kernels' registers (94 to 216): D = 96 five
+// (unsymmetric two-bit codes four), 160 three (two), 192 four (one-bit codes three, unsymmetric two).  us for 1 Mi vectors with 512 /
+// 768 / 1024 / 1280 / 2560 workgroups, chosen *:
+//   D =  96  symmetric 62.1 54.6 54.0  52.8* 53.4   one bit  58.2 49.9  47.1  47.6* 48.5   unsymmetric  64.7  57.4  57.2* 62.1  58.9
+//   D = 160           115.1 106.8* 124.2 116.3 115.9        103.9 91.4* 109.8 99.2 101.4                123.1* 150.4 127.7 141.6 143.3
+//   D = 192           109.3 101.7 103.1* 109.7 101.2         98.9 90.2* 103.6 95.8  95.1                118.0* 143.9 121.5 131.0 127.9
+// Without operands in LDS smaller shares even out better (D = 256, symmetric: 126.5 / 129.1 / 139.5 / 134.9 / 125.9, 5120 119.0).
+template <int BITS_, bool SYMMETRIC>
+constexpr int64_t most_matrix_workgroups() {
+  if (!EncShape<D>::kLds) return 5120;
+  constexpr bool kUnsymmetric = BITS_ == 2 && !SYMMETRIC;
+  return 256 * (D == 96 ? (kUnsymmetric ? 4 : 5) : D == 160 ? (kUnsymmetric ? 2 : 3) : kUnsymmetric ? 2 : BITS_ == 1 ? 3 : 4);
+}
+
 template <int BITS_>
 void launch_encode_rows(hipStream_t st, const uint16_t* src, uint8_t* dst, int64_t head_stride_rows,
                         int64_t row_begin, int64_t n_rows, int64_t n_vec, const Thresholds& thr) {
@@ -88,14 +106,12 @@ void launch_encode_rows(hipStream_t st, const uint16_t* src, uint8_t* dst, int64
   if (n_vec < ((int64_t)1 << 32) && n_rows >= 1) by_rows = Divisor32::of((uint32_t)n_rows);
   if constexpr (has_matrix_encode<BITS_>()) {
     if (matrix_encode_pays(thr, n_vec)) {
-      // 64 vectors per workgroup and step.  Five workgroups fit a compute unit; where they put operands in LDS
-      // first, that many (D = 96, 1 Mi rows: 1280 / 2560 / 5120 workgroups 51.3 / 52.1 / 53.8 us), otherwise
-      // smaller shares even out better (D = 128: 61.2 / 60.8 / 58.2).
-      constexpr int64_t kMost = EncShape<D>::kLds ? 1280 : 5120;
+      // 64 vectors per workgroup and step
       const int64_t want = (n_vec + 63) / 64;
-      const int grid = (int)(want < kMost ? want : kMost);
-      const int64_t step_heads = (int64_t)grid * 64 / n_rows, step_rows = (int64_t)grid * 64 % n_rows;
       auto launch = [&](auto symmetric) {
+        constexpr int64_t kMost = most_matrix_workgroups<BITS_, decltype(symmetric)::value>();
+        const int grid = (int)(want < kMost ? want : kMost);
+        const int64_t step_heads = (int64_t)grid * 64 / n_rows, step_rows = (int64_t)grid * 64 % n_rows;
         hipLaunchKernelGGL((encode_rows_matrix_kernel<BITS_, D, decltype(symmetric)::value>), dim3(grid), dim3(256), 0,
                            st, src, dst, head_stride_rows, row_begin, n_rows, n_vec, thr, by_rows, step_heads, step_rows);
       };
