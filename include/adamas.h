@@ -335,10 +335,17 @@ int adamas_decode_step_paged(const adamas_config *cfg, const void *q,
  * every sequence (dense decode attention), the baseline of the paper's
  * "self-attention speedup" (Sec. 4.3), so that both sides of that ratio can be
  * measured on one GPU.  q bf16 [batch][Hq][128]; K, V pools as above;
- * out fp32 [batch][Hq][128] (zeros for an empty sequence).  Workspace:
- * adamas_full_attn_workspace_bytes(cfg, batch, max_seq_len) bytes, 256-byte
- * aligned, no initialisation needed.  Same argument checks and error codes as
- * adamas_sparse_attn.
+ * out fp32 [batch][Hq][128] (zeros for an empty sequence).  Arithmetic: fp32,
+ * not the fp64 scores of the sparse calls.  A score is a sum of exact products
+ * of bf16 numbers, added in fp32 inside the matrix instruction with a partial
+ * sum per 32 dims (64 at head_dim 256): no further from the exact score than a
+ * chain of fp32 multiply-adds.  Weights are fp32 numbers of at most 1 (below
+ * 2^-126 they count as zero) and multiply V with all their bits.  Their sums
+ * are fp32 and divided by the sum of the weights only at the end: what they
+ * reach (weights, at most 1 each, times V) has to be in the range of fp32.
+ * Workspace: adamas_full_attn_workspace_bytes(cfg, batch, max_seq_len) bytes
+ * for the same cfg, batch and max_seq_len, 256-byte aligned, no initialisation
+ * needed.  Same argument checks and error codes as adamas_sparse_attn.
  */
 size_t adamas_full_attn_workspace_bytes(const adamas_config *cfg, int32_t batch,
                                         int64_t max_seq_len);

@@ -627,7 +627,7 @@ __global__ __launch_bounds__(256) void encode_rows_kernel(const uint16_t* __rest
 // What bounds it: HBM at D = 64 and 256 (5.0 and 5.2 TB/s of 1 Mi rows; a copy reaches 5.1), at the others the
 // comparisons and the additions that join the chunks.  The lane-group kernel above is bound by the issue of its
 // butterflies.  Lane groups -> matrix cores, us for 640000 rows: D = 64 18.8 -> 16.8, 96 45.5 -> 33.3,
-// 160 90.7 -> 74.6, 192 114.4 -> 67.7, 256 86.0 -> 71.2 (D = 128 37.2 -> 35.6, but 56.9 -> 58.3 for 1 Mi rows:
+// 160 90.7 -> 71.9, 192 114.4 -> 64.5, 256 86.0 -> 71.2 (D = 128 37.2 -> 35.6, but 56.9 -> 58.3 for 1 Mi rows:
 // both at the rate of a copy, and a row is read in pieces of 64 bytes here).
 template <int D>
 struct EncShape {
