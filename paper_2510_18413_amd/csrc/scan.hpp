@@ -6,9 +6,9 @@
 // (sequence, KV head) and evaluates all G query heads of that KV head's
 // group on it, so every code row is fetched once.  It writes
 //   - one distance per (query head, token), staged through LDS so that a lane
-//     stores four consecutive tokens: a byte each (plus one bit per token in a
-//     plane of ninth bits, written straight from wave ballots) when the metric's
-//     distances stay below 512, as Eq. 6 does (0..384); uint16 otherwise, and
+//     stores eight consecutive tokens: a byte each (plus one bit per token in a
+//     plane of ninth bits) when the metric's distances stay below 512, as Eq. 6
+//     does (0..384); uint16 otherwise, and
 //   - one histogram of those distances (385 bins for Eq. 6) per (query head, tile),
 // both with plain stores: nothing needs zero-initialised memory and the
 // result does not depend on the order workgroups run in.
@@ -101,14 +101,19 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   constexpr int kPairs = Fmt::kPairs;  // 32-bit words of a histogram: two 16-bit bins each
   constexpr bool kWideBins = hist_wide_bins(G);
   constexpr int kHistWords = kWideBins ? 2 * kPairs : kPairs;  // LDS words of one histogram copy
-  __shared__ uint32_t s_hist[G][kHistReplicas][kHistWords];
+  // [G][kHistReplicas][kHistWords], rounded up to whole 16-byte pieces
+  constexpr int kHistTotal = (G * kHistReplicas * kHistWords + 3) & ~3;
+  __shared__ __align__(16) uint32_t s_hist[kHistTotal];
   // per query head: plane p of word wd at [W * p + wd]; 2-bit codes also keep lo^hi at [2W + wd]
   __shared__ uint32_t s_q[G][3 * W];
   __shared__ uint32_t s_new[kRowWords];  // code row of the appended key, as stored
   __shared__ uint32_t s_ready;      // query / new-key code rows published so far
-  // per wave: its 256 distances per query head, in token order, for wide stores
-  using DistT = typename std::conditional<Fmt::kByteDist, uint8_t, uint16_t>::type;
-  __shared__ __align__(8) DistT s_dt[WAVES][G][kScanTokPerThread * kWave];
+  // Up to 24 words of query planes at a time: the heads of a group are served in passes (see below).
+  constexpr int QP = BITS == 2 ? 3 : BITS;
+  constexpr bool kPlanesInVgprs = G * QP * W <= 24;
+  constexpr int kPassHeads = kPlanesInVgprs ? G : (24 / (QP * W) > 0 ? 24 / (QP * W) : 1);
+  // per wave: its 256 distances to each query head of a pass, in token order
+  __shared__ __align__(16) uint16_t s_dt[WAVES][kPassHeads][kScanTokPerThread * kWave];
 
   // blockIdx.y = KV head * g_split + part: the G query heads of this workgroup are
   // part `gsub` of the KV head's group of G * g_split (the parts re-read the rows).
@@ -170,8 +175,8 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   // the waves must not wait for each other: a compute unit serves memory
   // requests in order, so late waves get their rows late, and a barrier after
   // the row loads would hold the early waves back with them.
-  for (int i = tid; i < G * kHistReplicas * kHistWords; i += nthreads)
-    (&s_hist[0][0][0])[i] = 0u;
+  for (int i = tid; i < kHistTotal / 4; i += nthreads)
+    reinterpret_cast<uint4*>(s_hist)[i] = make_uint4(0u, 0u, 0u, 0u);
   if (tid == 0) s_ready = 0u;
   __syncthreads();
 
@@ -208,16 +213,17 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   for (int i = 0; i < kScanTokPerThread; ++i) {
     // Unconditional: a lane past the end re-reads the last row (masked at use).
     // A branch here would make the compiler wait for all loads at once.
-    int64_t r;
+    // A wave-uniform base and a 32-bit offset per lane (a sequence's rows span less than 2^27 bytes).
+    const int t = min(t0 + (wave * kScanTokPerThread + i) * kWave + lane, L - 1);
+    const uint8_t* base = plane;
+    uint32_t in_base = (uint32_t)t;
     if constexpr (PAGED) {
-      // a page number outside the pool is clamped into it; lanes past the end read row 0
-      const int t = t0 + (wave * kScanTokPerThread + i) * kWave + lane;
+      // a page number outside the pool is clamped into it; a lane past the end reads some row of the page
       const int64_t pg = min(max((int64_t)pte[i], (int64_t)0), (p.pool_tokens >> p.page_shift) - 1);
-      r = t < L ? (pg << p.page_shift) + (t & ((1 << p.page_shift) - 1)) : 0;
-    } else {
-      r = min(t0 + (wave * kScanTokPerThread + i) * kWave + lane, L - 1);
+      base += (pg << p.page_shift) * kRowBytes;
+      in_base = (uint32_t)t & ((1u << p.page_shift) - 1u);
     }
-    const uint8_t* row = plane + r * kRowBytes;
+    const uint8_t* row = base + in_base * (uint32_t)kRowBytes;
 #pragma unroll
     for (int c = 0; c < C; ++c) load_piece<kPiece>(row + c * kPiece, &rr[i][c * (kPiece / 4)]);
   }
@@ -290,159 +296,147 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   // waves a compute unit holds (measured: the only resource the dispatcher
   // reports as full, with about four waves per SIMD resident).
   // qp[g][j][wd]: plane j of word wd; for 2-bit codes j = 2 is lo ^ hi.
-  constexpr int QP = BITS == 2 ? 3 : BITS;
-  constexpr bool kPlanesInVgprs = G * QP * W <= 24;
-  constexpr int kPassHeads = kPlanesInVgprs ? G : (24 / (QP * W) > 0 ? 24 / (QP * W) : 1);
-  uint32_t* hist_lane = &s_hist[0][lane & (kHistReplicas - 1)][0];
-
-  // Ninth bits (byte planes of distances up to 511): the ballot of step i over the
-  // wave's 64 tokens is one word of the plane; lane i keeps the word of step i.
-  uint32_t high_lo[G], high_hi[G];
-#pragma unroll
-  for (int g = 0; g < G; ++g) high_lo[g] = high_hi[g] = 0u;
-#pragma unroll
-  for (int g0 = 0; g0 < G; g0 += kPassHeads) {
-  uint32_t qp[kPassHeads][QP][W];
-#pragma unroll
-  for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
-#pragma unroll
-    for (int j = 0; j < QP; ++j) {
+  uint32_t* hist_lane = s_hist + (lane & (kHistReplicas - 1)) * kHistWords;
+  // The distance of a key row (row[BITS * wd + pl]: plane pl of word wd) to the query with planes q(j, wd).
+  auto distance = [](const uint32_t (&row)[kRowWords], auto q) -> uint32_t {
+    if constexpr (BITS == 2) {
+      uint32_t c1 = 0, c2 = 0, c3 = 0;
 #pragma unroll
       for (int wd = 0; wd < W; ++wd) {
-        if constexpr (kPlanesInVgprs) qp[g - g0][j][wd] = s_q[g][W * j + wd];
-        else qp[g - g0][j][wd] = __builtin_amdgcn_readfirstlane(s_q[g][W * j + wd]);
+        // Every instruction below takes one query plane: with two of them in one
+        // instruction (the compiler's choice when it may merge them) a plane held
+        // in a scalar register must first be copied.  Hence the opaque values.
+        uint32_t xl = row[2 * wd] ^ q(0, wd);
+        asm("" : "+v"(xl));
+        uint32_t both = xl & q(2, wd);
+        asm("" : "+v"(both));
+        const uint32_t u = (row[2 * wd + 1] ^ q(1, wd)) & ~both;
+        // (and opaque running sums: the count instruction adds to them, a regrouped sum takes additions of its own)
+        c1 += __popc(xl);
+        c2 += __popc(u);
+        asm("" : "+v"(c1), "+v"(c2));
+        if constexpr (METRIC == kMetricL2) c3 += __popc(u & xl);
       }
+      return METRIC == kMetricL1 ? c1 + 2u * c2 : c1 + 4u * (c2 + c3);
+    } else if constexpr (BITS == 1) {
+      uint32_t c = 0;
+#pragma unroll
+      for (int wd = 0; wd < W; ++wd) c += __popc(row[wd] ^ q(0, wd));
+      return c;
+    } else {
+      // |a - b| of 3-bit codes on bit planes (a query, b key): subtract with
+      // borrow, then negate where the borrow out (a < b) is set.
+      uint32_t c0 = 0, c1 = 0, c2 = 0;
+#pragma unroll
+      for (int wd = 0; wd < W; ++wd) {
+        const uint32_t a0 = q(0, wd), a1 = q(1, wd), a2 = q(2, wd);
+        const uint32_t b0 = row[3 * wd], b1 = row[3 * wd + 1], b2 = row[3 * wd + 2];
+        const uint32_t d0 = a0 ^ b0, br1 = ~a0 & b0;
+        const uint32_t x1 = a1 ^ b1, d1 = x1 ^ br1, br2 = (~a1 & b1) | (~x1 & br1);
+        const uint32_t x2 = a2 ^ b2, d2 = x2 ^ br2, sg = (~a2 & b2) | (~x2 & br2);
+        const uint32_t e1 = d1 ^ sg, cy1 = ~d0 & sg;
+        const uint32_t r1 = e1 ^ cy1, cy2 = e1 & cy1;
+        const uint32_t r2 = d2 ^ sg ^ cy2;
+        c0 += __popc(d0);
+        c1 += __popc(r1);
+        c2 += __popc(r2);
+      }
+      return c0 + 2u * c1 + 4u * c2;
     }
-  }
-  auto qplane = [&](int g, int j, int wd) -> uint32_t { return qp[g - g0][j][wd]; };
+  };
+
+  uint32_t one = 1;  // (opaque: otherwise written anew for every use)
+  asm("" : "+v"(one));
 #pragma unroll
-  for (int i = 0; i < kScanTokPerThread; ++i) {
-    // keep the tokens in load order, so that each waits only for its own rows
-    if (g0 == 0) __builtin_amdgcn_sched_barrier(0);
-    const int t = t0 + (wave * kScanTokPerThread + i) * kWave + lane;
-    const uint64_t in_range = __builtin_amdgcn_ballot_w64(t < L);
-    // kw[BITS * wd + pl]: plane pl of word wd of the key row
-    uint32_t kw[kRowWords];
-#pragma unroll
-    for (int wq = 0; wq < kRowWords; ++wq) kw[wq] = rr[i][wq];
-    if (appending && t == L - 1) {
-#pragma unroll
-      for (int wq = 0; wq < kRowWords; ++wq) kw[wq] = s_new[wq];
-    }
+  for (int g0 = 0; g0 < G; g0 += kPassHeads) {
+    uint32_t qp[kPassHeads][QP][W];
 #pragma unroll
     for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
-      uint32_t d;
-      if constexpr (BITS == 2) {
-        uint32_t c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+      for (int j = 0; j < QP; ++j) {
 #pragma unroll
         for (int wd = 0; wd < W; ++wd) {
-          // Every instruction below takes one query plane: with two of them in one
-          // instruction (the compiler's choice when it may merge them) a plane held
-          // in a scalar register must first be copied.  Hence the opaque values.
-          uint32_t xl = kw[2 * wd] ^ qplane(g, 0, wd);
-          asm("" : "+v"(xl));
-          uint32_t both = xl & qplane(g, 2, wd);
-          asm("" : "+v"(both));
-          const uint32_t u = (kw[2 * wd + 1] ^ qplane(g, 1, wd)) & ~both;
-          c1 += __popc(xl);
-          c2 += __popc(u);
-          if constexpr (METRIC == kMetricL2) c3 += __popc(u & xl);
+          if constexpr (kPlanesInVgprs) qp[g - g0][j][wd] = s_q[g][W * j + wd];
+          else qp[g - g0][j][wd] = __builtin_amdgcn_readfirstlane(s_q[g][W * j + wd]);
         }
-        d = METRIC == kMetricL1 ? c1 + 2u * c2 : c1 + 4u * (c2 + c3);
-      } else if constexpr (BITS == 1) {
-        d = 0;
-#pragma unroll
-        for (int wd = 0; wd < W; ++wd) d += __popc(kw[wd] ^ qplane(g, 0, wd));
-      } else {
-        // |a - b| of 3-bit codes on bit planes (a query, b key): subtract with
-        // borrow, then negate where the borrow out (a < b) is set.
-        uint32_t c0 = 0, c1 = 0, c2 = 0;
-#pragma unroll
-        for (int wd = 0; wd < W; ++wd) {
-          const uint32_t a0 = qplane(g, 0, wd), a1 = qplane(g, 1, wd), a2 = qplane(g, 2, wd);
-          const uint32_t b0 = kw[3 * wd], b1 = kw[3 * wd + 1], b2 = kw[3 * wd + 2];
-          const uint32_t d0 = a0 ^ b0, br1 = ~a0 & b0;
-          const uint32_t x1 = a1 ^ b1, d1 = x1 ^ br1, br2 = (~a1 & b1) | (~x1 & br1);
-          const uint32_t x2 = a2 ^ b2, d2 = x2 ^ br2, sg = (~a2 & b2) | (~x2 & br2);
-          const uint32_t e1 = d1 ^ sg, cy1 = ~d0 & sg;
-          const uint32_t r1 = e1 ^ cy1, cy2 = e1 & cy1;
-          const uint32_t r2 = d2 ^ sg ^ cy2;
-          c0 += __popc(d0);
-          c1 += __popc(r1);
-          c2 += __popc(r2);
-        }
-        d = c0 + 2u * c1 + 4u * c2;
-      }
-      s_dt[wave][g][i * kWave + lane] = (DistT)d;
-      // ninth bits of 64 consecutive tokens = one word of the plane, straight from the ballot
-      if constexpr (Fmt::kHighPlane) {
-        const uint64_t word = __builtin_amdgcn_ballot_w64(d > 255u) & in_range;
-        write_lane(high_lo[g], (uint32_t)word, i);
-        write_lane(high_hi[g], (uint32_t)(word >> 32), i);
-      }
-      if constexpr (kWideBins) {
-        if (t < L) atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + d, 1u);
-      } else {
-        // two 16-bit bins per word: 1 for an even distance, 0x10000 for an odd one
-        // (opaque halves: otherwise the compiler turns them into a compare and a select)
-        uint32_t pair = d >> 1, odd16 = (d & 1u) << 4;
-        asm("" : "+v"(pair), "+v"(odd16));
-        if (t < L) atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + pair, 1u << odd16);
       }
     }
-  }
-  }  // passes over the heads of the group
-
-  trace.stamp(kScanRowsDone);
-  // Distances leave through LDS: a lane computed tokens 64 apart, but stores
-  // four consecutive tokens (8 bytes), so a wave writes 512 contiguous bytes
-  // per query head with one instruction instead of four 2-byte-per-lane ones.
-  // The region is private to the wave, so no barrier is needed.
-  // A row of the plane holds a multiple of 128 tokens, so a lane whose first
-  // token exists may store all four.
-  if constexpr (Fmt::kHighPlane) {
-    // The wave's kScanTokPerThread words of the ninth-bit plane are consecutive:
-    // lane i stores word i (64 tokens from t64), if that word holds tokens.
-    const int t64 = t0 + (wave * kScanTokPerThread + lane) * kWave;
-    if (p.dist != nullptr && lane < kScanTokPerThread && t64 < L) {
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-        p.dist_high[((int64_t)(head0 + g) * p.dist_stride + t64) >> 6] =
-            ((uint64_t)high_hi[g] << 32) | high_lo[g];
-    }
-  }
-  if (p.dist_user != nullptr) {  // the caller's own array of distances (adamas_distances)
 #pragma unroll
     for (int i = 0; i < kScanTokPerThread; ++i) {
+      // keep the tokens in load order, so that each waits only for its own rows
+      if (g0 == 0) __builtin_amdgcn_sched_barrier(0);
       const int t = t0 + (wave * kScanTokPerThread + i) * kWave + lane;
+      // The appended token's row is not in memory yet.  It takes the place of the loaded one once, before
+      // the first head (a copy of the row for every pass costs 64 moves per wave with a group of four).
+      if (g0 == 0 && appending) {
+        if (t == L - 1) {
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        uint32_t d = s_dt[wave][g][i * kWave + lane];
-        if constexpr (Fmt::kHighPlane) {
-          const uint32_t w_lo = (uint32_t)__builtin_amdgcn_readlane((int)high_lo[g], i);
-          const uint32_t w_hi = (uint32_t)__builtin_amdgcn_readlane((int)high_hi[g], i);
-          d |= (((lane < 32 ? w_lo : w_hi) >> (lane & 31)) & 1u) << 8;
+          for (int wq = 0; wq < kRowWords; ++wq) rr[i][wq] = s_new[wq];
         }
-        if (t < L) p.dist_user[(int64_t)(head0 + g) * p.dist_user_stride + t] = (uint16_t)d;
+      }
+      if (t < L) {
+#pragma unroll
+        for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
+          const uint32_t d = distance(rr[i], [&](int j, int wd) { return qp[g - g0][j][wd]; });
+          s_dt[wave][g - g0][i * kWave + lane] = (uint16_t)d;
+          if constexpr (kWideBins) {
+            atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + d, one);
+          } else {
+            // two 16-bit bins per word: 1 for an even distance, 0x10000 for an odd one
+            // (opaque halves: otherwise the compiler turns them into a compare and a select)
+            uint32_t pair = d >> 1, odd16 = (d & 1u) << 4;
+            asm("" : "+v"(pair), "+v"(odd16));
+            atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + pair, 1u << odd16);
+          }
+        }
       }
     }
-  }
-  if (p.dist != nullptr) {
-    const int tt = t0 + wave * (kScanTokPerThread * kWave) + kScanTokPerThread * lane;
-    if (tt < L) {
+    if (g0 + kPassHeads >= G) trace.stamp(kScanRowsDone);
+    // The distances of the pass leave through LDS: a lane computed tokens 64 apart, but stores eight consecutive ones.
+    // Byte planes: the low bytes of its eight are picked with two byte permutes, the ninth bits with two permutes and two dot
+    // products (weights 1, 2, 4 ... 128).  For 64 tokens of a head that is less than one instruction; a ballot and
+    // two lane writes per 64 tokens took three of 27.  (Words of ninth bits computed only where a distance above 255 occurs,
+    // by a second walk over the rows: 51.8 instead of 44.3 us a layer for 16 ragged sequences; such distances are common
+    // where a few channels of the keys are large.)  With the copies of the rows, the masks and the flush below
+    // this loop went from about 30 to 23 vector instructions per 64 tokens and head: 16.1 -> 15.3 us a layer for one sequence
+    // of 32771 tokens and G = 4, 34.9 -> 33.9 for four of 60001 and G = 8, 45.4 -> 44.3 for 16 ragged ones and G = 4.
+    // The region is private to the wave, so no barrier is needed.  A row of the planes holds a multiple of
+    // 128 tokens, so a lane whose first token exists may store all eight.
+    constexpr int kLanes = kScanTokPerThread * kWave / 8;  // lanes per head
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int64_t at = (int64_t)(head0 + g) * p.dist_stride + tt;
+    for (int c = 0; c < (kPassHeads * kLanes + kWave - 1) / kWave; ++c) {
+      const int at = c * kWave + lane, g = g0 + at / kLanes;
+      const int tt = t0 + wave * (kScanTokPerThread * kWave) + 8 * (at % kLanes);
+      if (p.dist != nullptr && at < kPassHeads * kLanes && g < G && tt < L) {
+        uint32_t v[4];
+        __builtin_memcpy(v, __builtin_assume_aligned(&s_dt[wave][0][0] + 8 * at, 16), 16);
+        const int64_t to = (int64_t)(head0 + g) * p.dist_stride + tt;
         if constexpr (Fmt::kByteDist) {
-          *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.dist) + at) =
-              *reinterpret_cast<const uint32_t*>(&s_dt[wave][g][kScanTokPerThread * lane]);
+          uint2 low;
+          low.x = __builtin_amdgcn_perm(v[1], v[0], 0x06040200u);
+          low.y = __builtin_amdgcn_perm(v[3], v[2], 0x06040200u);
+          *reinterpret_cast<uint2*>(static_cast<uint8_t*>(p.dist) + to) = low;
         } else {
-          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.dist) + at) =
-              *reinterpret_cast<const uint2*>(&s_dt[wave][g][kScanTokPerThread * lane]);
+          *reinterpret_cast<uint4*>(static_cast<uint16_t*>(p.dist) + to) = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+        if constexpr (Fmt::kHighPlane) {
+          uint32_t high = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(v[1], v[0], 0x07050301u), 0x08040201u, 0u, false);
+          high = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(v[3], v[2], 0x07050301u), 0x80402010u, high, false);
+          reinterpret_cast<uint8_t*>(p.dist_high)[to >> 3] = (uint8_t)high;
         }
       }
     }
-  }
+    if (p.dist_user != nullptr) {  // the caller's own array of distances (adamas_distances)
+#pragma unroll 1
+      for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
+#pragma unroll
+        for (int i = 0; i < kScanTokPerThread; ++i) {
+          const int t = t0 + (wave * kScanTokPerThread + i) * kWave + lane;
+          if (t < L) p.dist_user[(int64_t)(head0 + g) * p.dist_user_stride + t] = s_dt[wave][g - g0][i * kWave + lane];
+        }
+      }
+    }
+  }  // passes over the heads of the group
 
   trace.stamp(kScanDistStored);
   // Algorithm 1, cache update: the new token's K, V and code row enter the cache.  The
@@ -465,15 +459,21 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   }
   if (p.tilehist != nullptr) {
     __syncthreads();
-    for (int i = tid; i < G * kPairs; i += nthreads) {
-      const int g = i / kPairs, pr = i - g * kPairs;
-      uint32_t v = 0;
+    // 64 words of one head at a time, so that everything but the lane is the same for a wave
+    constexpr int kRows = (kPairs + kWave - 1) / kWave;
+    for (int u = __builtin_amdgcn_readfirstlane(wave); u < G * kRows; u += WAVES) {
+      const int g = u / kRows, pr = u % kRows * kWave + lane;
+      if (pr < kPairs) {
+        const uint32_t* h = s_hist + g * (kHistReplicas * kHistWords);
+        uint32_t v = 0;
 #pragma unroll
-      for (int r = 0; r < kHistReplicas; ++r) {
-        if constexpr (kWideBins) v += s_hist[g][r][2 * pr] + (s_hist[g][r][2 * pr + 1] << 16);  // (a last odd bin that no distance reaches stays zero)
-        else v += s_hist[g][r][pr];
+        for (int r = 0; r < kHistReplicas; ++r) {
+          // (a last odd bin that no distance reaches stays zero)
+          if constexpr (kWideBins) v += h[r * kHistWords + 2 * pr] + (h[r * kHistWords + 2 * pr + 1] << 16);
+          else v += h[r * kHistWords + pr];
+        }
+        p.tilehist[((int64_t)(head0 + g) * p.n_tiles + tile_id) * kPairs + pr] = v;
       }
-      p.tilehist[((int64_t)(head0 + g) * p.n_tiles + tile_id) * kPairs + pr] = v;
     }
   }
   trace.stamp(kScanEnd);
