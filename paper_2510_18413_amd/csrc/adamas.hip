@@ -62,7 +62,7 @@ struct Plan {
   int n_segs;        // select workgroups per (sequence, query head)
   int metric;        // code format + distance estimator (struct Dist)
   int head_dim;      // 64, 128 or 256
-  int g_split;       // scan workgroups per (tile, KV head), each with a share of the query group
+  int g_shift;       // 2^g_shift scan workgroups per (tile, KV head), each with a share of the query group
   int64_t dist_stride;
   size_t off_dist, off_high, off_hist, off_partial, total;
 };
@@ -161,30 +161,52 @@ Plan make_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len, int32
   pl.metric = metric_of(c);
   pl.head_dim = c->head_dim;
   const int64_t planes = (int64_t)batch * c->num_kv_heads;
-  // Scan tile (measured on MI355X): large tiles amortise the per-workgroup
-  // prologue and leave the select kernel fewer tile histograms to read, small
-  // ones fit more workgroups on a compute unit.
-  auto n_wg = [&](int tile) { return planes * ((max_seq_len + tile - 1) / tile); };
-  if (n_wg(4096) >= 4 * kTargetWorkgroups) {
-    // many rounds of workgroups per compute unit: residency matters most
-    pl.tile_tokens = 1024;
-  } else if (n_wg(4096) >= kTargetWorkgroups) {
-    // Half-size workgroups balance better over the compute units (0.4 us on a
-    // 32 MiB plane) as long as a head keeps at most one batch of tile
-    // histograms for the select kernel to read.
-    pl.tile_tokens = (max_seq_len + 2047) / 2048 <= kHistBatch ? 2048 : 4096;
-  } else if (n_wg(2048) >= kTargetWorkgroups / 2) {
-    pl.tile_tokens = 2048;
-  } else {
-    pl.tile_tokens = 1024;
-  }
-  pl.n_tiles = (int)((max_seq_len + pl.tile_tokens - 1) / pl.tile_tokens);
-  // Few planes and a query group: the scan is then bound by the distance
-  // arithmetic of the workgroups that exist, not by memory, so the group is cut
-  // in two (each half re-reads the rows) until there is a workgroup per compute unit.
-  pl.g_split = 1;
+  // Scan: tokens per workgroup (4, 8 or 16 waves of 256) and the share of the query group that it serves (all, half or a
+  // quarter of it, each share reading the rows again).  A compute unit's time goes with the waves that each of its
+  // SIMDs gets, times what a wave does: about as much for the rows, the histogram and the prologue as for one head, and a
+  // share of encoding the queries, which costs 1.5 of that per query and is spread over the waves.  Below 2.5 waves per
+  // SIMD it is the chain of one wave that takes the time.  The select kernel loads the histograms of kHistBatch tiles at
+  // once and pays about four such units for each further batch.  Measured (us per layer, 32 query heads, d = 128; tile /
+  // parts of the group, chosen *):                2048 / 1  2048 / 2  4096 / 1  4096 / 2  4096 / 4
+  //   1 sequence of 20000, group of 4               13.6     12.6*     15.0      13.3      13.1
+  //   1 of 32771                                    14.8     15.6      15.3      14.0*     16.3
+  //   1 of 100000                                   22.3     24.0      19.2*     22.1
+  //   2 of 20011                                    15.2     16.0      16.3      14.7*     17.4
+  //   4 of 30000                                    21.8     24.3      20.9*     22.5
+  //   8 ragged, up to 16000                         24.2     25.4      22.6*     25.6
+  //   16 ragged, up to 32768 (1024 / 1: 44.2)       42.3     47.8      42.1*     53.5
+  //   48 ragged, up to 6001 (1024 / 1: 60.3)        58.5*    60.6      60.3      70.4
+  //   2 of 60000, group of 8                        21.5     20.6      22.6      19.1*     22.9
+  //   4 of 60001, group of 8                        28.2     28.8      26.5*     26.9
+  //   1 of 100000, 16 heads, group of 8             20.3     18.0      21.1      17.5      16.7*
+  //   1 of 32768, group of 1                        16.8*              17.2
+  //   1 of 50000, group of 1                        21.2               20.1*
+  // d = 64, 96, 192 and 256 rank alike (six shapes each).
   const int group = c->num_q_heads / c->num_kv_heads;
-  if (group % 2 == 0 && n_wg(pl.tile_tokens) * 2 <= kTargetWorkgroups) pl.g_split = 2;
+  auto n_tiles_of = [&](int tile) { return (max_seq_len + tile - 1) / tile; };
+  double best = 0.0;
+  for (int tile = 4096; tile >= 1024; tile /= 2) {
+    if (tile > 1024 && tile >= 2 * max_seq_len) continue;
+    // with workgroups for half of the compute units or more, tiles of 1024 lose
+    if (tile == 1024 && pl.tile_tokens != 0 && planes * n_tiles_of(2048) >= kTargetWorkgroups / 2) break;
+    for (int shift = 0; shift <= 2 && group % (1 << shift) == 0; ++shift) {
+      const int64_t n_wg = planes * n_tiles_of(tile) << shift;
+      if (shift > 0 && n_wg > kTargetWorkgroups) break;
+      // whole rounds while there are few, the average beyond
+      const double per_unit = n_wg < 4 * kTargetWorkgroups ? (double)((n_wg + kTargetWorkgroups - 1) / kTargetWorkgroups)
+                                                           : (double)n_wg / kTargetWorkgroups;
+      const double waves = std::fmax(2.5, per_unit * (tile / 1024)), heads = group >> shift;
+      double cost = waves * (1.0 + heads + 1.5 * heads / (tile / 256)) +
+                    4.0 * (double)((n_tiles_of(tile) + kHistBatch - 1) / kHistBatch - 1);
+      // one head per row is bound by memory, and two workgroups per unit keep that busier than one (32 planes of 32768: see above)
+      if (group == 1 && tile == 4096 && n_wg <= kTargetWorkgroups) cost *= 1.1;
+      if (pl.tile_tokens == 0 || cost < best) {
+        best = cost;
+        pl.tile_tokens = tile;
+        pl.g_shift = shift;
+      }
+    }
+  }
   // Select + attention: a head is cut into segments, one workgroup each (a
   // single compute unit is too slow to compact a whole 32K-token head or to
   // gather all of its rows), and the segments' attention partials are merged
@@ -202,18 +224,30 @@ Plan make_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len, int32
   pl.n_segs = (int)((max_seq_len + seg - 1) / seg);
   pl.dist_stride = (max_seq_len + 127) & ~(int64_t)127;
   const size_t heads = (size_t)batch * c->num_q_heads;
-  size_t off = 0;
-  pl.off_dist = off;
-  off = align256(off + heads * (size_t)pl.dist_stride * dist_bytes_of(pl.metric, c->head_dim));
-  pl.off_high = off;
-  if (high_plane_of(pl.metric, c->head_dim)) off = align256(off + heads * (size_t)pl.dist_stride / 8);
-  pl.off_hist = off;
-  // + kHistBatch rows: the select kernel reads whole batches of tile rows, also behind the last head's
-  off = align256(off + (heads * (size_t)pl.n_tiles + kHistBatch) * hist_pairs_of(pl.metric, c->head_dim) *
-                           sizeof(uint32_t));
-  pl.off_partial = off;
-  off = align256(off + heads * (size_t)kMaxParts * partial_stride(c->head_dim) * sizeof(float));
-  pl.total = off;
+  auto lay_out = [&]() {
+    pl.n_tiles = (int)n_tiles_of(pl.tile_tokens);
+    size_t off = 0;
+    pl.off_dist = off;
+    off = align256(off + heads * (size_t)pl.dist_stride * dist_bytes_of(pl.metric, c->head_dim));
+    pl.off_high = off;
+    if (high_plane_of(pl.metric, c->head_dim)) off = align256(off + heads * (size_t)pl.dist_stride / 8);
+    pl.off_hist = off;
+    // + kHistBatch rows: the select kernel reads whole batches of tile rows, also behind the last head's
+    off = align256(off + (heads * (size_t)pl.n_tiles + kHistBatch) * hist_pairs_of(pl.metric, c->head_dim) *
+                             sizeof(uint32_t));
+    pl.off_partial = off;
+    off = align256(off + heads * (size_t)kMaxParts * partial_stride(c->head_dim) * sizeof(float));
+    pl.total = off;
+  };
+  lay_out();
+  // adamas_decode_step_static takes whatever fits its array with the fewest histograms
+  if (pl.total > (size_t)ADAMAS_STATIC_SCRATCH_BYTES && pl.tile_tokens < 4096) {
+    const Plan chosen = pl;
+    pl.tile_tokens = 4096;
+    pl.g_shift = 0;
+    lay_out();
+    if (pl.total > (size_t)ADAMAS_STATIC_SCRATCH_BYTES) pl = chosen;
+  }
   return pl;
 }
 
@@ -284,9 +318,9 @@ int launch_status() {
 void launch_scan(const adamas_config* c, bool fused, const Plan& pl, int batch, hipStream_t st,
                  ScanParams sp) {
   const int group = c->num_q_heads / c->num_kv_heads;
-  sp.g_split = group % pl.g_split == 0 ? pl.g_split : 1;
-  const dim3 grid(pl.n_tiles, c->num_kv_heads * sp.g_split, batch);
-  set_of(c).scan(fused, group / sp.g_split, pl.tile_tokens, grid, st, sp);
+  sp.g_shift = pl.g_shift;
+  const dim3 grid(pl.n_tiles, c->num_kv_heads << pl.g_shift, batch);
+  set_of(c).scan(fused, group >> pl.g_shift, pl.tile_tokens, grid, st, sp);
 }
 
 struct FullPlan {

@@ -66,7 +66,7 @@ struct ScanParams {
   int64_t arrivals_stride;
   int64_t pool_tokens, max_seq_len;
   int32_t Hq, Hkv, n_tiles;
-  int32_t g_split;           // workgroups per (tile, KV head), 1 or 2: each takes G of the group's G * g_split query heads
+  int32_t g_shift;           // 2^g_shift workgroups per (tile, KV head), each takes G of the group's G << g_shift query heads
   // Paged cache (PAGED kernels only): token t of sequence b lives in pool row
   // page_table[b * max_pages + (t >> page_shift)] << page_shift | (t & page mask).
   const int32_t* page_table;
@@ -115,21 +115,20 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   // per wave: its 256 distances to each query head of a pass, in token order
   __shared__ __align__(16) uint16_t s_dt[WAVES][kPassHeads][kScanTokPerThread * kWave];
 
-  // blockIdx.y = KV head * g_split + part: the G query heads of this workgroup are
-  // part `gsub` of the KV head's group of G * g_split (the parts re-read the rows).
+  // blockIdx.y = KV head << g_shift | part: the G query heads of this workgroup are
+  // part `gsub` of the KV head's group of G << g_shift (the parts re-read the rows).
   PhaseTrace trace;
   trace.stamp(kScanStart);
   // requested first of all: the row loads cannot be addressed without them
   SeqInfo seq = SeqInfo::request<PAGED, true>(p.seq_len, p.seq_start, (int)blockIdx.z);
   __builtin_amdgcn_sched_barrier(0);
-  // g_split is 1 or 2
-  const int tile_id = blockIdx.x, kvh = blockIdx.y >> (p.g_split - 1), gsub = blockIdx.y & (p.g_split - 1);
+  const int tile_id = blockIdx.x, kvh = blockIdx.y >> p.g_shift, gsub = blockIdx.y & ((1 << p.g_shift) - 1);
   const int b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int nthreads = WAVES * kWave;
   constexpr int tile_tokens = nthreads * kScanTokPerThread;
   const int t0 = tile_id * tile_tokens;
-  const int head0 = b * p.Hq + (kvh * p.g_split + gsub) * G;
+  const int head0 = b * p.Hq + (int)blockIdx.y * G;
 
   // First of all the encoding waves request their vectors (G queries and, if
   // the call appends, the new key): their addresses need nothing from memory,

@@ -1,0 +1,67 @@
+"""The scan's cuts, by tile (1024, 2048 or 4096 tokens) and by parts of the query group (1, 2 or 4): distances, selected
+positions and outputs against the oracle where each cut is chosen, one token before, on and after the edge of a tile, of
+a wave's 256 tokens and of a lane's eight."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2510_18413_amd as A
+import synth_inputs as synth
+
+# B, query heads, KV heads, length, head dimension
+CUTS = [
+    (1, 2, 1, 1017, 128),      # one tile of 1024, two heads
+    (1, 4, 1, 2049, 128),      # 2048 tokens, a head per workgroup
+    (1, 8, 1, 2304, 128),      # 2048, two heads of eight per workgroup
+    (1, 8, 1, 8191, 64),
+    (2, 12, 4, 4097, 128),     # a group of three is not cut
+    (3, 24, 4, 4105, 128),     # a group of six: halves only
+    (5, 16, 2, 33000, 128),    # 4096, four parts of eight heads
+    (9, 32, 8, 4096, 128),     # 4096, halves of four heads
+    (9, 32, 8, 4097, 96),
+    (16, 32, 8, 8200, 128),    # 4096, more workgroups than compute units
+    (33, 16, 8, 2049, 256),    # uint16 distances
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,L,d", CUTS)
+def test_step_at_every_cut_of_the_scan(oracle, B, Hq, Hkv, L, d):
+    from gpu_harness import ATTN_TOL, DeviceCase, attn_rel_err, oracle_step
+    G = Hq // Hkv
+    lens = [max(2, L - 3 * i) for i in range(B)]
+    case = synth.make_case("cut", 7000 + L + B, B, Hq, Hkv, lens, [0],
+                           lambda b, Lc, h, rng: rng.choice(Lc, size=(G, 1), replace=False), append=True, head_dim=d)
+    k = min(96, L - 3 * B)
+    dc = DeviceCase(case, k)
+    out, idx = dc.decode_step()
+    want = oracle_step(case, k)
+    assert np.array_equal(idx, want["idx"])
+    assert attn_rel_err(out, want["out"]) <= ATTN_TOL
+    got_rows = dc.codes.cpu().numpy()
+    for b in range(B):       # the appended row is in the cache
+        at = int(case.seq_start[b]) + lens[b] - 1
+        assert np.array_equal(got_rows[:, at], want["rows"][:, at])
+    # the distances themselves, of the stand-alone scan
+    qcodes = torch.zeros(B, Hq, dc.cfg.code_row_bytes, dtype=torch.uint8, device="cuda")
+    A.adamas_encode_query(dc.cfg, dc.q, qcodes)
+    dist = torch.zeros(B, Hq, dc.max_len, dtype=torch.uint16, device="cuda")
+    A.adamas_manhattan_distance(dc.cfg, qcodes, dc.codes, dc.seq_start, dc.seq_len, dist)
+    got = dist.cpu().view(torch.int16).numpy().view(np.uint16).astype(np.int32)
+    for b in range(B):
+        assert np.array_equal(got[b, :, :lens[b]], want["dist"][b][:, :lens[b]])
+
+
+def test_the_static_array_takes_every_shape_that_fits_with_the_fewest_histograms():
+    """Tiles of 4096 tokens need the least scratch: a call that fits with them is never refused because the plan
+    would rather have smaller ones."""
+    for group, kv, batch in [(1, 32, 1), (4, 8, 3), (4, 8, 11), (8, 2, 20), (2, 8, 7), (4, 1, 150)]:
+        heads = batch * kv * group
+        cfg = A.Config.make(kv * group, kv, 1 << 22)
+        fits = lambda L: A.adamas_workspace_bytes(cfg, batch, L, 64) <= A.STATIC_SCRATCH_BYTES
+        for L in range(700, 1 << 17, 1777):
+            tiles = -(-L // 4096)
+            least = heads * (-(-L // 128) * 128) * 9 // 8 + (heads * tiles + 16) * 193 * 4 + heads * 16 * 132 * 4 + 4 * 256
+            if least <= A.STATIC_SCRATCH_BYTES:
+                assert fits(L), (group, kv, batch, L)
