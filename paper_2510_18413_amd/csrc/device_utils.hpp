@@ -236,6 +236,8 @@ struct PhaseTrace {
 // no LDS round trip.  A "row" is 16 consecutive lanes.
 constexpr int kDppQuadXor1 = 0xB1;       // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;       // quad_perm [2,3,0,1]
+constexpr int kDppQuadMirror = 0x1B;     // quad_perm [3,2,1,0]
+constexpr int kDppRowRor8 = 0x128;       // row_ror:8
 constexpr int kDppRowShr = 0x110;        // + n: lane i reads lane i-n of its row
 constexpr int kDppRowMirror = 0x140;     // lane i reads lane 15-i of its row
 constexpr int kDppRowHalfMirror = 0x141; // lane i reads lane 7-i of its half row
@@ -278,7 +280,7 @@ __device__ __forceinline__ void exchange_pair(float v, float& a, float& b) {
     a = __uint_as_float(r[0]);
     b = __uint_as_float(r[1]);
   } else {
-    const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, (int)u, 0x128 /* row_ror:8 */, 0xf, 0xf, false));
+    const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, (int)u, kDppRowRor8, 0xf, 0xf, false));
     const bool upper = (threadIdx.x & 8) != 0;
     a = upper ? o : v;
     b = upper ? v : o;
@@ -315,6 +317,34 @@ __device__ __forceinline__ double lanes_sum_f64(double v) {
   if constexpr (LANES >= 16) v += dpp_f64<kDppRowMirror>(v);
   if constexpr (LANES >= 32) v += __shfl_xor(v, 16, kWave);
   return v;
+}
+
+// One butterfly across lanes i and i ^ H of a wave: the lane whose H bit is clear receives the sum, the other one the lower
+// lane's value minus its own.  Vector instructions only (a shuffle through LDS costs a round trip per step).
+template <int H>
+__device__ __forceinline__ double lane_butterfly_f64(double v) {
+  static_assert(H == 1 || H == 2 || H == 4 || H == 8 || H == 16 || H == 32, "a lane bit");
+  const double sign = (threadIdx.x & H) != 0 ? -1.0 : 1.0;
+  if constexpr (H >= 16) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    // the values of the lower lane of the pair in r[0], of the upper one in r[1], in both lanes
+    auto swap = [](uint32_t x) {
+      if constexpr (H == 16) return __builtin_amdgcn_permlane16_swap(x, x, false, false);
+      else return __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    };
+    const auto l = swap(lo), h = swap(hi);
+    const double lower = __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]);
+    const double upper = __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+    return fma(sign, upper, lower);  // the product is exact: one rounding, as in an addition
+  } else {
+    double partner;
+    if constexpr (H == 1) partner = dpp_f64<kDppQuadXor1>(v);
+    if constexpr (H == 2) partner = dpp_f64<kDppQuadXor2>(v);
+    if constexpr (H == 4) partner = dpp_f64<kDppQuadMirror>(dpp_f64<kDppRowHalfMirror>(v));  // i ^ 7 ^ 3
+    if constexpr (H == 8) partner = dpp_f64<kDppRowRor8>(v);
+    return fma(sign, v, partner);
+  }
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave (Hillis-Steele inside each

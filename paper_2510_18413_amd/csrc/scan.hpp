@@ -137,7 +137,10 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   // unit requests are served in order across waves, so a needless load here
   // would sit in front of other waves' rows.
   constexpr int kEncRounds = (G + 1 + WAVES - 1) / WAVES;  // G queries + 1 new key over the waves
-  uint32_t enc[kEncRounds][E];
+  // 16 bits each until they are used, loaded one by one (wavefront-scope atomic loads, which are plain loads here): widened
+  // or split on arrival (D = 64, 192), an encoding wave waited for them before it requested any row, and some of
+  // them were requested behind the rows (D = 96, 160).
+  uint16_t enc[kEncRounds][E];
 #pragma unroll
   for (int r = 0; r < kEncRounds; ++r) {
     const int v = wave + r * WAVES;
@@ -147,8 +150,9 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
       const uint16_t* src = v < G ? p.q + (int64_t)(head0 + v) * D
                                   : p.k_new + ((int64_t)b * p.Hkv + kvh) * D;
 #pragma unroll
-      for (int e = 0; e < E; ++e)
-        enc[r][e] = lane < HeadDim<D>::kEncLanes ? src[HeadDim<D>::enc_index(lane, e)] : 0u;
+      for (int e = 0; e < E; ++e)  // (lanes beyond the encoding ones read along; their values are not used)
+        enc[r][e] = __hip_atomic_load(src + HeadDim<D>::enc_index(min(lane, HeadDim<D>::kEncLanes - 1), e),
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
   }
 
@@ -245,7 +249,10 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
       const int v = wave + r * WAVES;
       if (v < n_enc) {
         uint32_t w[BITS][W];
-        encode_values_wave<BITS, D>(enc[r], v < G ? p.thr_q : p.thr_k, w);
+        uint32_t raw[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) raw[e] = enc[r][e];
+        encode_values_wave<BITS, D>(raw, v < G ? p.thr_q : p.thr_k, w);
         // lane wd publishes word wd (every lane holds the whole row)
 #pragma unroll
         for (int wd = 0; wd < W; ++wd) {
@@ -404,7 +411,7 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
     constexpr int kLanes = kScanTokPerThread * kWave / 8;  // lanes per head
 #pragma unroll
     for (int c = 0; c < (kPassHeads * kLanes + kWave - 1) / kWave; ++c) {
-      const int at = c * kWave + lane, g = g0 + at / kLanes;
+      const int at = c * kWave + lane, g = kPassHeads == 1 ? g0 : g0 + at / kLanes;
       const int tt = t0 + wave * (kScanTokPerThread * kWave) + 8 * (at % kLanes);
       if (p.dist != nullptr && at < kPassHeads * kLanes && g < G && tt < L) {
         uint32_t v[4];
