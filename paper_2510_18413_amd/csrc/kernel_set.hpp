@@ -30,7 +30,7 @@ struct KernelSet {
   void (*encode_rows)(hipStream_t st, const uint16_t* src, uint8_t* dst, int64_t head_stride_rows,
                       int64_t row_begin, int64_t n_rows, int64_t n_vec, const Thresholds& thr);
   // Kernels that depend on the head dimension only: set in the kMetricL1 set, null elsewhere.
-  void (*sparse_attn)(dim3 grid, hipStream_t st, const AttnParams& ap);
+  void (*sparse_attn)(bool wide, dim3 grid, hipStream_t st, const AttnParams& ap);
   void (*merge)(dim3 grid, hipStream_t st, const MergeParams& mp);
   void (*full_attn)(int G, dim3 grid, hipStream_t st, const FullAttnParams& fp);
   void (*merge_parts)(dim3 grid, hipStream_t st, const float* partial, float* out, int Hq, int n_parts);

@@ -131,8 +131,9 @@ void launch_encode_rows(hipStream_t st, const uint16_t* src, uint8_t* dst, int64
 }
 
 template <int D_>
-void launch_sparse_attn(dim3 grid, hipStream_t st, const AttnParams& ap) {
-  hipLaunchKernelGGL(sparse_attn_kernel<D_>, grid, dim3(kAttnThreads), 0, st, ap);
+void launch_sparse_attn(bool wide, dim3 grid, hipStream_t st, const AttnParams& ap) {
+  if (wide) hipLaunchKernelGGL((sparse_attn_kernel<kAttnThreadsWide, D_>), grid, dim3(kAttnThreadsWide), 0, st, ap);
+  else hipLaunchKernelGGL((sparse_attn_kernel<kAttnThreads, D_>), grid, dim3(kAttnThreads), 0, st, ap);
 }
 
 template <int D_>

@@ -920,7 +920,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
 
 // ---------------------------------------------------------------- stand-alone attention
 
-constexpr int kAttnThreads = 256;
+constexpr int kAttnThreads = 256, kAttnThreadsWide = 1024;  // workgroups of the two forms (see the launch rule)
 
 struct AttnParams {
   const uint16_t* q;
@@ -938,12 +938,12 @@ struct AttnParams {
 
 // Grid (n_parts, Hq, B): workgroup `part` attends over idx entries
 // [part*chunk, (part+1)*chunk) of its head.  n_parts == 1 writes out directly.
-template <int D>
-__global__ __launch_bounds__(kAttnThreads) void sparse_attn_kernel(const AttnParams p) {
+template <int THREADS, int D>
+__global__ __launch_bounds__(THREADS) void sparse_attn_kernel(const AttnParams p) {
   constexpr int kPartial = partial_stride(D);
   __shared__ int32_t s_sel[kMaxK];
-  __shared__ uint32_t s_scan[kAttnThreads / kWave];
-  __shared__ AttnShared<kAttnThreads, D> s_attn;
+  __shared__ uint32_t s_scan[THREADS / kWave];
+  __shared__ AttnShared<THREADS, D> s_attn;
   const int part = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x;
   const int64_t head = (int64_t)b * p.Hq + hq;
@@ -954,12 +954,12 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_attn_kernel(const AttnPar
   // Order-preserving compaction of the usable entries of this chunk: negative
   // entries are padding; an entry that would leave the pool is dropped too.
   uint32_t n = 0;
-  for (int base = i0; base < i1; base += kAttnThreads) {
+  for (int base = i0; base < i1; base += THREADS) {
     const int i = base + tid;
     const int32_t tok = i < i1 ? idx_row[i] : -1;
     const bool use = tok >= 0 && start >= 0 && start + tok < p.pool_tokens;
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kAttnThreads>(use ? 1u : 0u, s_scan, total);
+    const uint32_t ex = block_excl_scan<THREADS>(use ? 1u : 0u, s_scan, total);
     if (use) s_sel[n + ex] = tok;
     n += total;
   }
@@ -968,7 +968,7 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_attn_kernel(const AttnPar
   const int64_t row0 = ((int64_t)kvh * p.pool_tokens + start) * D;
   float M, lsum, o;
   PhaseTrace trace;  // not recorded for the stand-alone kernel
-  attention_rows<kAttnThreads, D>(s_sel, (int)n, (int)min((int64_t)0x7fffffff, p.pool_tokens - start),
+  attention_rows<THREADS, D>(s_sel, (int)n, (int)min((int64_t)0x7fffffff, p.pool_tokens - start),
                                qv, p.K + row0, p.V + row0, p.scale_log2e, s_attn, M, lsum, o, trace);
   if (tid < D) {
     if (gridDim.x == 1) {
