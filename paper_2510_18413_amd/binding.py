@@ -1,4 +1,5 @@
-"""ctypes binding of libadamas.so: argument marshalling only.
+"""Binding of libadamas.so: argument marshalling only, through ctypes, and for the calls of a decoding loop in native
+code (csrc/marshal.cpp), which hands back what it does not take as it is.
 
 Every function mirrors the C entry point of the same name in include/adamas.h, takes torch
 tensors that already live on the GPU, checks dtype / device / contiguity, and passes raw
@@ -85,6 +86,7 @@ class Config(ctypes.Structure):
 
 
 _lib = None
+_marshal = None  # the native marshalling module, once the library is loaded; None: ctypes only
 torch = None    # the module, once the library is loaded (imported there, not with this package)
 
 
@@ -96,7 +98,7 @@ def library() -> ctypes.CDLL:
     """Loads libadamas.so, building it first (in a child process, before anything here touches
     the GPU library) when it is missing or was built from sources other than the tree's.  The
     environment variable ADAMAS_LIBRARY names another built library to load instead."""
-    global _lib, torch
+    global _lib, _marshal, torch
     if _lib is None:
         # torch first: the process then has one HIP runtime (the one torch ships), and this
         # library, which only needs the public HIP launch API, binds to it.
@@ -148,8 +150,37 @@ def library() -> ctypes.CDLL:
         lib.adamas_decode_step_stages.restype = ctypes.c_int
         lib.adamas_decode_step_stages.argtypes = lib.adamas_decode_step.argtypes + [ctypes.c_uint32]
         torch = torch_module
+        _marshal = _load_marshal(lib)
         _lib = lib
     return _lib
+
+
+def _load_marshal(lib):
+    """The native marshalling module, bound to this library's entry points; built if it is missing or was built from
+    other sources.  None where it cannot be built: every call then goes through ctypes."""
+    import importlib.machinery
+    import importlib.util
+    import subprocess
+
+    def load():
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", str(_build.MARSHAL_LIB))
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+        loader.exec_module(module)
+        return module
+
+    try:
+        # (a module that has been loaded once stays what it is in this process: look before loading)
+        if not _build.MARSHAL_LIB.exists() or _build.marshal_id().encode() not in _build.MARSHAL_LIB.read_bytes():
+            _build.build_marshal()
+        module = load()
+    except (ImportError, OSError, subprocess.CalledProcessError):
+        return None
+    address = lambda fn: ctypes.cast(fn, ctypes.c_void_p).value
+    import torch as torch_module
+    module.bind(Config, torch_module._C._cuda_getDevice, torch_module._C._cuda_getCurrentRawStream,
+                address(lib.adamas_decode_step), address(lib.adamas_decode_step_paged),
+                address(lib.adamas_encode_keys), address(lib.adamas_full_attn))
+    return module
 
 
 def adamas_status_string(status: int) -> str:
@@ -200,7 +231,14 @@ def _check(rc, where):
         raise AdamasError(rc, where)
 
 
+# The functions with a native form try that first; it returns a status, or None for arguments that it does not take as they
+# are, and the checks below then say what is wrong with them (or accept them).
+
 def adamas_encode_keys(cfg: Config, K, codes, row_begin: int, n_rows: int, stream=None) -> None:
+    if _marshal is not None:
+        rc = _marshal.encode_keys(cfg, K, codes, row_begin, n_rows, None if stream is None else _stream(stream))
+        if rc is not None:
+            return _check(rc, "adamas_encode_keys")
     lib = _lib or library()
     hkv, pool = cfg.num_kv_heads, cfg.pool_tokens
     rc = lib.adamas_encode_keys(
@@ -223,6 +261,11 @@ def adamas_encode_query(cfg: Config, q, qcodes, stream=None) -> None:
 def adamas_decode_step_paged(cfg: Config, q, K, V, codes, page_table, page_tokens: int, seq_len,
                              k: int, out, max_seq_len: int, workspace, k_new=None, v_new=None,
                              idx_out=None, stream=None, stages=STAGE_ALL) -> None:
+    if _marshal is not None:
+        rc = _marshal.decode_step_paged(cfg, q, K, V, codes, page_table, page_tokens, seq_len, k, out, max_seq_len, workspace,
+                                        k_new, v_new, idx_out, None if stream is None else _stream(stream), stages)
+        if rc is not None:
+            return _check(rc, "adamas_decode_step_paged")
     lib = _lib or library()
     batch = q.shape[0]
     hkv, pool = cfg.num_kv_heads, cfg.pool_tokens
@@ -250,6 +293,11 @@ def adamas_full_attn_workspace_bytes(cfg: Config, batch: int, max_seq_len: int) 
 
 def adamas_full_attn(cfg: Config, q, K, V, seq_start, seq_len, out, max_seq_len: int, workspace,
                      stream=None) -> None:
+    if _marshal is not None:
+        rc = _marshal.full_attn(cfg, q, K, V, seq_start, seq_len, out, max_seq_len, workspace,
+                                None if stream is None else _stream(stream))
+        if rc is not None:
+            return _check(rc, "adamas_full_attn")
     lib = _lib or library()
     batch = q.shape[0]
     hkv, pool = cfg.num_kv_heads, cfg.pool_tokens
@@ -327,6 +375,11 @@ def adamas_sparse_attn(cfg: Config, q, K, V, seq_start, idx, out, max_seq_len: i
 def adamas_decode_step(cfg: Config, q, K, V, codes, seq_start, seq_len, k: int, out,
                        max_seq_len: int, workspace, k_new=None, v_new=None, idx_out=None,
                        stream=None) -> None:
+    if _marshal is not None:
+        rc = _marshal.decode_step(cfg, q, K, V, codes, seq_start, seq_len, k, out, max_seq_len, workspace, k_new, v_new, idx_out,
+                                  None if stream is None else _stream(stream))
+        if rc is not None:
+            return _check(rc, "adamas_decode_step")
     adamas_decode_step_stages(cfg, q, K, V, codes, seq_start, seq_len, k, out, max_seq_len,
                               workspace, k_new=k_new, v_new=v_new, idx_out=idx_out, stream=stream,
                               stages=None)

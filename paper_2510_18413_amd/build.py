@@ -124,6 +124,43 @@ def build(verbose: bool = False, extra_flags=(), jobs: int = 0, only=None, out: 
     return out
 
 
+MARSHAL_SRC = CSRC / "marshal.cpp"
+MARSHAL_LIB = PKG / "_marshal.so"
+
+
+def marshal_id() -> str:
+    """What a marshalling module built now would carry: its sources, the interpreter and torch."""
+    import sys
+    import torch
+    h = hashlib.sha256((sys.version + torch.__version__).encode())
+    for s in (MARSHAL_SRC, ROOT / "include" / "adamas.h"):
+        h.update(s.read_bytes())
+    return h.hexdigest()[:16]
+
+
+def build_marshal(verbose: bool = False) -> Path:
+    """Compiles the binding's native argument marshalling (host code only) against torch's headers."""
+    import sysconfig
+    import torch
+    inc = Path(torch.__file__).parent / "include"
+    tmp = Path(str(MARSHAL_LIB) + ".tmp%d" % os.getpid())
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           '-DADAMAS_MARSHAL_ID="%s"' % marshal_id(), "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I", sysconfig.get_paths()["include"], "-I", str(inc),
+           "-I", str(inc / "torch" / "csrc" / "api" / "include"), "-I", str(ROOT / "include"), str(MARSHAL_SRC), "-o", str(tmp),
+           # (already in the process, which has imported torch, when the module is loaded)
+           "-L", str(inc.parent / "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    try:
+        subprocess.run(cmd, check=True)
+        os.replace(tmp, MARSHAL_LIB)
+    finally:
+        if tmp.exists():
+            tmp.unlink()
+    return MARSHAL_LIB
+
+
 TRACE_LIB = PKG / "libadamas_trace.so"
 
 
