@@ -45,21 +45,32 @@ void launch_scan(bool fused, int G, int tile_tokens, dim3 grid, hipStream_t st, 
   }
 }
 
-template <int CHUNK>
-void launch_select_chunk(bool attn, bool paged, dim3 grid, hipStream_t st, const SelectParams& sl) {
+template <int CHUNK, int TILES>
+void launch_select_as(bool attn, bool paged, dim3 grid, hipStream_t st, const SelectParams& sl) {
   if (!attn)
-    hipLaunchKernelGGL((select_kernel<kSelThreads, false, METRIC, false, D, CHUNK>), grid, dim3(kSelThreads), 0, st, sl);
+    hipLaunchKernelGGL((select_kernel<kSelThreads, false, METRIC, false, D, CHUNK, TILES>), grid, dim3(kSelThreads), 0, st, sl);
   else if (paged)
-    hipLaunchKernelGGL((select_kernel<kSelThreads, true, METRIC, true, D, CHUNK>), grid, dim3(kSelThreads), 0, st, sl);
+    hipLaunchKernelGGL((select_kernel<kSelThreads, true, METRIC, true, D, CHUNK, TILES>), grid, dim3(kSelThreads), 0, st, sl);
   else
-    hipLaunchKernelGGL((select_kernel<kSelThreads, true, METRIC, false, D, CHUNK>), grid, dim3(kSelThreads), 0, st, sl);
+    hipLaunchKernelGGL((select_kernel<kSelThreads, true, METRIC, false, D, CHUNK, TILES>), grid, dim3(kSelThreads), 0, st, sl);
 }
 
+// The histograms that a call loads together: as many as its longest sequence has tiles, rounded up to four (see select_kernel).
 void launch_select(bool attn, bool paged, dim3 grid, hipStream_t st, const SelectParams& sl) {
   // segments of more than two passes (4096 tokens each) share one barrier among up to eight passes;
   // only planes of byte distances have that form
-  if (Dist<METRIC, D>::kByteDist && sl.seg_len > 2 * 4096) launch_select_chunk<8>(attn, paged, grid, st, sl);
-  else launch_select_chunk<1>(attn, paged, grid, st, sl);
+  if (Dist<METRIC, D>::kByteDist && sl.seg_len > 2 * 4096) {
+    if (sl.n_tiles <= 8) launch_select_as<8, 8>(attn, paged, grid, st, sl);
+    else launch_select_as<8, kHistBatch>(attn, paged, grid, st, sl);
+  } else if (sl.n_tiles <= 4) {
+    launch_select_as<1, 4>(attn, paged, grid, st, sl);
+  } else if (sl.n_tiles <= 8) {
+    launch_select_as<1, 8>(attn, paged, grid, st, sl);
+  } else if (sl.n_tiles <= 12) {
+    launch_select_as<1, 12>(attn, paged, grid, st, sl);
+  } else {
+    launch_select_as<1, kHistBatch>(attn, paged, grid, st, sl);
+  }
 }
 
 // The launchers below are templates so that a set that does not export them

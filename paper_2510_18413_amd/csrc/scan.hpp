@@ -380,19 +380,21 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
           for (int wq = 0; wq < kRowWords; ++wq) rr[i][wq] = s_new[wq];
         }
       }
-      if (t < L) {
+      // up to two heads mask their atomics alone (0.1 us of 12.9 for 32 planes of 9235 ragged tokens), larger groups the whole step
+      constexpr bool kMaskEach = kPlanesInVgprs;
+      if (kMaskEach || t < L) {
 #pragma unroll
         for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
           const uint32_t d = distance(rr[i], [&](int j, int wd) { return qp[g - g0][j][wd]; });
           s_dt[wave][g - g0][i * kWave + lane] = (uint16_t)d;
           if constexpr (kWideBins) {
-            atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + d, one);
+            if (!kMaskEach || t < L) atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + d, one);
           } else {
             // two 16-bit bins per word: 1 for an even distance, 0x10000 for an odd one
             // (opaque halves: otherwise the compiler turns them into a compare and a select)
             uint32_t pair = d >> 1, odd16 = (d & 1u) << 4;
             asm("" : "+v"(pair), "+v"(odd16));
-            atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + pair, 1u << odd16);
+            if (!kMaskEach || t < L) atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + pair, 1u << odd16);
           }
         }
       }

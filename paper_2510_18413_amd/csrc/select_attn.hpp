@@ -397,9 +397,14 @@ __device__ __forceinline__ float merge_slots(const float* ph, int n_active, int 
 // A workgroup is one wave per SIMD and runs alone on its compute unit, so its
 // time is the number of instructions a wave issues (about 2 ns each) plus the
 // memory round trips: the code below is written to issue few.
-template <int THREADS, bool ATTN, int METRIC, bool PAGED, int D, int CHUNK>
+// TILES = tiles whose histograms are loaded together: kHistBatch, or 4, 8 or 12 for calls of at most that many tiles, which
+// would otherwise request, and mask, the rows of other heads.  us per layer with 16 / as many as needed: four tiles, one sequence
+// of 8000 tokens 12.6 / 12.1; three, 48 ragged sequences 62.3 / 61.4.  Groups of four behind a branch each in one
+// kernel instead of instantiations cost calls of 16 tiles 0.2 to 0.5.
+template <int THREADS, bool ATTN, int METRIC, bool PAGED, int D, int CHUNK, int TILES>
 __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
   static_assert(CHUNK == 1 || CHUNK == 8, "passes per workgroup barrier");
+  static_assert(TILES <= kHistBatch, "rows of slack behind the last histogram");
   static_assert(ATTN || !PAGED, "only the gather needs the page table");
   static_assert(THREADS >= D, "one thread per output dimension in the merge");
   using Fmt = Dist<METRIC, D>;
@@ -435,7 +440,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
   if constexpr (ATTN) qv = load_query_piece<D>(p.q + head * D);
 
   // Nothing below depends on the sequence length until the loads are issued:
-  // the workspace rows exist up to dist_stride / n_tiles (+ kHistBatch rows of
+  // the workspace rows exist up to dist_stride / n_tiles (+ TILES rows of
   // slack behind the last histogram) whatever L is, and what lies beyond L is
   // masked once L has arrived.
   const uint8_t* drow = static_cast<const uint8_t*>(p.dist) +
@@ -474,9 +479,9 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
   int pair_off[PP];
 #pragma unroll
   for (int j = 0; j < PP; ++j) pair_off[j] = min(tid * PP + j, kHistPairs - 1);
-  uint32_t hv[PP][kHistBatch];
+  uint32_t hv[PP][TILES];
 #pragma unroll
-  for (int u = 0; u < kHistBatch; ++u) {
+  for (int u = 0; u < TILES; ++u) {
 #pragma unroll
     for (int j = 0; j < PP; ++j) hv[j][u] = hbase[u * kHistPairs + pair_off[j]];
   }
@@ -503,39 +508,39 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
 #pragma unroll
   for (int j = 0; j < PP; ++j) tot0[j] = tot1[j] = pre0[j] = pre1[j] = 0;
   const bool packed_sums = p.max_seq_len < 65536;
-  for (int tb = 0; tb < tiles_active; tb += kHistBatch) {
+  for (int tb = 0; tb < tiles_active; tb += TILES) {
     if (tb > 0) {
 #pragma unroll
-      for (int u = 0; u < kHistBatch; ++u) {
+      for (int u = 0; u < TILES; ++u) {
 #pragma unroll
         for (int j = 0; j < PP; ++j) hv[j][u] = hbase[(tb + u) * kHistPairs + pair_off[j]];
       }
     }
     const int n_tot = tiles_active - tb, n_pre = first_tile - tb;  // tiles of this batch that count
     if (packed_sums) {
-      if (n_tot >= kHistBatch) {
+      if (n_tot >= TILES) {
 #pragma unroll
-        for (int u = 0; u < kHistBatch; ++u) {
+        for (int u = 0; u < TILES; ++u) {
 #pragma unroll
           for (int j = 0; j < PP; ++j) tot0[j] += hv[j][u];
         }
       } else {
 #pragma unroll
-        for (int u = 0; u < kHistBatch; ++u) {
+        for (int u = 0; u < TILES; ++u) {
           const uint32_t on = u < n_tot ? 0xffffffffu : 0u;
 #pragma unroll
           for (int j = 0; j < PP; ++j) tot0[j] += hv[j][u] & on;
         }
       }
-      if (n_pre >= kHistBatch) {
+      if (n_pre >= TILES) {
 #pragma unroll
-        for (int u = 0; u < kHistBatch; ++u) {
+        for (int u = 0; u < TILES; ++u) {
 #pragma unroll
           for (int j = 0; j < PP; ++j) pre0[j] += hv[j][u];
         }
       } else if (n_pre > 0) {
 #pragma unroll
-        for (int u = 0; u < kHistBatch; ++u) {
+        for (int u = 0; u < TILES; ++u) {
           const uint32_t on = u < n_pre ? 0xffffffffu : 0u;
 #pragma unroll
           for (int j = 0; j < PP; ++j) pre0[j] += hv[j][u] & on;
@@ -543,7 +548,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
       }
     } else {
 #pragma unroll
-      for (int u = 0; u < kHistBatch; ++u) {
+      for (int u = 0; u < TILES; ++u) {
         const uint32_t on = u < n_tot ? 0xffffffffu : 0u, before = u < n_pre ? 0xffffffffu : 0u;
 #pragma unroll
         for (int j = 0; j < PP; ++j) {

@@ -22,6 +22,9 @@ CUTS = [
     (9, 32, 8, 4097, 96),
     (16, 32, 8, 8200, 128),    # 4096, more workgroups than compute units
     (33, 16, 8, 2049, 256),    # uint16 distances
+    # six, nine, ten, thirteen and seventeen tiles: as many histograms at once as the select kernel's instance takes, and more
+    (1, 4, 1, 12001, 128), (1, 4, 1, 17001, 96), (1, 4, 1, 40003, 128), (1, 4, 1, 26001, 64), (2, 8, 2, 66001, 128),
+    (2, 64, 8, 66001, 64),     # segments of 16384 tokens, seventeen tiles
 ]
 
 
