@@ -4,20 +4,17 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plan.hpp"
+
 namespace adamas {
 
 constexpr int kHeadDim = 128;
 constexpr int kRowBytes = 32;        // packed code row of the method (2-bit codes)
-// Code format and distance estimator, one id for both:
-//   kMetricL1   2-bit codes, Eq. 6 (sum of |a - b|, 0..384): the method
-//   kMetricL2   2-bit codes, squared differences (Section 4.4 ablation, 0..1152)
-//   kMetricB1   1-bit codes, Eq. 6 = Hamming distance (Section 4.4, 0..128)
-//   kMetricB3   3-bit codes, Eq. 6 (Section 4.4, 0..896)
+// Code rows and distances of a metric (kMetricL1 ... kMetricB3, see plan.hpp).
 // A code row is four words of kBits 32-bit planes (16 * kBits bytes): plane p of
 // word g holds, at bit j, bit p of the code of coefficient 32g + j.
 // D is the head dimension (128 in the paper's models; 64 and 256 are built for
 // the method itself): D / 32 words per row, distances up to 3 * D.
-constexpr int kMetricL1 = 0, kMetricL2 = 1, kMetricB1 = 2, kMetricB3 = 3;
 template <int METRIC, int D = 128>
 struct Dist {
   static constexpr int kBits = METRIC == kMetricB1 ? 1 : METRIC == kMetricB3 ? 3 : 2;
@@ -93,8 +90,6 @@ struct HeadDim {
   static constexpr int kRowGroup = kRowLanes <= 8 ? 8 : kRowLanes <= 16 ? 16 : 32;
 };
 
-// floats per attention partial of a head of dimension d: m, l, pad, pad, o[d]
-constexpr int partial_stride(int d) { return d + 4; }
 constexpr int kWave = 64;
 
 // D = A B + C on the matrix cores, bf16 in, fp32 out: 16 x 32 by 32 x 16.  Lane l = (n, g) =

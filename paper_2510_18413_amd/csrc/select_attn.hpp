@@ -32,8 +32,6 @@
 namespace adamas {
 
 constexpr int kSelTokPerThread = 16;
-constexpr int kHistBatch = 16;               // tiles whose histograms are loaded together
-constexpr int kMaxParts = 16;  // attention partial slots per head in the workspace
 constexpr int kMaxK = 4096;
 constexpr float kNegBig = -1.0e30f;
 

@@ -1,0 +1,33 @@
+"""The launch plan of the library (csrc/plan.hpp), compiled by itself: the cut that a call gets."""
+
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+from collections import namedtuple
+
+import paper_2510_18413_amd as A
+from paper_2510_18413_amd import build as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+Cut = namedtuple("Cut", "tile parts n_tiles scratch")
+
+
+@functools.lru_cache(maxsize=1)
+def _lib():
+    with tempfile.TemporaryDirectory() as tmp:
+        so = os.path.join(tmp, "scan_plan.so")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-fPIC", "-shared", "-I", str(B.ROOT / "include"),
+                        "-I", str(B.CSRC), os.path.join(HERE, "scan_plan.cpp"), "-o", so], check=True)
+        return ctypes.CDLL(so)
+
+
+def cut(cfg, batch, max_seq_len, k=64):
+    got = (ctypes.c_int64 * 4)()
+    _lib().scan_plan(ctypes.byref(cfg), ctypes.c_int32(batch), ctypes.c_int64(max_seq_len), ctypes.c_int32(k), got)
+    return Cut(*got)
+
+
+def config(heads, kv_heads, batch=1, context=1, **kw):
+    return A.Config.make(heads, kv_heads, max(1, batch * context), **kw)
