@@ -250,8 +250,11 @@ int adamas_decode_step(const adamas_config *cfg, const void *q,
  * ADAMAS_STATIC_SCRATCH_BYTES that is part of the library's code object; every
  * GPU the library runs on holds its own copy until the process ends.  The call
  * allocates and frees nothing.  Sizes whose scratch would exceed the array
- * (adamas_workspace_bytes(cfg, batch, max_seq_len, k) >
- * ADAMAS_STATIC_SCRATCH_BYTES) -> ADAMAS_ERR_WORKSPACE, nothing enqueued.
+ * -> ADAMAS_ERR_WORKSPACE, nothing enqueued.  Every size with
+ * adamas_workspace_bytes(cfg, batch, max_seq_len, k) <=
+ * ADAMAS_STATIC_SCRATCH_BYTES fits, and some larger ones, for which the call
+ * cuts the scan so that it needs the least scratch (the others cut it so that
+ * it takes the least time).
  * All calls on one GPU share that GPU's array: two calls whose work may overlap
  * on one GPU (different streams, different threads) race; calls on one stream
  * are ordered and safe.  The first call on each device looks the array's

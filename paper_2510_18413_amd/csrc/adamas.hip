@@ -464,8 +464,9 @@ int adamas_sparse_attn(const adamas_config* cfg, const void* q, const void* K, c
 }
 
 namespace {
-int decode_step_impl(const adamas_config* cfg, const void* q, const void* k_new, const void* v_new,
-                     void* K, void* V, void* codes, const int64_t* seq_start,
+// given: the plan to run, if it is not the one that make_plan chooses.
+int decode_step_impl(const adamas_config* cfg, const Plan* given, const void* q, const void* k_new,
+                     const void* v_new, void* K, void* V, void* codes, const int64_t* seq_start,
                      const int32_t* page_table, int32_t max_pages, int32_t page_shift,
                      const int32_t* seq_len, int32_t batch, int32_t k, float* out, int32_t* idx_out,
                      int64_t max_seq_len, void* workspace, size_t workspace_bytes, void* stream,
@@ -489,16 +490,16 @@ int adamas_decode_step_static(const adamas_config* cfg, const void* q, const voi
                               void* stream) {
   if (int rc = check_config(cfg)) return rc;
   if (int rc = check_sizes(batch, max_seq_len, k)) return rc;
-  if (make_plan(cfg, batch, max_seq_len, k).total > (size_t)ADAMAS_STATIC_SCRATCH_BYTES)
-    return ADAMAS_ERR_WORKSPACE;
+  const Plan pl = make_plan_within(ADAMAS_STATIC_SCRATCH_BYTES, cfg, batch, max_seq_len, k);
+  if (pl.total > (size_t)ADAMAS_STATIC_SCRATCH_BYTES) return ADAMAS_ERR_WORKSPACE;
   if (!q || !K || !V || !codes || !seq_start || !seq_len || !out) return ADAMAS_ERR_BAD_ARG;
   void* ws = static_scratch();
   if (ws == nullptr) return ADAMAS_ERR_HIP;
   // Nothing in the scratch has to start at zero: the scan kernel clears the
   // arrival counters it hands to the select kernel, everything else is written
   // before it is read.
-  return adamas_decode_step(cfg, q, k_new, v_new, K, V, codes, seq_start, seq_len, batch, k, out,
-                            idx_out, max_seq_len, ws, (size_t)ADAMAS_STATIC_SCRATCH_BYTES, stream);
+  return decode_step_impl(cfg, &pl, q, k_new, v_new, K, V, codes, seq_start, nullptr, 0, 0, seq_len, batch, k, out,
+                          idx_out, max_seq_len, ws, (size_t)ADAMAS_STATIC_SCRATCH_BYTES, stream, ADAMAS_STAGE_ALL);
 }
 
 int adamas_decode_step_stages(const adamas_config* cfg, const void* q, const void* k_new,
@@ -508,7 +509,7 @@ int adamas_decode_step_stages(const adamas_config* cfg, const void* q, const voi
                               void* workspace, size_t workspace_bytes, void* stream,
                               uint32_t stages) {
   if (seq_start == nullptr) return ADAMAS_ERR_BAD_ARG;
-  return decode_step_impl(cfg, q, k_new, v_new, K, V, codes, seq_start, nullptr, 0, 0, seq_len,
+  return decode_step_impl(cfg, nullptr, q, k_new, v_new, K, V, codes, seq_start, nullptr, 0, 0, seq_len,
                           batch, k, out, idx_out, max_seq_len, workspace, workspace_bytes, stream,
                           stages);
 }
@@ -528,7 +529,7 @@ int adamas_decode_step_paged(const adamas_config* cfg, const void* q, const void
   if (max_seq_len > (int64_t)max_pages * page_tokens) return ADAMAS_ERR_BAD_ARG;
   int shift = 0;
   while ((1 << shift) < page_tokens) ++shift;
-  return decode_step_impl(cfg, q, k_new, v_new, K, V, codes, nullptr, page_table, max_pages, shift,
+  return decode_step_impl(cfg, nullptr, q, k_new, v_new, K, V, codes, nullptr, page_table, max_pages, shift,
                           seq_len, batch, k, out, idx_out, max_seq_len, workspace, workspace_bytes,
                           stream, stages);
 }
@@ -536,8 +537,8 @@ int adamas_decode_step_paged(const adamas_config* cfg, const void* q, const void
 }  // extern "C"
 
 namespace {
-int decode_step_impl(const adamas_config* cfg, const void* q, const void* k_new, const void* v_new,
-                     void* K, void* V, void* codes, const int64_t* seq_start,
+int decode_step_impl(const adamas_config* cfg, const Plan* given, const void* q, const void* k_new,
+                     const void* v_new, void* K, void* V, void* codes, const int64_t* seq_start,
                      const int32_t* page_table, int32_t max_pages, int32_t page_shift,
                      const int32_t* seq_len, int32_t batch, int32_t k, float* out, int32_t* idx_out,
                      int64_t max_seq_len, void* workspace, size_t workspace_bytes, void* stream,
@@ -551,7 +552,7 @@ int decode_step_impl(const adamas_config* cfg, const void* q, const void* k_new,
   if (!aligned16(q) || !aligned16(K) || !aligned16(V) || !aligned16(codes)) return ADAMAS_ERR_BAD_ARG;
   if (k_new && (!aligned16(k_new) || !aligned16(v_new))) return ADAMAS_ERR_BAD_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return ADAMAS_ERR_BAD_ARG;
-  const Plan pl = make_plan(cfg, batch, max_seq_len, k);
+  const Plan pl = given != nullptr ? *given : make_plan(cfg, batch, max_seq_len, k);
   if (workspace_bytes < pl.total) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();

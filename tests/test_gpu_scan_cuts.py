@@ -57,14 +57,39 @@ def test_step_at_every_cut_of_the_scan(oracle, B, Hq, Hkv, L, d):
 
 
 def test_the_static_array_takes_every_shape_that_fits_with_the_fewest_histograms():
-    """Tiles of 4096 tokens need the least scratch: a call that fits with them is never refused because the plan
-    would rather have smaller ones."""
-    for group, kv, batch in [(1, 32, 1), (4, 8, 3), (4, 8, 11), (8, 2, 20), (2, 8, 7), (4, 1, 150)]:
+    """Tiles of 4096 tokens need the least scratch: the static call is never refused because the plan would rather have
+    smaller ones.  (No pointer is given, so a call that fits ends at the check behind the one of its scratch.)"""
+    lib = A.library()
+
+    def fits(cfg, batch, L):
+        rc = lib.adamas_decode_step_static(cfg, None, None, None, None, None, None, None, None, batch, 64, None, None, L, None)
+        assert rc in (-1, -3)
+        return rc == -1
+
+    for group, kv, batch in [(1, 32, 1), (4, 8, 3), (4, 8, 11), (8, 2, 20), (2, 8, 7), (4, 1, 150), (4, 8, 16), (4, 8, 41)]:
         heads = batch * kv * group
         cfg = A.Config.make(kv * group, kv, 1 << 22)
-        fits = lambda L: A.adamas_workspace_bytes(cfg, batch, L, 64) <= A.STATIC_SCRATCH_BYTES
         for L in range(700, 1 << 17, 1777):
             tiles = -(-L // 4096)
             least = heads * (-(-L // 128) * 128) * 9 // 8 + (heads * tiles + 16) * 193 * 4 + heads * 16 * 132 * 4 + 4 * 256
             if least <= A.STATIC_SCRATCH_BYTES:
-                assert fits(L), (group, kv, batch, L)
+                assert fits(cfg, batch, L), (group, kv, batch, L)
+            if A.adamas_workspace_bytes(cfg, batch, L, 64) <= A.STATIC_SCRATCH_BYTES:
+                assert fits(cfg, batch, L), (group, kv, batch, L)
+
+
+@pytest.mark.gpu
+def test_the_static_step_with_the_fewest_histograms(oracle):
+    """A shape that fits the static array only with tiles of 4096 tokens, while the plan takes 2048: same results."""
+    from gpu_harness import ATTN_TOL, DeviceCase, attn_rel_err, oracle_step
+    B, L, k = 41, 2560, 48
+    case = synth.make_case("static cut", 31, B, 32, 8, [L - 5 * b for b in range(B)], [0],
+                           lambda b, Lc, h, rng: rng.choice(Lc, size=(4, 1), replace=False), append=True)
+    dc = DeviceCase(case, k)
+    assert A.adamas_workspace_bytes(dc.cfg, B, dc.max_len, k) > A.STATIC_SCRATCH_BYTES
+    A.adamas_decode_step_static(dc.cfg, dc.q, dc.K, dc.V, dc.codes, dc.seq_start, dc.seq_len, k, dc.out, dc.max_len,
+                                k_new=dc.k_new, v_new=dc.v_new, idx_out=dc.idx)
+    torch.cuda.synchronize()
+    want = oracle_step(case, k)
+    assert np.array_equal(dc.idx.cpu().numpy(), want["idx"])
+    assert attn_rel_err(dc.out.cpu().numpy(), want["out"]) <= ATTN_TOL
