@@ -160,7 +160,9 @@ const char *adamas_build_id(void);
 int adamas_last_hip_error(void);
 
 /* Bytes of workspace the calls below need for these sizes; 0 if the
- * arguments are invalid or unsupported.  Host-only, enqueues nothing. */
+ * arguments are invalid or unsupported.  Host-only, enqueues nothing.
+ * Never less for a larger batch or max_seq_len: a workspace for a program's
+ * largest call serves its smaller ones. */
 size_t adamas_workspace_bytes(const adamas_config *cfg, int32_t batch,
                               int64_t max_seq_len, int32_t k);
 

@@ -277,7 +277,7 @@ int adamas_phase_trace(void* scan_records, void* select_records, int64_t n_recor
 size_t adamas_workspace_bytes(const adamas_config* cfg, int32_t batch, int64_t max_seq_len,
                               int32_t k) {
   if (check_config(cfg) != ADAMAS_OK || check_sizes(batch, max_seq_len, k) != ADAMAS_OK) return 0;
-  return make_plan(cfg, batch, max_seq_len, k).total;
+  return workspace_need(cfg, batch, max_seq_len);
 }
 
 int adamas_encode_keys(const adamas_config* cfg, const void* K, void* codes, int64_t row_begin,
@@ -344,7 +344,7 @@ int adamas_select_topk(const adamas_config* cfg, const void* qcodes, const void*
   if (!aligned16(codes) || !aligned16(qcodes)) return ADAMAS_ERR_BAD_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return ADAMAS_ERR_BAD_ARG;
   const Plan pl = make_plan(cfg, batch, max_seq_len, k);
-  if (workspace_bytes < pl.total) return ADAMAS_ERR_WORKSPACE;
+  if (workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
 
@@ -401,7 +401,7 @@ int adamas_sparse_attn(const adamas_config* cfg, const void* q, const void* K, c
   if (!aligned16(q) || !aligned16(K) || !aligned16(V)) return ADAMAS_ERR_BAD_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return ADAMAS_ERR_BAD_ARG;
   const Plan pl = make_plan(cfg, batch, max_seq_len, k);
-  if (workspace_bytes < pl.total) return ADAMAS_ERR_WORKSPACE;
+  if (workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
   AttnParams ap{};
@@ -553,7 +553,7 @@ int decode_step_impl(const adamas_config* cfg, const Plan* given, const void* q,
   if (k_new && (!aligned16(k_new) || !aligned16(v_new))) return ADAMAS_ERR_BAD_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return ADAMAS_ERR_BAD_ARG;
   const Plan pl = given != nullptr ? *given : make_plan(cfg, batch, max_seq_len, k);
-  if (workspace_bytes < pl.total) return ADAMAS_ERR_WORKSPACE;
+  if (given == nullptr && workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
 

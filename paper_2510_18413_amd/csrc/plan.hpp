@@ -65,10 +65,8 @@ inline bool high_plane_of(int metric, int head_dim) {
   return m > 255 && m <= 511;
 }
 
-// Tiles and offsets that follow from tile_tokens, the metric and the head dimension.
-inline void lay_out(Plan* pl, const adamas_config* c, int32_t batch, int64_t max_seq_len) {
-  const size_t heads = (size_t)batch * c->num_q_heads;
-  pl->n_tiles = (int)((max_seq_len + pl->tile_tokens - 1) / pl->tile_tokens);
+// Offsets for so many tile histograms.
+inline void lay_out(Plan* pl, size_t heads, int64_t max_seq_len, size_t histograms) {
   pl->dist_stride = (max_seq_len + 127) & ~(int64_t)127;
   size_t off = 0;
   pl->off_dist = off;
@@ -76,11 +74,34 @@ inline void lay_out(Plan* pl, const adamas_config* c, int32_t batch, int64_t max
   pl->off_high = off;
   if (high_plane_of(pl->metric, pl->head_dim)) off = align256(off + heads * (size_t)pl->dist_stride / 8);
   pl->off_hist = off;
-  // + kHistBatch rows: the select kernel reads whole batches of tile rows, also behind the last head's
-  off = align256(off + (heads * (size_t)pl->n_tiles + kHistBatch) * hist_pairs_of(pl->metric, pl->head_dim) * sizeof(uint32_t));
+  // + kHistBatch: the select kernel reads whole batches of them, also behind the last head's
+  off = align256(off + (histograms + kHistBatch) * hist_pairs_of(pl->metric, pl->head_dim) * sizeof(uint32_t));
   pl->off_partial = off;
   off = align256(off + heads * (size_t)kMaxParts * partial_stride(pl->head_dim) * sizeof(float));
   pl->total = off;
+}
+
+// Tiles and offsets that follow from tile_tokens, the metric and the head dimension.
+inline void lay_out(Plan* pl, const adamas_config* c, int32_t batch, int64_t max_seq_len) {
+  const size_t heads = (size_t)batch * c->num_q_heads;
+  pl->n_tiles = (int)((max_seq_len + pl->tile_tokens - 1) / pl->tile_tokens);
+  lay_out(pl, heads, max_seq_len, heads * (size_t)pl->n_tiles);
+}
+
+// Bytes that the calls of these sizes ask for, whatever their plan: never less for more sequences or a longer context, so that a
+// workspace for a program's largest call holds all its smaller ones.  (The plans' own totals are not: a smaller call may
+// take smaller tiles, which leave more histograms.)  Tiles are of 2048 tokens or more, except where fewer than two of
+// 1024 per compute unit exist, or the context is no longer than one.
+inline size_t workspace_need(const adamas_config* c, int32_t batch, int64_t max_seq_len) {
+  Plan pl{};
+  pl.metric = metric_of(c);
+  pl.head_dim = c->head_dim;
+  const size_t heads = (size_t)batch * c->num_q_heads, group = (size_t)(c->num_q_heads / c->num_kv_heads);
+  const size_t large = heads * (size_t)((max_seq_len + 2047) / 2048);
+  size_t small = heads * (size_t)((max_seq_len + 1023) / 1024);
+  if (small > 2 * kTargetWorkgroups * group) small = 2 * kTargetWorkgroups * group;
+  lay_out(&pl, heads, max_seq_len, large > small ? large : small);
+  return pl.total;
 }
 
 inline Plan make_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len, int32_t k) {
