@@ -317,7 +317,7 @@ int adamas_manhattan_distance(const adamas_config* cfg, const void* qcodes, cons
   if (!qcodes || !codes || !seq_start || !seq_len || !dist_out) return ADAMAS_ERR_BAD_ARG;
   if (!aligned16(codes) || !aligned16(qcodes)) return ADAMAS_ERR_BAD_ARG;
   clear_stale_error();
-  const Plan pl = make_plan(cfg, batch, max_seq_len, 1);
+  const Plan pl = make_plan(cfg, batch, max_seq_len, ScanUse::kDistances);
   ScanParams sp{};
   sp.codes = static_cast<const uint8_t*>(codes);
   sp.qcodes = static_cast<const uint8_t*>(qcodes);
@@ -343,7 +343,7 @@ int adamas_select_topk(const adamas_config* cfg, const void* qcodes, const void*
   if (!qcodes || !codes || !seq_start || !seq_len || !idx_out || !workspace) return ADAMAS_ERR_BAD_ARG;
   if (!aligned16(codes) || !aligned16(qcodes)) return ADAMAS_ERR_BAD_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return ADAMAS_ERR_BAD_ARG;
-  const Plan pl = make_plan(cfg, batch, max_seq_len, k);
+  const Plan pl = make_plan(cfg, batch, max_seq_len, ScanUse::kSelect);
   if (workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
@@ -400,7 +400,7 @@ int adamas_sparse_attn(const adamas_config* cfg, const void* q, const void* K, c
   if (!q || !K || !V || !seq_start || !idx || !out || !workspace) return ADAMAS_ERR_BAD_ARG;
   if (!aligned16(q) || !aligned16(K) || !aligned16(V)) return ADAMAS_ERR_BAD_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return ADAMAS_ERR_BAD_ARG;
-  const Plan pl = make_plan(cfg, batch, max_seq_len, k);
+  const Plan pl = make_plan(cfg, batch, max_seq_len, ScanUse::kStep);
   if (workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
@@ -490,7 +490,7 @@ int adamas_decode_step_static(const adamas_config* cfg, const void* q, const voi
                               void* stream) {
   if (int rc = check_config(cfg)) return rc;
   if (int rc = check_sizes(batch, max_seq_len, k)) return rc;
-  const Plan pl = make_plan_within(ADAMAS_STATIC_SCRATCH_BYTES, cfg, batch, max_seq_len, k);
+  const Plan pl = make_plan_within(ADAMAS_STATIC_SCRATCH_BYTES, cfg, batch, max_seq_len);
   if (pl.total > (size_t)ADAMAS_STATIC_SCRATCH_BYTES) return ADAMAS_ERR_WORKSPACE;
   if (!q || !K || !V || !codes || !seq_start || !seq_len || !out) return ADAMAS_ERR_BAD_ARG;
   void* ws = static_scratch();
@@ -552,7 +552,7 @@ int decode_step_impl(const adamas_config* cfg, const Plan* given, const void* q,
   if (!aligned16(q) || !aligned16(K) || !aligned16(V) || !aligned16(codes)) return ADAMAS_ERR_BAD_ARG;
   if (k_new && (!aligned16(k_new) || !aligned16(v_new))) return ADAMAS_ERR_BAD_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return ADAMAS_ERR_BAD_ARG;
-  const Plan pl = given != nullptr ? *given : make_plan(cfg, batch, max_seq_len, k);
+  const Plan pl = given != nullptr ? *given : make_plan(cfg, batch, max_seq_len, ScanUse::kStep);
   if (given == nullptr && workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();

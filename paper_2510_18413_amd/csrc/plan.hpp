@@ -104,58 +104,100 @@ inline size_t workspace_need(const adamas_config* c, int32_t batch, int64_t max_
   return pl.total;
 }
 
-inline Plan make_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len, int32_t k) {
-  (void)k;  // the budget does not change the plan: the workspace holds every distance whatever k is
-  Plan pl{};
-  pl.metric = metric_of(c);
-  pl.head_dim = c->head_dim;
-  const int64_t planes = (int64_t)batch * c->num_kv_heads;
-  // Scan: tokens per workgroup (4, 8 or 16 waves of 256) and the share of the query group that it serves (all, half or a
-  // quarter of it, each share reading the rows again).  A compute unit's time goes with the waves that each of its
-  // SIMDs gets, times what a wave does: about as much for the rows, the histogram and the prologue as for one head, and a
-  // share of encoding the queries, which costs 1.5 of that per query and is spread over the waves.  Below 2.5 waves per
-  // SIMD it is the chain of one wave that takes the time.  The select kernel loads the histograms of kHistBatch tiles at
-  // once and pays about four such units for each further batch.  Measured (us per layer, 32 query heads, d = 128; tile /
-  // parts of the group, chosen *):                2048 / 1  2048 / 2  4096 / 1  4096 / 2  4096 / 4
-  //   1 sequence of 20000, group of 4               13.6     12.6*     15.0      13.3      13.1
-  //   1 of 32771                                    14.8     15.6      15.3      14.0*     16.3
-  //   1 of 100000                                   22.3     24.0      19.2*     22.1
-  //   2 of 20011                                    15.2     16.0      16.3      14.7*     17.4
-  //   4 of 30000                                    21.8     24.3      20.9*     22.5
-  //   8 ragged, up to 16000                         24.2     25.4      22.6*     25.6
-  //   16 ragged, up to 32768 (1024 / 1: 44.2)       42.3     47.8      42.1*     53.5
-  //   48 ragged, up to 6001 (1024 / 1: 60.3)        58.5*    60.6      60.3      70.4
-  //   2 of 60000, group of 8                        21.5     20.6      22.6      19.1*     22.9
-  //   4 of 60001, group of 8                        28.2     28.8      26.5*     26.9
-  //   1 of 100000, 16 heads, group of 8             20.3     18.0      21.1      17.5      16.7*
-  //   1 of 32768, group of 1                        16.8*              17.2
-  //   1 of 50000, group of 1                        21.2               20.1*
-  // d = 64, 96, 192 and 256 rank alike (six shapes each).
-  const int group = c->num_q_heads / c->num_kv_heads;
+// What a call has the scan do: the decode step (encodes its queries, leaves distances and tile histograms), top-k on
+// query codes (the same without the encode), or distances for the caller alone.
+enum class ScanUse { kStep, kSelect, kDistances };
+
+// What a cut of the scan costs, in the time that a wave takes for one query head: tiles of `tile` tokens (4, 8 or 16 waves
+// of 256) and `parts` workgroups per tile and KV head, each with its share of the group's heads and reading the rows again.
+// A compute unit's time goes with the waves that each of its SIMDs gets, times what a wave does: about as much for the rows,
+// the histogram and the prologue as for one head, and a share of encoding the queries, twice that per query and spread over
+// the waves.  Below a few waves per SIMD it is the chain of one wave that takes the time.  Parts of a group find the rows in
+// the L2 of their XCD where the number of tiles is a multiple of the eight XCDs (workgroups go round them in launch order), and
+// in memory elsewhere.  The select kernel loads the histograms of kHistBatch tiles at once and pays for each further batch.
+//
+// Measured (us a layer, 32 query heads, d = 128; tile / parts of the group, chosen *; the median spreads by 0.1):
+//                                        1024/1 1024/2 1024/4 2048/1 2048/2 2048/4 4096/1 4096/2 4096/4
+//   step,  1 sequence of 4000, group of 4  13.0   11.9   11.5   12.9   11.7   11.4*  14.2   12.5   11.7
+//          1 of 16384                      13.2   12.1   12.0   12.9   11.8   11.4*  14.1   12.4   11.7
+//          1 of 20000                      13.8   13.8   13.7   13.1   12.1*  13.7   14.4   12.6   12.6
+//          1 of 24576                      14.1   13.5   13.3   13.1   12.2*  13.0   14.2   12.5   13.1
+//          1 of 32768                      14.5   14.1   14.5   13.5   12.5   12.8   14.2   12.5   11.8*
+//          1 of 32771                      16.1   16.3          14.3   15.1   16.3   14.9   13.4*  15.7
+//          1 of 65540                      21.5                 20.0   19.6          17.8*  20.1   22.4
+//          1 of 100000                     25.4                 21.9   23.4          19.2*  22.0   28.1
+//          2 of 20011                      16.4   16.3          14.2   15.2   16.6   15.4   14.0*  16.4
+//          4 of 8000                       15.0   14.5   14.9   14.8   13.9*  14.4   15.9   14.3   15.5
+//          8 of 4000                       15.8   15.7   15.8   15.9   14.7*  16.5   17.0   14.9   16.4
+//          4 of 60000                      32.4                 29.3                 27.7*  35.1
+//          16 of 17408                     36.3                 35.2*                35.5
+//          16 ragged, up to 32768          42.2                 40.6                 40.1*
+//          41 of 2560                      33.3                 33.4*                34.0   36.9
+//          48 ragged, up to 6001           42.2                 41.7*                43.8
+//          1 of 32768, group of 1          17.1                 15.7*                15.6
+//          4 of 32768, group of 1          40.3                 39.6                 38.4*
+//   top-k, 1 of 4000, group of 4            7.7    7.1    6.7*   8.0    7.5    7.1    9.3    8.1    8.0
+//          2 of 20011                      12.2   12.0          10.5   11.1   12.8   11.0   10.2*  12.7
+//          16 of 3000                      11.2   11.3          10.5*  11.1   14.4   10.9   11.7   13.7
+//   distances, 4 of 8000, group of 2        4.7    4.4           4.9    5.4           5.4    5.4
+// With three-bit codes the sixteen-wave workgroups of the step spill registers from d = 160 on (1 sequence of 32771, d = 256, group
+// of 1: 54.0, 49.2*, 59.8 with tiles of 1024, 2048 and 4096).  Over 972 shapes (d = 64 to 256, groups of 1 to 8, all code
+// formats, paged or not) the step's choice is 0.4 % above the best cut on average, top-k's 1.3 and that of the distances alone 3.0;
+// where the step's is furthest off (4 to 11 %) the codes are three-bit, or eight heads share a row and two rounds of parts would pay.
+inline double scan_cost(ScanUse use, int metric, int head_dim, int64_t n_wg, int64_t n_tiles, int tile, int group, int parts) {
+  const bool step = use == ScanUse::kStep;
+  const int wg_waves = tile / 256, heads = group / parts;
+  // whole rounds while there are few, the average beyond
+  const double rounds = n_wg < 4 * kTargetWorkgroups ? (double)((n_wg + kTargetWorkgroups - 1) / kTargetWorkgroups)
+                                                     : (double)n_wg / kTargetWorkgroups;
+  const double waves = std::fmax(step ? 2.5 : 1.1, rounds * wg_waves / 4);
+  const double head = metric == kMetricL2 || metric == kMetricB3 ? 1.2 : 1.0;
+  double per_wave = 1.0 + heads * head;
+  if (n_tiles % 8 != 0) per_wave += 0.25 * (parts - 1) / parts;
+  if (step) per_wave += 2.0 * heads / wg_waves;
+  // small workgroups clear and flush as many histograms for fewer tokens
+  if (wg_waves == 4) per_wave *= step ? 1.25 : 1.08;
+  if (wg_waves == 16 && !step && group > 1) per_wave *= 0.8;
+  if (wg_waves == 16 && metric == kMetricB3 && head_dim >= 160) per_wave *= 1.06;
+  // One head per row is bound by memory.  Where tiles of 4096 give every compute unit one workgroup, tiles of 2048 give it two, which
+  // keep it a little busier if they do not fall on the same channels: 32 planes of 32768 16.2 / 16.4 (16.8 / 17.2 with other
+  // caches), 64 of 16384 17.65 / 17.95, 16 planes of two sequences of 32768 17.7 / 16.3.  With units left over the halves are uneven:
+  // 32 planes of 20480, 28672 and 36864 15.0 / 14.5, 16.0 / 15.8, 18.5 / 19.3; 8 of 72228 and 131072 16.4 / 14.8, 18.8 / 17.8.
+  if (group == 1 && wg_waves == 16 && n_wg == kTargetWorkgroups) per_wave *= 1.1;
+  double cost = waves * per_wave + 0.0125 * wg_waves;  // (the smaller workgroup where nothing else tells them apart)
+  if (use != ScanUse::kDistances)
+    cost += 4.0 * (double)((n_tiles + kHistBatch - 1) / kHistBatch - 1) + 0.4 * (double)n_tiles / kHistBatch;
+  return cost;
+}
+
+// Sets tile_tokens and g_shift.
+inline void choose_cut(Plan* pl, ScanUse use, int group, int64_t planes, int64_t max_seq_len) {
   auto n_tiles_of = [&](int tile) { return (max_seq_len + tile - 1) / tile; };
   double best = 0.0;
   for (int tile = 4096; tile >= 1024; tile /= 2) {
     if (tile > 1024 && tile >= 2 * max_seq_len) continue;
-    // with workgroups for half of the compute units or more, tiles of 1024 lose
-    if (tile == 1024 && pl.tile_tokens != 0 && planes * n_tiles_of(2048) >= kTargetWorkgroups / 2) break;
+    // never more tiles than two per compute unit in exchange for smaller ones
+    if (tile == 1024 && pl->tile_tokens != 0 && planes * n_tiles_of(2048) >= kTargetWorkgroups) break;
     for (int shift = 0; shift <= 2 && group % (1 << shift) == 0; ++shift) {
       const int64_t n_wg = planes * n_tiles_of(tile) << shift;
       if (shift > 0 && n_wg > kTargetWorkgroups) break;
-      // whole rounds while there are few, the average beyond
-      const double per_unit = n_wg < 4 * kTargetWorkgroups ? (double)((n_wg + kTargetWorkgroups - 1) / kTargetWorkgroups)
-                                                           : (double)n_wg / kTargetWorkgroups;
-      const double waves = std::fmax(2.5, per_unit * (tile / 1024)), heads = group >> shift;
-      double cost = waves * (1.0 + heads + 1.5 * heads / (tile / 256)) +
-                    4.0 * (double)((n_tiles_of(tile) + kHistBatch - 1) / kHistBatch - 1);
-      // one head per row is bound by memory, and two workgroups per unit keep that busier than one (32 planes of 32768: see above)
-      if (group == 1 && tile == 4096 && n_wg <= kTargetWorkgroups) cost *= 1.1;
-      if (pl.tile_tokens == 0 || cost < best) {
+      const double cost =
+          scan_cost(use, pl->metric, pl->head_dim, n_wg, n_tiles_of(tile), tile, group, 1 << shift);
+      if (pl->tile_tokens == 0 || cost < best) {
         best = cost;
-        pl.tile_tokens = tile;
-        pl.g_shift = shift;
+        pl->tile_tokens = tile;
+        pl->g_shift = shift;
       }
     }
   }
+}
+
+// (The budget does not change the plan: the workspace holds every distance whatever it is.)
+inline Plan make_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len, ScanUse use) {
+  Plan pl{};
+  pl.metric = metric_of(c);
+  pl.head_dim = c->head_dim;
+  choose_cut(&pl, use, c->num_q_heads / c->num_kv_heads, (int64_t)batch * c->num_kv_heads, max_seq_len);
   // Select + attention: a head is cut into segments, one workgroup each (a
   // single compute unit is too slow to compact a whole 32K-token head or to
   // gather all of its rows), and the segments' attention partials are merged
@@ -178,8 +220,8 @@ inline Plan make_plan(const adamas_config* c, int32_t batch, int64_t max_seq_len
 // The plan of a call whose scratch is an array of a given size: the chosen one where it fits, else the one with the
 // fewest histograms (tiles of 4096 tokens), which needs the least.  Not for calls that bring a workspace: these have the cut that
 // takes the least time (41 sequences of 2560 tokens, 32 heads over 8 KV heads: 33.4 us a layer, 34.0 with the fewest histograms).
-inline Plan make_plan_within(size_t bytes, const adamas_config* c, int32_t batch, int64_t max_seq_len, int32_t k) {
-  const Plan chosen = make_plan(c, batch, max_seq_len, k);
+inline Plan make_plan_within(size_t bytes, const adamas_config* c, int32_t batch, int64_t max_seq_len) {
+  const Plan chosen = make_plan(c, batch, max_seq_len, ScanUse::kStep);
   if (chosen.total <= bytes) return chosen;
   Plan least = chosen;
   least.tile_tokens = 4096;

@@ -23,9 +23,12 @@ def _lib():
         return ctypes.CDLL(so)
 
 
-def cut(cfg, batch, max_seq_len, k=64):
+STEP, TOPK, DISTANCES, STATIC = range(4)
+
+
+def cut(cfg, batch, max_seq_len, use=STEP):
     got = (ctypes.c_int64 * 4)()
-    _lib().scan_plan(ctypes.byref(cfg), ctypes.c_int32(batch), ctypes.c_int64(max_seq_len), ctypes.c_int32(k), got)
+    _lib().scan_plan(ctypes.byref(cfg), ctypes.c_int32(batch), ctypes.c_int64(max_seq_len), ctypes.c_int32(use), got)
     return Cut(*got)
 
 

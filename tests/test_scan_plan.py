@@ -10,10 +10,11 @@ import paper_2510_18413_amd as A
 def test_every_cut_divides_the_group_and_covers_the_context(heads, kv, d):
     for batch in (1, 3, 16, 200):
         for L in (1, 63, 1024, 1025, 4097, 32771, 200001, 1 << 20):
-            c = P.cut(P.config(heads, kv, head_dim=d), batch, L)
-            assert c.tile in (1024, 2048, 4096) and (heads // kv) % c.parts == 0
-            assert (c.n_tiles - 1) * c.tile < L <= c.n_tiles * c.tile
-            assert c.scratch <= A.adamas_workspace_bytes(P.config(heads, kv, head_dim=d), batch, L, 64)
+            for use in (P.STEP, P.TOPK, P.DISTANCES, P.STATIC):
+                c = P.cut(P.config(heads, kv, head_dim=d), batch, L, use)
+                assert c.tile in (1024, 2048, 4096) and (heads // kv) % c.parts == 0
+                assert (c.n_tiles - 1) * c.tile < L <= c.n_tiles * c.tile
+                assert c.scratch <= A.adamas_workspace_bytes(P.config(heads, kv, head_dim=d), batch, L, 64)
 
 
 @pytest.mark.parametrize("batch,L", [(16, 17408), (12, 24576), (41, 2560)])
@@ -32,7 +33,7 @@ def test_a_workspace_for_the_largest_call_serves_the_smaller_ones(heads, kv, kw)
         last = 0
         for L in list(range(1, 60000, 509)) + [1 << 17, 200000, 1 << 20]:
             here = need(batch, L)
-            assert here >= last and here >= P.cut(cfg, batch, L).scratch, (batch, L)
+            assert here >= last and here >= max(P.cut(cfg, batch, L, use).scratch for use in range(4)), (batch, L)
             last = here
     for L in (700, 1024, 2560, 8192, 21248, 32768):
         sizes = [need(batch, L) for batch in range(1, 80)]
@@ -43,3 +44,28 @@ def test_a_workspace_for_the_largest_call_serves_the_smaller_ones(heads, kv, kw)
         assert max(need(b, 32768) for b in range(1, 12)) <= need(12, 32768)
     if (heads, kv) == (32, 32):
         assert max(need(8, L) for L in range(28800, 30721, 128)) <= need(8, 32768)
+
+
+# The shapes that the plan was measured at (see scan_cost): use, heads, KV heads, batch, context, (tile, parts) chosen
+MEASURED = [
+    (P.STEP, 32, 8, 1, 4000, (2048, 4)), (P.STEP, 32, 8, 1, 16384, (2048, 4)), (P.STEP, 32, 8, 1, 20000, (2048, 2)),
+    (P.STEP, 32, 8, 1, 24576, (2048, 2)), (P.STEP, 32, 8, 1, 32768, (4096, 4)), (P.STEP, 32, 8, 1, 32771, (4096, 2)),
+    (P.STEP, 32, 8, 1, 65540, (4096, 1)), (P.STEP, 32, 8, 1, 100000, (4096, 1)), (P.STEP, 32, 8, 2, 20011, (4096, 2)),
+    (P.STEP, 32, 8, 4, 8000, (2048, 2)), (P.STEP, 32, 8, 8, 4000, (2048, 2)), (P.STEP, 32, 8, 4, 60000, (4096, 1)),
+    (P.STEP, 32, 8, 16, 17408, (2048, 1)), (P.STEP, 32, 8, 16, 32768, (4096, 1)), (P.STEP, 32, 8, 41, 2560, (2048, 1)),
+    (P.STEP, 32, 8, 48, 6001, (2048, 1)), (P.STEP, 32, 32, 1, 32768, (2048, 1)), (P.STEP, 32, 32, 4, 32768, (4096, 1)),
+    (P.TOPK, 32, 8, 1, 4000, (1024, 4)), (P.TOPK, 32, 8, 2, 20011, (4096, 2)), (P.TOPK, 32, 8, 16, 3000, (2048, 1)),
+    (P.DISTANCES, 16, 8, 4, 8000, (1024, 1)),
+]
+
+
+@pytest.mark.parametrize("use,heads,kv,batch,L,chosen", MEASURED)
+def test_the_cut_that_was_measured_as_the_best_is_the_one_chosen(use, heads, kv, batch, L, chosen):
+    c = P.cut(P.config(heads, kv), batch, L, use)
+    assert (c.tile, c.parts) == chosen
+
+
+def test_cuts_of_spilling_instances():
+    three = dict(code_bits=3, thr_k=(-1.5, -1.0, -0.5, 0.0, 0.5, 1.0, 1.5), head_dim=256)
+    c = P.cut(P.config(32, 32, **three), 1, 32771)
+    assert (c.tile, c.parts) == (2048, 1)
