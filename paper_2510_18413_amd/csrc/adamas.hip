@@ -165,13 +165,14 @@ int launch_status() {
   return ADAMAS_OK;
 }
 
-// pl.tile_tokens is 1024, 2048 or 4096 (make_plan).
-void launch_scan(const adamas_config* c, bool fused, const Plan& pl, int batch, hipStream_t st,
-                 ScanParams sp) {
-  const int group = c->num_q_heads / c->num_kv_heads;
+// Launches the scan as the plan cuts it.
+int launch_scan(const adamas_config* c, bool fused, const Plan& pl, int batch, hipStream_t st,
+                ScanParams sp) {
+  const int heads = heads_per_part(c->num_q_heads / c->num_kv_heads, pl.g_shift);
   sp.g_shift = pl.g_shift;
   const dim3 grid(pl.n_tiles, c->num_kv_heads << pl.g_shift, batch);
-  set_of(c).scan(fused, group >> pl.g_shift, pl.tile_tokens, grid, st, sp);
+  if (heads == 0 || !set_of(c).scan(fused, heads, pl.tile_tokens, grid, st, sp)) return ADAMAS_ERR_UNSUPPORTED;
+  return launch_status();
 }
 
 struct FullPlan {
@@ -330,8 +331,7 @@ int adamas_manhattan_distance(const adamas_config* cfg, const void* qcodes, cons
   sp.Hq = cfg->num_q_heads;
   sp.Hkv = cfg->num_kv_heads;
   sp.n_tiles = pl.n_tiles;
-  launch_scan(cfg, false, pl, batch, (hipStream_t)stream, sp);
-  return launch_status();
+  return launch_scan(cfg, false, pl, batch, (hipStream_t)stream, sp);
 }
 
 int adamas_select_topk(const adamas_config* cfg, const void* qcodes, const void* codes,
@@ -364,8 +364,7 @@ int adamas_select_topk(const adamas_config* cfg, const void* qcodes, const void*
   sp.Hq = cfg->num_q_heads;
   sp.Hkv = cfg->num_kv_heads;
   sp.n_tiles = pl.n_tiles;
-  launch_scan(cfg, false, pl, batch, st, sp);
-  if (int rc = launch_status()) return rc;
+  if (int rc = launch_scan(cfg, false, pl, batch, st, sp)) return rc;
 
   SelectParams sl{};
   sl.dist = sp.dist;
@@ -587,8 +586,7 @@ int decode_step_impl(const adamas_config* cfg, const Plan* given, const void* q,
   sp.trace = g_trace_scan;
   sp.trace_records = g_trace_records;
   if (stages & ADAMAS_STAGE_SCAN) {
-    launch_scan(cfg, true, pl, batch, st, sp);
-    if (int rc = launch_status()) return rc;
+    if (int rc = launch_scan(cfg, true, pl, batch, st, sp)) return rc;
   }
   if (!(stages & ADAMAS_STAGE_SELECT_ATTN)) return ADAMAS_OK;
 

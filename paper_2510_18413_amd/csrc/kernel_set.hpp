@@ -21,8 +21,9 @@ namespace adamas {
 struct KernelSet {
   // Distance scan.  fused: query encode + append in the prologue (decode step);
   // paged cache iff sp.page_table != nullptr (fused only).  G = query heads per
-  // workgroup (1..8), tile_tokens = 1024, 2048 or 4096.
-  void (*scan)(bool fused, int G, int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp);
+  // workgroup (1..8), tile_tokens = 1024, 2048 or 4096; false, and nothing
+  // launched, for any other.
+  bool (*scan)(bool fused, int G, int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp);
   // Top-k (+ gather + attention when attn).  256 threads per workgroup.
   void (*select)(bool attn, bool paged, dim3 grid, hipStream_t st, const SelectParams& sl);
   // Bulk encode of n_vec vectors.  Null in the squared-distance set: its code

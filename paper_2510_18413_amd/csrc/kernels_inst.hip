@@ -17,31 +17,34 @@ constexpr int BITS = Dist<METRIC, D>::kBits;
 constexpr int kSelThreads = 256;
 
 template <int G, bool FUSED, bool PAGED>
-void launch_scan_tile(int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp) {
+bool launch_scan_tile(int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp) {
   switch (tile_tokens) {
-    case 1024: hipLaunchKernelGGL((scan_kernel<G, FUSED, 4, METRIC, PAGED, D>), grid, dim3(256), 0, st, sp); break;
-    case 2048: hipLaunchKernelGGL((scan_kernel<G, FUSED, 8, METRIC, PAGED, D>), grid, dim3(512), 0, st, sp); break;
-    default: hipLaunchKernelGGL((scan_kernel<G, FUSED, 16, METRIC, PAGED, D>), grid, dim3(1024), 0, st, sp); break;
+    case 1024: hipLaunchKernelGGL((scan_kernel<G, FUSED, 4, METRIC, PAGED, D>), grid, dim3(256), 0, st, sp); return true;
+    case 2048: hipLaunchKernelGGL((scan_kernel<G, FUSED, 8, METRIC, PAGED, D>), grid, dim3(512), 0, st, sp); return true;
+    case 4096: hipLaunchKernelGGL((scan_kernel<G, FUSED, 16, METRIC, PAGED, D>), grid, dim3(1024), 0, st, sp); return true;
+    default: return false;
   }
 }
 
 template <int G>
-void launch_scan_g(bool fused, int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp) {
+bool launch_scan_g(bool fused, int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp) {
   if (!fused) return launch_scan_tile<G, false, false>(tile_tokens, grid, st, sp);
   if (sp.page_table != nullptr) return launch_scan_tile<G, true, true>(tile_tokens, grid, st, sp);
-  launch_scan_tile<G, true, false>(tile_tokens, grid, st, sp);
+  return launch_scan_tile<G, true, false>(tile_tokens, grid, st, sp);
 }
 
-void launch_scan(bool fused, int G, int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp) {
+// (a kernel of more heads than the caller's grid is cut for would read and write heads beyond the tensors)
+bool launch_scan(bool fused, int G, int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp) {
   switch (G) {
-    case 1: launch_scan_g<1>(fused, tile_tokens, grid, st, sp); break;
-    case 2: launch_scan_g<2>(fused, tile_tokens, grid, st, sp); break;
-    case 3: launch_scan_g<3>(fused, tile_tokens, grid, st, sp); break;
-    case 4: launch_scan_g<4>(fused, tile_tokens, grid, st, sp); break;
-    case 5: launch_scan_g<5>(fused, tile_tokens, grid, st, sp); break;
-    case 6: launch_scan_g<6>(fused, tile_tokens, grid, st, sp); break;
-    case 7: launch_scan_g<7>(fused, tile_tokens, grid, st, sp); break;
-    default: launch_scan_g<8>(fused, tile_tokens, grid, st, sp); break;
+    case 1: return launch_scan_g<1>(fused, tile_tokens, grid, st, sp);
+    case 2: return launch_scan_g<2>(fused, tile_tokens, grid, st, sp);
+    case 3: return launch_scan_g<3>(fused, tile_tokens, grid, st, sp);
+    case 4: return launch_scan_g<4>(fused, tile_tokens, grid, st, sp);
+    case 5: return launch_scan_g<5>(fused, tile_tokens, grid, st, sp);
+    case 6: return launch_scan_g<6>(fused, tile_tokens, grid, st, sp);
+    case 7: return launch_scan_g<7>(fused, tile_tokens, grid, st, sp);
+    case 8: return launch_scan_g<8>(fused, tile_tokens, grid, st, sp);
+    default: return false;
   }
 }
 

@@ -170,6 +170,11 @@ inline double scan_cost(ScanUse use, int metric, int head_dim, int64_t n_wg, int
   return cost;
 }
 
+// Query heads per workgroup if 2^g_shift of them share a group; 0 if they cannot share it evenly.
+inline int heads_per_part(int group, int g_shift) {
+  return g_shift >= 0 && g_shift <= 3 && group % (1 << g_shift) == 0 ? group >> g_shift : 0;
+}
+
 // Sets tile_tokens and g_shift.
 inline void choose_cut(Plan* pl, ScanUse use, int group, int64_t planes, int64_t max_seq_len) {
   auto n_tiles_of = [&](int tile) { return (max_seq_len + tile - 1) / tile; };
@@ -178,7 +183,7 @@ inline void choose_cut(Plan* pl, ScanUse use, int group, int64_t planes, int64_t
     if (tile > 1024 && tile >= 2 * max_seq_len) continue;
     // never more tiles than two per compute unit in exchange for smaller ones
     if (tile == 1024 && pl->tile_tokens != 0 && planes * n_tiles_of(2048) >= kTargetWorkgroups) break;
-    for (int shift = 0; shift <= 2 && group % (1 << shift) == 0; ++shift) {
+    for (int shift = 0; shift <= 2 && heads_per_part(group, shift) != 0; ++shift) {
       const int64_t n_wg = planes * n_tiles_of(tile) << shift;
       if (shift > 0 && n_wg > kTargetWorkgroups) break;
       const double cost =

@@ -34,3 +34,7 @@ def cut(cfg, batch, max_seq_len, use=STEP):
 
 def config(heads, kv_heads, batch=1, context=1, **kw):
     return A.Config.make(heads, kv_heads, max(1, batch * context), **kw)
+
+
+def heads_per_part(group, shift):
+    return _lib().heads_per_part(group, shift)

@@ -10,3 +10,5 @@ extern "C" void scan_plan(const adamas_config* c, int32_t batch, int64_t max_seq
   out[2] = pl.n_tiles;
   out[3] = (int64_t)pl.total;
 }
+
+extern "C" int heads_per_part(int group, int g_shift) { return adamas::heads_per_part(group, g_shift); }

@@ -1,5 +1,7 @@
 """The scan's plan (csrc/plan.hpp) without a GPU."""
 
+import ctypes
+
 import pytest
 
 import plan_query as P
@@ -69,3 +71,24 @@ def test_cuts_of_spilling_instances():
     three = dict(code_bits=3, thr_k=(-1.5, -1.0, -0.5, 0.0, 0.5, 1.0, 1.5), head_dim=256)
     c = P.cut(P.config(32, 32, **three), 1, 32771)
     assert (c.tile, c.parts) == (2048, 1)
+
+
+def test_a_group_that_cannot_be_shared_evenly_has_no_heads_per_part():
+    assert [P.heads_per_part(8, s) for s in range(4)] == [8, 4, 2, 1]
+    assert [P.heads_per_part(6, s) for s in range(4)] == [6, 3, 0, 0]
+    assert P.heads_per_part(1, 1) == P.heads_per_part(8, -1) == P.heads_per_part(8, 4) == 0
+
+
+def test_the_launcher_takes_only_cuts_that_have_a_kernel():
+    """Asked without a GPU and for cuts that do not exist: false, and no launch is tried."""
+    lib = A.library()
+    of = getattr(lib, "_ZN6adamas10kernel_setILi128ELi0EEERKNS_9KernelSetEv")
+    of.restype = ctypes.c_void_p
+    # the table's first entry; a dim3 (three 32-bit words) travels as two 64-bit words
+    address = ctypes.cast(of(), ctypes.POINTER(ctypes.c_void_p))[0]
+    scan = ctypes.CFUNCTYPE(ctypes.c_bool, ctypes.c_bool, ctypes.c_int, ctypes.c_int, ctypes.c_uint64, ctypes.c_uint64,
+                            ctypes.c_void_p, ctypes.c_void_p)(address)
+    params = (ctypes.c_char * 4096)()
+    for fused in (False, True):
+        for heads, tile in [(0, 2048), (9, 2048), (-1, 4096), (16, 1024), (1, 0), (4, 512), (8, 8192)]:
+            assert scan(fused, heads, tile, 1 | 1 << 32, 1, None, params) is False, (fused, heads, tile)
