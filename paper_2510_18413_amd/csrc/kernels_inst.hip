@@ -50,13 +50,12 @@ bool launch_scan(bool fused, int G, int tile_tokens, dim3 grid, hipStream_t st, 
 
 template <int CHUNK, int TILES>
 void launch_select_as(bool attn, bool paged, dim3 grid, hipStream_t st, const SelectParams& sl) {
-  constexpr int kShape = kSelThreads + (TILES == kHistBatch ? 0 : TILES);
   if (!attn)
-    hipLaunchKernelGGL((select_kernel<kShape, false, METRIC, false, D, CHUNK>), grid, dim3(kSelThreads), 0, st, sl);
+    hipLaunchKernelGGL((select_kernel<kSelThreads, false, METRIC, false, D, CHUNK, TILES>), grid, dim3(kSelThreads), 0, st, sl);
   else if (paged)
-    hipLaunchKernelGGL((select_kernel<kShape, true, METRIC, true, D, CHUNK>), grid, dim3(kSelThreads), 0, st, sl);
+    hipLaunchKernelGGL((select_kernel<kSelThreads, true, METRIC, true, D, CHUNK, TILES>), grid, dim3(kSelThreads), 0, st, sl);
   else
-    hipLaunchKernelGGL((select_kernel<kShape, true, METRIC, false, D, CHUNK>), grid, dim3(kSelThreads), 0, st, sl);
+    hipLaunchKernelGGL((select_kernel<kSelThreads, true, METRIC, false, D, CHUNK, TILES>), grid, dim3(kSelThreads), 0, st, sl);
 }
 
 // The histograms that a call loads together: as many as its longest sequence has tiles, rounded up to four (see select_kernel).

@@ -399,13 +399,8 @@ __device__ __forceinline__ float merge_slots(const float* ph, int n_active, int 
 // would otherwise request, and mask, the rows of other heads.  us per layer with 16 / as many as needed: four tiles, one sequence
 // of 8000 tokens 12.6 / 12.1; three, 48 ragged sequences 62.3 / 61.4.  Groups of four behind a branch each in one
 // kernel instead of instantiations cost calls of 16 tiles 0.2 to 0.5.
-// SHAPE = threads (a multiple of 64), plus TILES where that is not kHistBatch.  (A body shared by two kernels with TILES as an
-// argument took 114 instead of 79 registers with sixteen tiles.)
-constexpr int threads_of(int shape) { return shape / kWave * kWave; }
-constexpr int tiles_of(int shape) { return shape % kWave == 0 ? kHistBatch : shape % kWave; }
-template <int SHAPE, bool ATTN, int METRIC, bool PAGED, int D, int CHUNK>
-__global__ __launch_bounds__(threads_of(SHAPE)) void select_kernel(const SelectParams p) {
-  constexpr int THREADS = threads_of(SHAPE), TILES = tiles_of(SHAPE);
+template <int THREADS, bool ATTN, int METRIC, bool PAGED, int D, int CHUNK, int TILES>
+__global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
   static_assert(CHUNK == 1 || CHUNK == 8, "passes per workgroup barrier");
   static_assert(TILES <= kHistBatch, "rows of slack behind the last histogram");
   static_assert(ATTN || !PAGED, "only the gather needs the page table");

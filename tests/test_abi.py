@@ -213,10 +213,10 @@ def test_merge_uses_device_scope_accesses(tmp_path):
                                       "-S", "--cuda-device-only", "-o", str(out),
                                       str(B.CSRC / "kernels_inst.hip")], check=True)
     text = out.read_text()
-    # the decode step's select kernels (a pass at a time / eight passes per barrier): 256 threads,
-    # with attention, Eq. 6, contiguous cache, d = 128
-    starts = list(re.finditer(r"^_ZN6adamas13select_kernelILi256ELb1ELi0ELb0ELi128ELi\d+EEE\w*:", text, re.M))
-    assert len(starts) == 2, "select kernels not found in the assembly"
+    # the decode step's select kernels: 256 threads, with attention, Eq. 6, contiguous or paged cache, d = 128; a pass at a
+    # time for 4, 8, 12 or 16 tiles of histograms, eight passes per barrier for 8 or 16
+    starts = list(re.finditer(r"^_ZN6adamas13select_kernelILi256ELb1ELi0ELb[01]ELi128ELi(\d+)ELi(\d+)EEE\w*:", text, re.M))
+    assert sorted((int(s[1]), int(s[2])) for s in starts) == sorted(2 * [(1, 4), (1, 8), (1, 12), (1, 16), (8, 8), (8, 16)])
     body = ""
     for start in starts:
         one = text[start.end():text.index(".Lfunc_end", start.end())]
