@@ -416,39 +416,11 @@ int adamas_sparse_attn(const adamas_config* cfg, const void* q, const void* K, c
   ap.Hkv = cfg->num_kv_heads;
   ap.k = k;
   ap.group_magic = group_magic_of(cfg);
-  // About 32 rows per workgroup, at most kMaxParts workgroups per head; half as many from half as many heads as
-  // compute units on.  One workgroup per head, which needs no merge launch, where there are at least as many heads as
-  // compute units and as rows, up to 512 rows.  Powers of two: with 11 or 6 workgroups per head, 96 and 192 heads of 2048
-  // rows take 22.9 and 37.8 us instead of 17.4 and 30.3 (d = 128).
-  // One workgroup per head also below that, for up to 16384 elements of K per list (four rows per wave and step, four steps),
-  // and one of sixteen waves for twice as many where there are 64 to 256 heads, and for lists of any length from 192
-  // heads on (one per compute unit; two of them per unit lose).  us as several with their merge / one of four waves / one of sixteen:
-  //    k d = 16384:  1 head, d = 128  6.1  5.3* 5.6    64 heads  7.0  6.3* 6.2   192 heads  9.1  7.3* 7.2   192, d = 64  9.8  7.2* 7.4
-  //    k d = 32768:  32 heads         7.0* 8.6  7.3    64 heads  8.3  8.8  7.5*  192 heads 11.1 10.3  9.2*  192, d = 256 11.4 10.4 9.2*
-  //    k d = 65536:  64 heads         9.7* 13.9 9.9   128 heads 12.3* 16.3 11.9  192 heads 15.5 17.9 14.2*  256 heads 20.0 20.5 17.5*
-  //    k d = 131072: 64 heads        12.1* 27.3 16.1  128 heads 17.9* 29.7 19.6  192 heads 24.3 31.0 22.8*  256 heads 31.4 34.8 29.2*
-  // us at 1 / 4 / 8 / 16 workgroups of four waves per head, d = 64, 128, 256 (chosen: *):
-  //    96 heads, 2048 rows   26.1  14.5  12.1  12.5*   51.5  22.1  18.0  17.4*   101.6  35.2  28.0  29.2*
-  //   128 heads,  512 rows    9.0   8.5   8.2*  9.9    14.5  11.6  11.4* 11.7     25.1  16.7  16.4* 16.7
-  //   128 heads, 1024 rows   15.2  11.5  11.2* 12.0    27.2  16.5  15.8* 15.3     49.8  25.2  24.1* 24.3
-  //   192 heads, 2048 rows   27.3  20.9  16.9* 19.2    54.3  33.3  28.8* 30.3    107.2  60.9  55.3* 57.3
-  //   256 heads,  256 rows    6.5*  8.6  10.2  13.7    10.4* 11.9  12.2  13.6     16.1* 17.1  17.2  18.3
-  //   256 heads, 4000 rows   54.5  37.4  30.6* 30.0   106.5  73.0  62.9* 60.7    203.0 133.3 111.3* 113.6
-  //   512 heads,  512 rows   15.5* 17.4  17.8  23.5    24.4* 26.8  26.5  28.4     48.1* 52.7  53.5  54.0
-  //   512 heads, 1500 rows   36.4  33.8  32.4* 35.2    69.3  69.4  62.2* 63.9    121.5 119.9 114.9* 117.4
-  //  1024 heads, 2048 rows   84.9  79.0  74.5* 82.2   164.6 155.9 141.0* 146.1   319.1 291.3 270.0* 277.5
-  const int64_t n_heads = (int64_t)batch * cfg->num_q_heads;
-  const int most = n_heads >= kTargetWorkgroups / 2 ? kMaxParts / 2 : kMaxParts;
-  int parts = (k + 31) / 32;
-  if (parts > most) parts = most;
-  if (n_heads >= kTargetWorkgroups && n_heads >= k && k <= 512) parts = 1;
-  const int64_t elements = (int64_t)k * cfg->head_dim;
-  const bool wide = elements > 16384 && n_heads >= (elements <= 32768 ? 64 : 192) && n_heads <= kTargetWorkgroups;
-  if (wide || (elements <= 16384 && n_heads < kTargetWorkgroups)) parts = 1;
-  ap.chunk = (k + parts - 1) / parts;
+  const SparseCut cut = sparse_cut((int64_t)batch * cfg->num_q_heads, k, cfg->head_dim);
+  ap.chunk = (k + cut.parts - 1) / cut.parts;
   ap.n_parts = (k + ap.chunk - 1) / ap.chunk;
   ap.scale_log2e = scale_log2e(cfg);
-  dim_set_of(cfg).sparse_attn(wide, dim3(ap.n_parts, cfg->num_q_heads, batch), st, ap);
+  dim_set_of(cfg).sparse_attn(cut.wide, dim3(ap.n_parts, cfg->num_q_heads, batch), st, ap);
   if (int rc = launch_status()) return rc;
   if (ap.n_parts == 1) return ADAMAS_OK;
   MergeParams mp{};

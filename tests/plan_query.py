@@ -38,3 +38,8 @@ def config(heads, kv_heads, batch=1, context=1, **kw):
 
 def heads_per_part(group, shift):
     return _lib().heads_per_part(group, shift)
+
+
+def sparse_parts(heads, k, d):
+    """Workgroups per head of the stand-alone attention; -1 for one of sixteen waves."""
+    return _lib().sparse_parts(ctypes.c_int64(heads), ctypes.c_int32(k), d)

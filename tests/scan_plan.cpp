@@ -12,3 +12,8 @@ extern "C" void scan_plan(const adamas_config* c, int32_t batch, int64_t max_seq
 }
 
 extern "C" int heads_per_part(int group, int g_shift) { return adamas::heads_per_part(group, g_shift); }
+
+extern "C" int sparse_parts(int64_t n_heads, int32_t k, int head_dim) {
+  const adamas::SparseCut cut = adamas::sparse_cut(n_heads, k, head_dim);
+  return cut.wide ? -cut.parts : cut.parts;
+}

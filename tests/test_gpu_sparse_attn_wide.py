@@ -9,10 +9,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("heads,k,d", [(1, 128, 128), (1, 129, 128), (63, 256, 128), (64, 129, 128), (64, 256, 128), (64, 257, 128),
                                        (191, 300, 128), (192, 300, 128), (256, 1025, 128), (257, 300, 128), (255, 1, 128),
-                                       (64, 257, 64), (70, 512, 64), (66, 300, 96), (200, 103, 160), (65, 160, 192), (256, 65, 256)])
+                                       (64, 257, 64), (70, 512, 64), (66, 300, 96), (200, 103, 160), (65, 160, 192), (256, 65, 256),
+                                       # several passes of the compaction, on both sides of the limits by rows
+                                       (192, 1024, 64), (208, 2047, 64), (208, 2048, 64), (193, 4096, 64)])
 def test_one_workgroup_per_head(heads, k, d):
     import paper_2510_18413_amd as A
-    L = 1200
+    L = max(1200, k + 50)
     gen = torch.Generator().manual_seed(heads * 1000 + k)
     K = (torch.randn(1, heads * L, d, generator=gen) * 2).to(torch.bfloat16)
     V = torch.randn(1, heads * L, d, generator=gen).to(torch.bfloat16)

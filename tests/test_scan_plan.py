@@ -92,3 +92,11 @@ def test_the_launcher_takes_only_cuts_that_have_a_kernel():
     for fused in (False, True):
         for heads, tile in [(0, 2048), (9, 2048), (-1, 4096), (16, 1024), (1, 0), (4, 512), (8, 8192)]:
             assert scan(fused, heads, tile, 1 | 1 << 32, 1, None, params) is False, (fused, heads, tile)
+
+
+@pytest.mark.parametrize("heads,k,d,parts", [
+    (1, 128, 128, 1), (1, 129, 128, 5), (63, 256, 128, 8), (64, 129, 128, -1), (64, 256, 128, -1), (64, 257, 128, 9), (128, 512, 128, 8),
+    (192, 1024, 128, -1), (192, 1025, 128, 8), (207, 2047, 64, 8), (208, 2047, 64, -1), (256, 2047, 256, -1), (192, 4096, 128, 8),
+    (256, 2048, 64, 8), (256, 4096, 256, 8), (257, 300, 128, 8), (512, 512, 128, 1), (256, 64, 64, 1)])
+def test_workgroups_of_the_stand_alone_attention(heads, k, d, parts):
+    assert P.sparse_parts(heads, k, d) == parts
