@@ -7,29 +7,50 @@ import pytest
 import torch
 
 import paper_2510_18413_amd as A
+import plan_query as P
 import synth_inputs as synth
 
-# B, query heads, KV heads, length, head dimension
+# B, query heads, KV heads, length, head dimension; (tile, parts) of the step, of top-k, of the distances alone
 CUTS = [
-    (1, 2, 1, 1017, 128),      # one tile of 1024, two heads
-    (1, 4, 1, 2049, 128),      # 2048 tokens, a head per workgroup
-    (1, 8, 1, 2304, 128),      # 2048, two heads of eight per workgroup
-    (1, 8, 1, 8191, 64),
-    (2, 12, 4, 4097, 128),     # a group of three is not cut
-    (3, 24, 4, 4105, 128),     # a group of six: halves only
-    (5, 16, 2, 33000, 128),    # 4096, four parts of eight heads
-    (9, 32, 8, 4096, 128),     # 4096, halves of four heads
-    (9, 32, 8, 4097, 96),
-    (16, 32, 8, 8200, 128),    # 4096, more workgroups than compute units
-    (33, 16, 8, 2049, 256),    # uint16 distances
-    # six, nine, ten, thirteen and seventeen tiles: as many histograms at once as the select kernel's instance takes, and more
-    (1, 4, 1, 12001, 128), (1, 4, 1, 17001, 96), (1, 4, 1, 40003, 128), (1, 4, 1, 26001, 64), (2, 8, 2, 66001, 128),
-    (2, 64, 8, 66001, 64),     # segments of 16384 tokens, seventeen tiles
+    ((2, 3, 1, 1023, 64), (1024, 1), (1024, 1), (1024, 1)),         # one tile
+    ((1, 2, 1, 1017, 128), (1024, 2), (1024, 2), (1024, 2)),        # a head per workgroup
+    ((1, 8, 1, 1023, 128), (1024, 4), (1024, 4), (1024, 4)),        # two heads of eight
+    ((1, 4, 1, 2049, 128), (2048, 4), (1024, 4), (1024, 4)),
+    ((1, 8, 1, 2304, 128), (2048, 4), (1024, 4), (1024, 4)),
+    ((1, 8, 1, 8191, 64), (2048, 4), (1024, 4), (1024, 4)),
+    ((2, 12, 4, 4097, 128), (2048, 1), (1024, 1), (1024, 1)),       # a group of three is not cut
+    ((3, 24, 4, 4105, 128), (2048, 2), (1024, 2), (1024, 2)),       # a group of six: halves only
+    ((40, 4, 1, 5000, 128), (2048, 2), (1024, 1), (1024, 1)),
+    ((5, 16, 2, 33000, 128), (4096, 2), (4096, 2), (4096, 2)),      # halves of eight heads
+    ((1, 16, 2, 65537, 128), (4096, 4), (4096, 4), (2048, 2)),      # quarters of eight heads, seventeen tiles
+    ((1, 4, 1, 40003, 128), (4096, 4), (4096, 4), (1024, 4)),       # quarters of four heads
+    ((9, 32, 8, 4096, 128), (4096, 2), (2048, 1), (2048, 1)),       # halves of four heads
+    ((3, 32, 8, 30001, 128), (4096, 1), (4096, 1), (4096, 1)),      # four heads together, sixteen waves
+    ((70, 3, 3, 4095, 128), (4096, 1), (2048, 1), (2048, 1)),       # one head per row, sixteen waves
+    ((9, 32, 8, 4097, 96), (2048, 1), (2048, 1), (2048, 1)),
+    ((16, 32, 8, 8200, 128), (2048, 1), (2048, 1), (2048, 1)),      # more workgroups than compute units
+    ((33, 16, 8, 2049, 256), (2048, 1), (2048, 1), (2048, 1)),      # uint16 distances
+    # six, nine, ten and thirteen tiles of histograms: as many at once as the select kernel's instance takes
+    ((1, 4, 1, 12001, 128), (2048, 4), (1024, 4), (1024, 4)), ((1, 4, 1, 17001, 96), (2048, 4), (2048, 4), (1024, 4)),
+    ((1, 4, 1, 26001, 64), (2048, 4), (2048, 4), (1024, 4)),
+    # seventeen: a second batch of them
+    ((2, 8, 2, 66001, 128), (4096, 2), (4096, 2), (2048, 1)), ((2, 32, 4, 66001, 64), (4096, 1), (4096, 1), (4096, 1)),
+    ((2, 64, 8, 66001, 64), (2048, 1), (4096, 1), (2048, 1)),       # segments of 16384 tokens, 33 and seventeen tiles
 ]
 
 
+def test_every_cut_is_here():
+    for shape, *cuts in CUTS:
+        B, Hq, Hkv, L, d = shape
+        for use, want in zip((P.STEP, P.TOPK, P.DISTANCES), cuts):
+            got = P.cut(P.config(Hq, Hkv, head_dim=d), B, L, use)
+            assert (got.tile, got.parts) == want, (shape, use)
+    every = {(tile, parts) for tile in (1024, 2048, 4096) for parts in (1, 2, 4)}
+    assert {c[1] for c in CUTS} == {c[2] for c in CUTS} | {c[3] for c in CUTS} == every
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,Hq,Hkv,L,d", CUTS)
+@pytest.mark.parametrize("B,Hq,Hkv,L,d", [c[0] for c in CUTS])
 def test_step_at_every_cut_of_the_scan(oracle, B, Hq, Hkv, L, d):
     from gpu_harness import ATTN_TOL, DeviceCase, attn_rel_err, oracle_step
     G = Hq // Hkv
@@ -46,14 +67,18 @@ def test_step_at_every_cut_of_the_scan(oracle, B, Hq, Hkv, L, d):
     for b in range(B):       # the appended row is in the cache
         at = int(case.seq_start[b]) + lens[b] - 1
         assert np.array_equal(got_rows[:, at], want["rows"][:, at])
-    # the distances themselves, of the stand-alone scan
+    # the distances themselves, of the stand-alone scan and of top-k
     qcodes = torch.zeros(B, Hq, dc.cfg.code_row_bytes, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(dc.cfg, dc.q, qcodes)
     dist = torch.zeros(B, Hq, dc.max_len, dtype=torch.uint16, device="cuda")
     A.adamas_manhattan_distance(dc.cfg, qcodes, dc.codes, dc.seq_start, dc.seq_len, dist)
-    got = dist.cpu().view(torch.int16).numpy().view(np.uint16).astype(np.int32)
-    for b in range(B):
-        assert np.array_equal(got[b, :, :lens[b]], want["dist"][b][:, :lens[b]])
+    dist2, idx2 = torch.zeros_like(dist), torch.zeros_like(dc.idx)
+    A.adamas_select_topk(dc.cfg, qcodes, dc.codes, dc.seq_start, dc.seq_len, k, idx2, dc.max_len, dc.workspace, dist_out=dist2)
+    assert np.array_equal(idx2.cpu().numpy(), want["idx"])
+    for got in (dist, dist2):
+        got = got.cpu().view(torch.int16).numpy().view(np.uint16).astype(np.int32)
+        for b in range(B):
+            assert np.array_equal(got[b, :, :lens[b]], want["dist"][b][:, :lens[b]])
 
 
 def test_the_static_array_takes_every_shape_that_fits_with_the_fewest_histograms():
