@@ -157,10 +157,12 @@ def library() -> ctypes.CDLL:
 
 def _load_marshal(lib):
     """The native marshalling module, bound to this library's entry points; built if it is missing or was built from
-    other sources.  None where it cannot be built: every call then goes through ctypes."""
+    other sources.  None, with a warning, where it cannot be built or torch has no GPU support to ask for a stream: every
+    call then goes through ctypes."""
     import importlib.machinery
     import importlib.util
     import subprocess
+    import warnings
 
     def load():
         loader = importlib.machinery.ExtensionFileLoader("_marshal", str(_build.MARSHAL_LIB))
@@ -173,13 +175,15 @@ def _load_marshal(lib):
         if not _build.MARSHAL_LIB.exists() or _build.marshal_id().encode() not in _build.MARSHAL_LIB.read_bytes():
             _build.build_marshal()
         module = load()
-    except (ImportError, OSError, subprocess.CalledProcessError):
+        import torch as torch_module
+        address = lambda fn: ctypes.cast(fn, ctypes.c_void_p).value
+        module.bind(Config, torch_module._C._cuda_getDevice, torch_module._C._cuda_getCurrentRawStream,
+                    address(lib.adamas_decode_step), address(lib.adamas_decode_step_paged),
+                    address(lib.adamas_encode_keys), address(lib.adamas_full_attn))
+    except (ImportError, OSError, AttributeError, subprocess.CalledProcessError) as e:
+        warnings.warn("no native argument marshalling (%s: %s): calls go through ctypes, some microseconds slower each"
+                      % (type(e).__name__, e), RuntimeWarning, stacklevel=3)
         return None
-    address = lambda fn: ctypes.cast(fn, ctypes.c_void_p).value
-    import torch as torch_module
-    module.bind(Config, torch_module._C._cuda_getDevice, torch_module._C._cuda_getCurrentRawStream,
-                address(lib.adamas_decode_step), address(lib.adamas_decode_step_paged),
-                address(lib.adamas_encode_keys), address(lib.adamas_full_attn))
     return module
 
 

@@ -72,6 +72,24 @@ def test_same_results_with_and_without_it(monkeypatch):
         assert torch.equal(a, b)
 
 
+def test_a_module_that_cannot_be_had_is_said_and_done_without(monkeypatch, tmp_path):
+    lib = A.library()
+
+    def no_compiler(*a, **k):
+        raise FileNotFoundError("g++")
+
+    with monkeypatch.context() as mp:
+        mp.setattr(binding._build, "MARSHAL_LIB", tmp_path / "_marshal.so")
+        mp.setattr(binding._build, "build_marshal", no_compiler)
+        with pytest.warns(RuntimeWarning, match="FileNotFoundError: g"):
+            assert binding._load_marshal(lib) is None
+    with monkeypatch.context() as mp:       # a torch without GPU support
+        mp.delattr(torch._C, "_cuda_getDevice")
+        with pytest.warns(RuntimeWarning, match="_cuda_getDevice"):
+            assert binding._load_marshal(lib) is None
+    assert binding._load_marshal(lib) is not None
+
+
 @pytest.mark.gpu
 def test_same_refusals_with_and_without_it(monkeypatch):
     A.library()
