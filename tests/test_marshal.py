@@ -90,6 +90,57 @@ def test_a_module_that_cannot_be_had_is_said_and_done_without(monkeypatch, tmp_p
     assert binding._load_marshal(lib) is not None
 
 
+def _outcomes(call, calls, monkeypatch):
+    """What every call does, with the native module and without it."""
+    def outcome(kw):
+        try:
+            call(**kw)
+        except Exception as e:
+            return type(e).__name__, str(e)
+        return "accepted"
+
+    assert binding._marshal is not None
+    native = [outcome(kw) for kw in calls]
+    with monkeypatch.context() as mp:
+        mp.setattr(binding, "_marshal", None)
+        without = [outcome(kw) for kw in calls]
+    torch.cuda.synchronize()
+    assert native == without
+    return native
+
+
+@pytest.mark.gpu
+def test_same_refusals_of_the_other_calls_with_and_without_it(monkeypatch):
+    A.library()
+    c, table, page = _call()
+    p = dict({n: v for n, v in c.items() if n != "seq_start"}, page_table=table, page_tokens=page)
+    bad = [{}, dict(page_tokens=64.0), dict(stages=True), dict(page_table=table[0]), dict(page_table=table.long()),
+           dict(page_table=table.cpu()), dict(page_table=torch.cat([table, table])), dict(page_tokens=63), dict(page_tokens=8192),
+           dict(page_tokens="64"), dict(stages=2), dict(stages=-1), dict(stages=2 ** 31), dict(max_seq_len=321), dict(q=c["q"].float()),
+           dict(K=c["K"][:, ::2]), dict(V=c["V"].cpu()), dict(codes=c["codes"][:, :, :16]), dict(seq_len=c["seq_len"][:0]),
+           dict(idx_out=c["idx_out"][:, :, 1:].contiguous()), dict(idx_out=None, k=0), dict(idx_out=None, k=2 ** 40), dict(v_new=None),
+           dict(workspace=c["workspace"][:1000]), dict(workspace=c["workspace"][1:]), dict(out=None), dict(cfg=None), dict(stream="x")]
+    got = _outcomes(A.adamas_decode_step_paged, [dict(p, **b) for b in bad], monkeypatch)
+    assert [i for i, g in enumerate(got) if g == "accepted"] == [0, 1, 2, 9]
+
+    e = dict(cfg=c["cfg"], K=c["K"], codes=c["codes"], row_begin=0, n_rows=320)
+    bad = [{}, dict(row_begin=True), dict(n_rows=0), dict(K=None), dict(K=c["K"].float()), dict(K=c["K"].transpose(0, 1)), dict(K=c["K"][0]),
+           dict(codes=c["codes"].cpu()), dict(codes=c["codes"][:, ::2]), dict(codes=c["codes"].view(torch.int8)), dict(n_rows=321),
+           dict(row_begin=-1), dict(n_rows=-1), dict(row_begin=2 ** 70), dict(n_rows="3"), dict(cfg=b"x" * 88), dict(stream=[])]
+    got = _outcomes(A.adamas_encode_keys, [dict(e, **b) for b in bad], monkeypatch)
+    assert [i for i, g in enumerate(got) if g == "accepted"] == [0, 2, 13]      # (ctypes takes the low bits of a number)
+
+    ws = torch.zeros(A.adamas_full_attn_workspace_bytes(c["cfg"], 1, 300), dtype=torch.uint8, device="cuda")
+    f = dict(cfg=c["cfg"], q=c["q"], K=c["K"], V=c["V"], seq_start=c["seq_start"], seq_len=c["seq_len"], out=c["out"], max_seq_len=300,
+             workspace=ws)
+    bad = [{}, dict(q=c["q"][0]), dict(q=c["q"].half()), dict(K=c["K"][:1]), dict(V=None), dict(seq_start=c["seq_start"].int()),
+           dict(seq_start=None), dict(seq_len=c["seq_len"].cpu()), dict(out=c["out"].double()), dict(out=c["out"].transpose(1, 2)),
+           dict(max_seq_len=0), dict(max_seq_len=2 ** 21), dict(max_seq_len=3.5), dict(workspace=ws[:100]), dict(workspace=None),
+           dict(workspace=ws.float()), dict(cfg="c"), dict(stream=object())]
+    got = _outcomes(A.adamas_full_attn, [dict(f, **b) for b in bad], monkeypatch)
+    assert [i for i, g in enumerate(got) if g == "accepted"] == [0]
+
+
 @pytest.mark.gpu
 def test_same_refusals_with_and_without_it(monkeypatch):
     A.library()
@@ -100,17 +151,7 @@ def test_same_refusals_with_and_without_it(monkeypatch):
            dict(k=5000, idx_out=None), dict(k=0, idx_out=None), dict(max_seq_len=0), dict(k_new=None), dict(cfg=3),
            dict(out=[1.0]), dict(max_seq_len=2 ** 70), dict(k=2 ** 40, idx_out=None)]
 
-    def outcome(change):
-        try:
-            A.adamas_decode_step(**dict(c, **change))
-        except Exception as e:
-            return type(e).__name__, str(e)
-        return "accepted"
-
-    native = [outcome(b) for b in bad]
-    with monkeypatch.context() as mp:
-        mp.setattr(binding, "_marshal", None)
-        assert native == [outcome(b) for b in bad]
+    native = _outcomes(A.adamas_decode_step, [dict(c, **b) for b in bad], monkeypatch)
     assert native[10][0] == native[11][0] == "AdamasError"
     # a transformed tensor has no storage of its own: refused, not dereferenced
     ran = []
