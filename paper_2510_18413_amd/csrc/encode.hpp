@@ -100,15 +100,7 @@ __device__ __forceinline__ double quad_bcast_f64(double v) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// One wave64 encodes one vector of D = 2^n * m elements.  Lane l < 4 * 2^n holds
-// the m / 4 consecutive elements from l * m / 4 on (raw bf16 bits; lanes beyond
-// hold nothing), so that a quad of lanes holds one block of m: the m-point stage
-// gathers the quad's values with DPP broadcasts and forms the lane's own m / 4
-// outputs as signed sums; the 2^n stage is butterflies across lane bits 2 and up.
-// All sums are fp64 and exact for inputs within the documented exponent spread.
-// The bucket indices then move to the lanes that own their bit of the packed
-// row (coefficient 64 k + l to lane l) and wave ballots give the planes.
-// Result: w[p][g], plane p of word g, identical in every lane.  All 64 lanes active.
+// One butterfly across lane bit H.
 // VIA_LDS: butterflies across lanes as shuffles through LDS instead of vector instructions, bit for bit the same.  For the bulk
 // kernels, which come here with few vectors and whose registers the vector form would add to (d = 128: 105 instead of 94, a
 // wave per SIMD less, 61.9 instead of 58.5 us for 1 Mi rows).
@@ -122,6 +114,15 @@ __device__ __forceinline__ double wave_butterfly(double v) {
   }
 }
 
+// One wave64 encodes one vector of D = 2^n * m elements.  Lane l < 4 * 2^n holds
+// the m / 4 consecutive elements from l * m / 4 on (raw bf16 bits; lanes beyond
+// hold nothing), so that a quad of lanes holds one block of m: the m-point stage
+// gathers the quad's values with DPP broadcasts and forms the lane's own m / 4
+// outputs as signed sums; the 2^n stage is butterflies across lane bits 2 and up.
+// All sums are fp64 and exact for inputs within the documented exponent spread.
+// The bucket indices then move to the lanes that own their bit of the packed
+// row (coefficient 64 k + l to lane l) and wave ballots give the planes.
+// Result: w[p][g], plane p of word g, identical in every lane.  All 64 lanes active.
 template <int BITS, int D, bool VIA_LDS>
 __device__ __forceinline__ void encode_values_wave_kron(const uint32_t (&raw)[HeadDim<D>::kEncElems],
                                                         const Thresholds& thr,

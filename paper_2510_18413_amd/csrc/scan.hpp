@@ -23,8 +23,6 @@
 //   (a - b)^2 = x_lo + 4 * u + 4 * (u & x_lo),  u = x_hi & ~(x_lo & g).
 #pragma once
 
-#include <type_traits>
-
 #include "device_utils.hpp"
 #include "encode.hpp"
 
@@ -380,7 +378,8 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
           for (int wq = 0; wq < kRowWords; ++wq) rr[i][wq] = s_new[wq];
         }
       }
-      // up to two heads mask their atomics alone (0.1 us of 12.9 for 32 planes of 9235 ragged tokens), larger groups the whole step
+      // Groups whose query planes fit the vector registers (up to two heads at d = 96 and 128, four at 64, one from 160 on; three times as
+      // many with one-bit codes) mask their atomics alone (0.1 us of 12.9 for 32 planes of 9235 ragged tokens), others the whole step.
       constexpr bool kMaskEach = kPlanesInVgprs;
       if (kMaskEach || t < L) {
 #pragma unroll
@@ -434,7 +433,7 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
         }
       }
     }
-    if (p.dist_user != nullptr) {  // the caller's own array of distances (adamas_distances)
+    if (p.dist_user != nullptr) {  // the caller's own array of distances
 #pragma unroll 1
       for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
 #pragma unroll
