@@ -142,7 +142,7 @@ enum class ScanUse { kStep, kSelect, kDistances };
 //   distances, 4 of 8000, group of 2        4.7    4.4           4.9    5.4           5.4    5.4
 // With three-bit codes the sixteen-wave workgroups of the step spill registers from d = 160 on (1 sequence of 32771, d = 256, group
 // of 1: 54.0, 49.2*, 59.8 with tiles of 1024, 2048 and 4096).  Over 972 shapes (d = 64 to 256, groups of 1 to 8, all code
-// formats, paged or not) the step's choice is 0.4 % above the best cut on average, top-k's 1.3 and that of the distances alone 3.0;
+// formats, paged or not) the step's choice is 0.5 % above the best cut on average, top-k's 1.3 and that of the distances alone 3.0;
 // where the step's is furthest off (4 to 11 %) the codes are three-bit, or eight heads share a row and two rounds of parts would pay.
 inline double scan_cost(ScanUse use, int metric, int head_dim, int64_t n_wg, int64_t n_tiles, int tile, int group, int parts) {
   const bool step = use == ScanUse::kStep;
