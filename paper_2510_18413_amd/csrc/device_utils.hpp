@@ -232,6 +232,8 @@ struct PhaseTrace {
 constexpr int kDppQuadXor1 = 0xB1;       // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;       // quad_perm [2,3,0,1]
 constexpr int kDppQuadMirror = 0x1B;     // quad_perm [3,2,1,0]
+constexpr int kDppQuadBcast = 0;         // + 0x55 * i: lane i of the quad
+constexpr int kDppRowRor4 = 0x124;       // row_ror:4
 constexpr int kDppRowRor8 = 0x128;       // row_ror:8
 constexpr int kDppRowShr = 0x110;        // + n: lane i reads lane i-n of its row
 constexpr int kDppRowMirror = 0x140;     // lane i reads lane 15-i of its row
@@ -285,6 +287,14 @@ __device__ __forceinline__ float lanes_sum_f32(float v) {
   return v;
 }
 
+// The largest value of each row of 16 lanes, in all of them.
+__device__ __forceinline__ float row_max_f32(float v) {
+  v = fmaxf(v, dpp_f32<kDppQuadXor1>(v));
+  v = fmaxf(v, dpp_f32<kDppQuadXor2>(v));
+  v = fmaxf(v, dpp_f32<kDppRowHalfMirror>(v));
+  return fmaxf(v, dpp_f32<kDppRowMirror>(v));
+}
+
 // The same for doubles (two 32-bit moves per step).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -301,6 +311,30 @@ __device__ __forceinline__ double lanes_sum_f64(double v) {
   v += dpp_f64<kDppRowHalfMirror>(v);
   if constexpr (LANES >= 16) v += dpp_f64<kDppRowMirror>(v);
   if constexpr (LANES >= 32) v += __shfl_xor(v, 16, kWave);
+  return v;
+}
+
+// One step of a sum over lanes for two values at once: a lane keeps the second one if `second`, the first one otherwise, and adds its
+// partner's share of it.
+template <int CTRL>
+__device__ __forceinline__ double hand_over(bool second, double a, double b) {
+  return (second ? b : a) + dpp_f64<CTRL>(second ? a : b);
+}
+// Sum of the lanes at the same place in each quad of an aligned group of LANES lanes (8, 16 or 32), in all of them.
+template <int LANES>
+__device__ __forceinline__ double quads_sum_f64(double v) {
+  if constexpr (LANES == 8) {
+    v += dpp_f64<kDppQuadMirror>(dpp_f64<kDppRowHalfMirror>(v));
+  } else {
+    v += dpp_f64<kDppRowRor8>(v);
+    v += dpp_f64<kDppRowRor4>(v);
+  }
+  if constexpr (LANES >= 32) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    v = __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+  }
   return v;
 }
 

@@ -116,25 +116,55 @@ struct AttnShared {
   float acc[kWaves][D];
 };
 
-// One step of combining the online-softmax states (m, l, acc[8]) of the lane
-// groups of a wave: afterwards lanes i and i ^ STEP hold the combination of
-// their two states (the same bits in both: each side is weighted and the two
-// products are added, which commutes).
-template <int STEP>
-__device__ __forceinline__ void combine_lane_groups(float& m, float& l, float (&acc)[8]) {
+// The lane groups of a wave (LPR lanes each, 8 dims a lane) combined: weights refer to the wave's maximum, and each exchange hands
+// half of a lane's dims to its partner, so that a step takes one instruction and one addition for two values.
+// Afterwards lane l holds N = 8 * LPR / 64 dims (two at least), from dim wave_dim(l) on, of the wave's sum, and every lane m and l.
+template <int LPR>
+constexpr int kWaveDims = LPR == 32 ? 4 : 2;
+template <int LPR>
+__device__ __forceinline__ int wave_dim(int lane) {
+  return (lane % LPR) * 8 + (lane & 32 ? 4 : 0) + (LPR <= 16 && (lane & 16) ? 2 : 0);
+}
+template <int LPR>
+__device__ __forceinline__ void combine_lane_groups(float& m, float& l, float (&acc)[8], float (&o)[kWaveDims<LPR>]) {
 #pragma clang fp contract(off)
-  float ma, mb, la, lb;
-  exchange_pair<STEP>(m, ma, mb);
-  exchange_pair<STEP>(l, la, lb);
-  const float mn = fmaxf(ma, mb);
-  const float wa = exp2_neg(ma - mn), wb = exp2_neg(mb - mn);
-  m = mn;
-  l = la * wa + lb * wb;
+  auto largest = [](float v, auto step_) {
+    float a, b;
+    exchange_pair<decltype(step_)::value>(v, a, b);
+    return fmaxf(a, b);
+  };
+  auto sum = [](float v, auto step_) {
+    float a, b;
+    exchange_pair<decltype(step_)::value>(v, a, b);
+    return a + b;
+  };
+  constexpr std::integral_constant<int, 8> k8{};
+  constexpr std::integral_constant<int, 16> k16{};
+  constexpr std::integral_constant<int, 32> k32{};
+  float mw = largest(m, k32);
+  if constexpr (LPR <= 16) mw = largest(mw, k16);
+  if constexpr (LPR <= 8) mw = largest(mw, k8);
+  const float w = exp2_neg(m - mw);
+  m = mw;
+  l = sum(l * w, k32);
+  if constexpr (LPR <= 16) l = sum(l, k16);
+  if constexpr (LPR <= 8) l = sum(l, k8);
+  float h[4];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    float xa, xb;
-    exchange_pair<STEP>(acc[j], xa, xb);
-    acc[j] = xa * wa + xb * wb;
+  for (int j = 0; j < 4; ++j) {  // lanes 0 to 31 keep dims j, the others dims 4 + j
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[j] * w), __float_as_uint(acc[4 + j] * w), false, false);
+    h[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  if constexpr (LPR == 32) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = h[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {  // even rows of 16 lanes keep j, odd ones 2 + j
+      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[j]), __float_as_uint(h[2 + j]), false, false);
+      o[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+      if constexpr (LPR == 8) o[j] = sum(o[j], k8);
+    }
   }
 }
 
@@ -174,7 +204,6 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
   // next power of two: the same for the paper's head dimensions; with D = 96,
   // 160 or 192 the last lanes of a group hold zeros and load nothing).
   constexpr int LPR = HeadDim<D>::kRowGroup, kRowLanes = HeadDim<D>::kRowLanes;
-  constexpr int kGroups = THREADS / LPR;
   constexpr int NW = THREADS / kWave;
   const int tid = threadIdx.x, grp = tid / LPR, gl = tid % LPR;
   const int wave = tid >> 6, lane = tid & 63;
@@ -189,54 +218,50 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
 
-  // U rows in flight per lane group.  Their scores come first, then one new maximum and
-  // one rescaling of the sums for all of them: with a maximum per row, 48 x 32 heads of 256 rows spent
-  // 26 of 46 us on the issue of vector instructions (64.3 us a layer with its scan before, 61.4 now).
+  // U rows in flight per lane group.  Their scores come first, then one new maximum and one rescaling of the sums for all of them.
+  // Where many heads share a compute unit this loop is bound by the issue of vector instructions: a maximum per row, then one for four
+  // rows, then one score and one exponential per lane instead of four took a decode layer of 48 x 32 heads of 256 rows
+  // from 64.3 over 61.4 to 59.6 us, and those of a few heads down by 0.15 to 0.4.
   constexpr int U = 4;
   const int wave_grp = __builtin_amdgcn_readfirstlane(wave) * (kWave / LPR);  // first lane group of the wave
   n = __builtin_amdgcn_readfirstlane(n);
+  // With several waves to a SIMD their fixed parts (maximum, rescaling, combination) take turns: a short list goes to as many waves
+  // as give a group two rows (64 rows of d = 128 in sixteen waves, with the scan of 1024 tokens 7.4 -> 6.8 us).
+  int used_waves = NW;
+  constexpr int kFew = 2 * (kWave / LPR);
+  if constexpr (NW > 4) used_waves = min(max((n + kFew - 1) / kFew, 4), NW);
+  const int kGroups = used_waves * (kWave / LPR);
   // Nothing that the rows' registers could wait for is left in flight (vmcnt = 0).  Said here, because the compiler would
   // otherwise put that wait between the requests of a batch where it comes too late: a round trip in every batch
   // (paged, 240 heads of 1160 rows: 81 us a step instead of 74).
   __builtin_amdgcn_s_waitcnt(0x0f70);
-  for (int b0 = 0; b0 + wave_grp < n; b0 += kGroups * U) {
-    const int i0 = b0 + grp;
-    // Row slots are filled in order, so one that the wave's first group does not use
-    // ends the batch (wave-uniform: the rows of a small selection take one or
-    // two slots, and unused ones cost nothing).
-    const int used = min((n - b0 - wave_grp + kGroups - 1) / kGroups, U);
-    uint4 kv[U], vv[U];
-    bool ok[U];
+  if (NW <= 4 || wave_grp < kGroups) {  // (not the waves that a short list leaves out)
+    for (int b0 = 0; b0 + wave_grp < n; b0 += kGroups * U) {
+      const int i0 = b0 + grp;
+      // Row slots are filled in order, so one that the wave's first group does not use
+      // ends the batch (wave-uniform: the rows of a small selection take one or
+      // two slots, and unused ones cost nothing).
+      const int left = n - b0 - wave_grp;
+      const int used = NW <= 4 ? min((left + kGroups - 1) / kGroups, U) : 1 + (left > kGroups) + (left > 2 * kGroups) + (left > 3 * kGroups);
+      uint4 kv[U], vv[U];
+      bool ok[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = i0 + u * kGroups;
-      ok[u] = i < n;
-      kv[u] = make_uint4(0, 0, 0, 0);
-      vv[u] = make_uint4(0, 0, 0, 0);
-      if (ok[u] && lane_on) {
-        // clamped: whatever the list holds, the gather stays inside the sequence
-        const int tok = min(max(s_sel[i], 0), n_tokens - 1);
-        const int64_t off = (int64_t)tok * D + gl * 8;
-        kv[u] = *reinterpret_cast<const uint4*>(Kp + off);
-        vv[u] = *reinterpret_cast<const uint4*>(Vp + off);
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * kGroups;
+        ok[u] = i < n;
+        kv[u] = make_uint4(0, 0, 0, 0);
+        vv[u] = make_uint4(0, 0, 0, 0);
+        if (ok[u] && lane_on) {
+          // clamped: whatever the list holds, the gather stays inside the sequence
+          const int tok = min(max(s_sel[i], 0), n_tokens - 1);
+          const int64_t off = (int64_t)tok * D + gl * 8;
+          kv[u] = *reinterpret_cast<const uint4*>(Kp + off);
+          vv[u] = *reinterpret_cast<const uint4*>(Vp + off);
+        }
       }
-    }
-    // Two rows at a time: their chains of additions run side by side (all four at once take
-    // 89 registers, and a sixth workgroup no longer fits a compute unit: 61.9 -> 66.2 us for 48 sequences).
-    // A last slot without a partner is computed alone (one slot, D = 64, 128 heads of 256 rows: 7.2 us, in a pair 7.5, with
-    // a maximum per row 7.0; three slots, D = 128, 768 heads of 700 rows: 50.0, 51.8, 50.7).
-    double sc[U];
-    float mn = m;
-    auto scores = [&](int u0, auto rows_) {
+      auto partial = [&](int u) {
 #pragma clang fp contract(off)
-      constexpr int kRows = decltype(rows_)::value;
-      double s[kRows];
-#pragma unroll
-      for (int v = 0; v < kRows; ++v) {
-        uint4 k4 = kv[u0 + v];
-        // (opaque in the path of a single row, or the compiler moves what it shares with the path of two
-        // in front of the branch and the chains of the two rows run one after the other)
-        if constexpr (kRows == 1) asm("" : "+v"(k4.x), "+v"(k4.y), "+v"(k4.z), "+v"(k4.w));
+        const uint4 k4 = kv[u];
         // two chains of four: the additions of a chain wait for each other
         double s1 = qf[0] * (double)bf16_lo(k4.x), s2 = qf[1] * (double)bf16_hi(k4.x);
         s1 = fma(qf[2], (double)bf16_lo(k4.y), s1);
@@ -245,75 +270,92 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
         s2 = fma(qf[5], (double)bf16_hi(k4.z), s2);
         s1 = fma(qf[6], (double)bf16_lo(k4.w), s1);
         s2 = fma(qf[7], (double)bf16_hi(k4.w), s2);
-        s[v] = s1 + s2;
+        return s1 + s2;
+      };
+      if (b0 == 0) trace.stamp(kSelRowsFirst);
+      // The sums over the lanes of a row: in the first two steps a lane keeps one row of two and hands the other one on, so that lane
+      // i of a quad ends with the score of row i, for three instructions a step instead of twelve, and one exponential.
+      const bool odd = lane & 1, high = lane & 2;
+      double s01 = partial(0), s23 = 0.0;
+      if (used >= 2) s01 = hand_over<kDppQuadXor1>(odd, s01, partial(1));
+      else s01 += dpp_f64<kDppQuadXor1>(s01);
+      if (used > 2) {
+        s23 = partial(2);
+        if (used > 3) s23 = hand_over<kDppQuadXor1>(odd, s23, partial(3));
+        else s23 += dpp_f64<kDppQuadXor1>(s23);
+        s01 = hand_over<kDppQuadXor2>(high, s01, s23);
+      } else {
+        s01 += dpp_f64<kDppQuadXor2>(s01);
       }
+      const double sc = quads_sum_f64<LPR>(s01) * scale_log2e;
+      const bool mine = i0 + (lane & 3) * kGroups < n;
+      float mn = mine ? (float)sc : kNegBig;
+      mn = fmaxf(mn, dpp_f32<kDppQuadXor1>(mn));
+      mn = fmaxf(fmaxf(mn, dpp_f32<kDppQuadXor2>(mn)), m);
+      const float pw = mine ? exp2_neg((float)(sc - (double)mn)) : 0.f;
+      const float corr = exp2_neg(m - mn);
+      m = mn;
+      l = l * corr + pw;
 #pragma unroll
-      for (int v = 0; v < kRows; ++v) {
-        // summed over the row's aligned group of 8, 16 or 32 lanes
-        s[v] = lanes_sum_f64<LPR>(s[v]) * scale_log2e;
-        if constexpr (kRows == 1) asm("" : "+v"(s[v]));
-        if (ok[u0 + v]) sc[u0 + v] = s[v];
-        mn = fmaxf(mn, (float)sc[u0 + v]);
-      }
-    };
-    auto weigh = [&](int u0, auto rows_) {
-#pragma clang fp contract(off)
-#pragma unroll
-      for (int u = u0; u < u0 + decltype(rows_)::value; ++u) {
-        const float pw = ok[u] ? exp2_neg((float)(sc[u] - (double)mn)) : 0.f;
-        l += pw;
-        acc[0] = fmaf(pw, bf16_lo(vv[u].x), acc[0]);
-        acc[1] = fmaf(pw, bf16_hi(vv[u].x), acc[1]);
-        acc[2] = fmaf(pw, bf16_lo(vv[u].y), acc[2]);
-        acc[3] = fmaf(pw, bf16_hi(vv[u].y), acc[3]);
-        acc[4] = fmaf(pw, bf16_lo(vv[u].z), acc[4]);
-        acc[5] = fmaf(pw, bf16_hi(vv[u].z), acc[5]);
-        acc[6] = fmaf(pw, bf16_lo(vv[u].w), acc[6]);
-        acc[7] = fmaf(pw, bf16_hi(vv[u].w), acc[7]);
-      }
-    };
-    constexpr std::integral_constant<int, 1> kOne{};
-    constexpr std::integral_constant<int, 2> kTwo{};
-    if (b0 == 0) trace.stamp(kSelRowsFirst);
-#pragma unroll
-    for (int u = 0; u < U; ++u) sc[u] = (double)kNegBig;
-    if (used >= 2) scores(0, kTwo);
-    else scores(0, kOne);
-    if (used > 2) {
-      if (used > 3) scores(2, kTwo);
-      else scores(2, kOne);
+      for (int j = 0; j < 8; ++j) acc[j] *= corr;
+      auto weigh = [&](int u, float w) {
+        acc[0] = fmaf(w, bf16_lo(vv[u].x), acc[0]);
+        acc[1] = fmaf(w, bf16_hi(vv[u].x), acc[1]);
+        acc[2] = fmaf(w, bf16_lo(vv[u].y), acc[2]);
+        acc[3] = fmaf(w, bf16_hi(vv[u].y), acc[3]);
+        acc[4] = fmaf(w, bf16_lo(vv[u].z), acc[4]);
+        acc[5] = fmaf(w, bf16_hi(vv[u].z), acc[5]);
+        acc[6] = fmaf(w, bf16_lo(vv[u].w), acc[6]);
+        acc[7] = fmaf(w, bf16_hi(vv[u].w), acc[7]);
+      };
+      weigh(0, dpp_f32<kDppQuadBcast + 0x00>(pw));
+      if (used > 1) weigh(1, dpp_f32<kDppQuadBcast + 0x55>(pw));
+      if (used > 2) weigh(2, dpp_f32<kDppQuadBcast + 0xAA>(pw));
+      if (used > 3) weigh(3, dpp_f32<kDppQuadBcast + 0xFF>(pw));
     }
-    const float corr = exp2_neg(m - mn);
-    m = mn;
-    l *= corr;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] *= corr;
-    weigh(0, kTwo);
-    if (used > 2) weigh(2, kTwo);
-  }
-  trace.stamp(kSelAttended);
+    trace.stamp(kSelAttended);
 
-  // The lane groups of a wave hold the same dims in the same lanes of their
-  // group: combine them pairwise with cross-lane moves (both partners compute
-  // the same values), then the waves through LDS.  A group without rows has
-  // l = 0 and m = kNegBig and drops out with weight exp2(kNegBig - M) = 0.
-  if constexpr (LPR <= 8) combine_lane_groups<8>(m, l, acc);
-  if constexpr (LPR <= 16) combine_lane_groups<16>(m, l, acc);
-  combine_lane_groups<32>(m, l, acc);
-  if (lane < kRowLanes) {
+    // A group without rows has l = 0 and m = kNegBig and drops out with weight exp2(kNegBig - M) = 0.
+    // (a lane of a quad has the weights of its rows)
+    l += dpp_f32<kDppQuadXor1>(l);
+    l += dpp_f32<kDppQuadXor2>(l);
+    constexpr int kDims = kWaveDims<LPR>;
+    float wo[kDims];
+    combine_lane_groups<LPR>(m, l, acc, wo);
     if (lane == 0) {
       sh.m[wave] = m;
       sh.l[wave] = l;
     }
+    if (lane_on) {
+      float* to = &sh.acc[wave][wave_dim<LPR>(lane)];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) sh.acc[wave][lane * 8 + j] = acc[j];
+      for (int j = 0; j < kDims; ++j) to[j] = wo[j];
+    }
   }
   __syncthreads();
 
   M = kNegBig;
   lsum = 0.f;
   o = 0.f;
-  if (tid < D) {
+  if constexpr (NW > 4) {
+    // a lane per wave's state, for the maximum and one exponential instead of NW of them in a row
+    if (wave < (D + kWave - 1) / kWave) {
+      const int from = lane & 15;
+      const float mw = from < used_waves ? sh.m[from] : kNegBig, lw = from < used_waves ? sh.l[from] : 0.f;
+      M = row_max_f32(mw);
+      const float wt = exp2_neg(mw - M);
+      lsum = lanes_sum_f32<16>(lw * wt);
+      if (tid < D) {
+        float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          if (w < used_waves)
+            part[w & 3] = fmaf(sh.acc[w][tid], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), w)), part[w & 3]);
+        }
+        o = (part[0] + part[1]) + (part[2] + part[3]);
+      }
+    }
+  } else if (tid < D) {
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.m[w]);
 #pragma unroll
