@@ -85,6 +85,89 @@ enum ScanPhase {
   kScanEnd           // histogram flushed and acknowledged
 };
 
+// v with lane I's value replaced by the wave-uniform x, whether that lane is active or not: only where the wave branched as a whole, by
+// a scalar condition.  (A branch by lanes may be run through with none of them active, and v's register hold another path's value.)
+template <int I>
+__device__ __forceinline__ uint32_t set_lane(uint32_t v, uint32_t x) {
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(I));
+  return v;
+}
+
+// An encoded vector from its wave (every lane holds all of it, w[p][g]: plane p of word g) to LDS, a word per lane: twelve lane
+// writes and one store, where a store per plane and lane took a quarter of a microsecond of the chain in front of the distances.
+// A query as the distances read it: plane p of word g at [W * p + g]; two-bit codes also keep lo ^ hi at [2 W + g].
+template <int BITS, int W>
+__device__ __forceinline__ void publish_query(const uint32_t (&w)[BITS][W], uint32_t* to, int lane) {
+  constexpr int QP = BITS == 2 ? 3 : BITS;
+  uint32_t word = 0;
+  static_for<QP * W>([&](auto i_) {
+    constexpr int i = decltype(i_)::value, pl = i / W, g = i % W;
+    word = set_lane<i>(word, pl < BITS ? w[pl < BITS ? pl : 0][g] : w[0][g] ^ w[BITS - 1][g]);
+  });
+  if (lane < QP * W) to[lane] = word;
+}
+// A key as a row of the cache.
+template <int BITS, int W>
+__device__ __forceinline__ void publish_row(const uint32_t (&w)[BITS][W], uint32_t* to, int lane) {
+  uint32_t word = 0;
+  static_for<BITS * W>([&](auto i_) {
+    constexpr int i = decltype(i_)::value;
+    word = set_lane<i>(word, w[i % BITS][i / BITS]);
+  });
+  if (lane < BITS * W) to[lane] = word;
+}
+
+// The distance of a key row (row[BITS * wd + pl]: plane pl of word wd) to the query with planes q(j, wd); for two-bit codes
+// plane 2 is lo ^ hi.
+template <int METRIC, int D, typename Q>
+__device__ __forceinline__ uint32_t row_distance(const uint32_t (&row)[Dist<METRIC, D>::kBits * (D / 32)], Q q) {
+  constexpr int BITS = Dist<METRIC, D>::kBits, W = D / 32;
+  if constexpr (BITS == 2) {
+    uint32_t c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+    for (int wd = 0; wd < W; ++wd) {
+      // Every instruction below takes one query plane: with two of them in one
+      // instruction (the compiler's choice when it may merge them) a plane held
+      // in a scalar register must first be copied.  Hence the opaque values.
+      uint32_t xl = row[2 * wd] ^ q(0, wd);
+      asm("" : "+v"(xl));
+      uint32_t both = xl & q(2, wd);
+      asm("" : "+v"(both));
+      const uint32_t u = (row[2 * wd + 1] ^ q(1, wd)) & ~both;
+      // (and opaque running sums: the count instruction adds to them, a regrouped sum takes additions of its own)
+      c1 += __popc(xl);
+      c2 += __popc(u);
+      asm("" : "+v"(c1), "+v"(c2));
+      if constexpr (METRIC == kMetricL2) c3 += __popc(u & xl);
+    }
+    return METRIC == kMetricL1 ? c1 + 2u * c2 : c1 + 4u * (c2 + c3);
+  } else if constexpr (BITS == 1) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int wd = 0; wd < W; ++wd) c += __popc(row[wd] ^ q(0, wd));
+    return c;
+  } else {
+    // |a - b| of 3-bit codes on bit planes (a query, b key): subtract with
+    // borrow, then negate where the borrow out (a < b) is set.
+    uint32_t c0 = 0, c1 = 0, c2 = 0;
+#pragma unroll
+    for (int wd = 0; wd < W; ++wd) {
+      const uint32_t a0 = q(0, wd), a1 = q(1, wd), a2 = q(2, wd);
+      const uint32_t b0 = row[3 * wd], b1 = row[3 * wd + 1], b2 = row[3 * wd + 2];
+      const uint32_t d0 = a0 ^ b0, br1 = ~a0 & b0;
+      const uint32_t x1 = a1 ^ b1, d1 = x1 ^ br1, br2 = (~a1 & b1) | (~x1 & br1);
+      const uint32_t x2 = a2 ^ b2, d2 = x2 ^ br2, sg = (~a2 & b2) | (~x2 & br2);
+      const uint32_t e1 = d1 ^ sg, cy1 = ~d0 & sg;
+      const uint32_t r1 = e1 ^ cy1, cy2 = e1 & cy1;
+      const uint32_t r2 = d2 ^ sg ^ cy2;
+      c0 += __popc(d0);
+      c1 += __popc(r1);
+      c2 += __popc(r2);
+    }
+    return c0 + 2u * c1 + 4u * c2;
+  }
+}
+
 // WAVES = wavefronts per workgroup (4, 8 or 16): the tile is WAVES * 256 tokens.
 // D = head dimension: W = D / 32 words per code row.
 template <int G, bool FUSED, int WAVES, int METRIC, bool PAGED, int D>
@@ -106,10 +189,11 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   __shared__ uint32_t s_q[G][3 * W];
   __shared__ uint32_t s_new[kRowWords];  // code row of the appended key, as stored
   __shared__ uint32_t s_ready;      // query / new-key code rows published so far
-  // Up to 24 words of query planes at a time: the heads of a group are served in passes (see below).
+  // The heads of a group are served in passes, the planes of a pass's heads together or one after the other (see below).
   constexpr int QP = BITS == 2 ? 3 : BITS;
-  constexpr bool kPlanesInVgprs = G * QP * W <= 24;
-  constexpr int kPassHeads = kPlanesInVgprs ? G : (24 / (QP * W) > 0 ? 24 / (QP * W) : 1);
+  constexpr bool kAllTogether = G * QP * W <= 24;
+  constexpr int kPassHeads = kAllTogether ? G : (24 / (QP * W) > 0 ? 24 / (QP * W) : 1);
+  constexpr int kTogether = kAllTogether ? G : 1;
   // per wave: its 256 distances to each query head of a pass, in token order
   __shared__ __align__(16) uint16_t s_dt[WAVES][kPassHeads][kScanTokPerThread * kWave];
 
@@ -244,25 +328,15 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   if (FUSED) {
 #pragma unroll
     for (int r = 0; r < kEncRounds; ++r) {
-      const int v = wave + r * WAVES;
+      const int v = __builtin_amdgcn_readfirstlane(wave) + r * WAVES;  // (scalar: see set_lane)
       if (v < n_enc) {
         uint32_t w[BITS][W];
         uint32_t raw[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) raw[e] = enc[r][e];
         encode_values_wave<BITS, D>(raw, v < G ? p.thr_q : p.thr_k, w);
-        // lane wd publishes word wd (every lane holds the whole row)
-#pragma unroll
-        for (int wd = 0; wd < W; ++wd) {
-          if (lane == wd) {
-#pragma unroll
-            for (int pl = 0; pl < BITS; ++pl) {
-              if (v < G) s_q[v][W * pl + wd] = w[pl][wd];
-              else s_new[BITS * wd + pl] = w[pl][wd];  // code row of the appended key
-            }
-            if (BITS == 2 && v < G) s_q[v][2 * W + wd] = w[0][wd] ^ w[BITS - 1][wd];
-          }
-        }
+        if (v < G) publish_query<BITS, W>(w, s_q[v], lane);
+        else publish_row<BITS, W>(w, s_new, lane);
         if (lane == 0)
           __hip_atomic_fetch_add(&s_ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
@@ -290,110 +364,61 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   }
 
   trace.stamp(kScanQueryReady);
-  // The query planes are wave-uniform.  Up to 24 words (the method's group of
-  // one or two) live in vector registers.  Larger groups keep them in scalar
-  // registers (every instruction of the distance needs only one of them, and the
-  // kernel then fits 64 vector registers), at most 24 words at a time: the heads
-  // of the group are served in passes of kPassHeads over the rows, which stay
-  // in registers.  All planes of a group of four at once take about 100 scalar
-  // registers, and it is then the scalar register file that limits how many
-  // waves a compute unit holds (measured: the only resource the dispatcher
-  // reports as full, with about four waves per SIMD resident).
+  // The query planes are wave-uniform, but live in vector registers: an instruction with a scalar operand takes twice the issue
+  // time of one without as soon as a SIMD has a second wave (exclusive or, and, three-input logic: 4.2 and 2.4 clocks), and with 24
+  // words of planes in scalar registers a wave takes more than 80, of which a compute unit holds 28 waves instead of
+  // 32, one workgroup of sixteen instead of two (16 ragged sequences 41.5 -> 45.4 us a layer).  Up to 24 words
+  // (the method's group of one or two) at once; larger groups one head after the other over the rows, which stay in registers.
   // qp[g][j][wd]: plane j of word wd; for 2-bit codes j = 2 is lo ^ hi.
   uint32_t* hist_lane = s_hist + (lane & (kHistReplicas - 1)) * kHistWords;
-  // The distance of a key row (row[BITS * wd + pl]: plane pl of word wd) to the query with planes q(j, wd).
-  auto distance = [](const uint32_t (&row)[kRowWords], auto q) -> uint32_t {
-    if constexpr (BITS == 2) {
-      uint32_t c1 = 0, c2 = 0, c3 = 0;
-#pragma unroll
-      for (int wd = 0; wd < W; ++wd) {
-        // Every instruction below takes one query plane: with two of them in one
-        // instruction (the compiler's choice when it may merge them) a plane held
-        // in a scalar register must first be copied.  Hence the opaque values.
-        uint32_t xl = row[2 * wd] ^ q(0, wd);
-        asm("" : "+v"(xl));
-        uint32_t both = xl & q(2, wd);
-        asm("" : "+v"(both));
-        const uint32_t u = (row[2 * wd + 1] ^ q(1, wd)) & ~both;
-        // (and opaque running sums: the count instruction adds to them, a regrouped sum takes additions of its own)
-        c1 += __popc(xl);
-        c2 += __popc(u);
-        asm("" : "+v"(c1), "+v"(c2));
-        if constexpr (METRIC == kMetricL2) c3 += __popc(u & xl);
-      }
-      return METRIC == kMetricL1 ? c1 + 2u * c2 : c1 + 4u * (c2 + c3);
-    } else if constexpr (BITS == 1) {
-      uint32_t c = 0;
-#pragma unroll
-      for (int wd = 0; wd < W; ++wd) c += __popc(row[wd] ^ q(0, wd));
-      return c;
-    } else {
-      // |a - b| of 3-bit codes on bit planes (a query, b key): subtract with
-      // borrow, then negate where the borrow out (a < b) is set.
-      uint32_t c0 = 0, c1 = 0, c2 = 0;
-#pragma unroll
-      for (int wd = 0; wd < W; ++wd) {
-        const uint32_t a0 = q(0, wd), a1 = q(1, wd), a2 = q(2, wd);
-        const uint32_t b0 = row[3 * wd], b1 = row[3 * wd + 1], b2 = row[3 * wd + 2];
-        const uint32_t d0 = a0 ^ b0, br1 = ~a0 & b0;
-        const uint32_t x1 = a1 ^ b1, d1 = x1 ^ br1, br2 = (~a1 & b1) | (~x1 & br1);
-        const uint32_t x2 = a2 ^ b2, d2 = x2 ^ br2, sg = (~a2 & b2) | (~x2 & br2);
-        const uint32_t e1 = d1 ^ sg, cy1 = ~d0 & sg;
-        const uint32_t r1 = e1 ^ cy1, cy2 = e1 & cy1;
-        const uint32_t r2 = d2 ^ sg ^ cy2;
-        c0 += __popc(d0);
-        c1 += __popc(r1);
-        c2 += __popc(r2);
-      }
-      return c0 + 2u * c1 + 4u * c2;
-    }
-  };
+  auto distance = [](const uint32_t (&row)[kRowWords], auto q) { return row_distance<METRIC, D>(row, q); };
 
   uint32_t one = 1;  // (opaque: otherwise written anew for every use)
   asm("" : "+v"(one));
 #pragma unroll
   for (int g0 = 0; g0 < G; g0 += kPassHeads) {
-    uint32_t qp[kPassHeads][QP][W];
 #pragma unroll
-    for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
+    for (int g1 = g0; g1 < g0 + kPassHeads && g1 < G; g1 += kTogether) {
+      uint32_t qp[kTogether][QP][W];
 #pragma unroll
-      for (int j = 0; j < QP; ++j) {
+      for (int g = 0; g < kTogether; ++g) {
 #pragma unroll
-        for (int wd = 0; wd < W; ++wd) {
-          if constexpr (kPlanesInVgprs) qp[g - g0][j][wd] = s_q[g][W * j + wd];
-          else qp[g - g0][j][wd] = __builtin_amdgcn_readfirstlane(s_q[g][W * j + wd]);
+        for (int j = 0; j < QP; ++j) {
+#pragma unroll
+          for (int wd = 0; wd < W; ++wd) qp[g][j][wd] = s_q[g1 + g][W * j + wd];
         }
       }
-    }
 #pragma unroll
-    for (int i = 0; i < kScanTokPerThread; ++i) {
-      // keep the tokens in load order, so that each waits only for its own rows
-      if (g0 == 0) __builtin_amdgcn_sched_barrier(0);
-      const int t = t0 + (wave * kScanTokPerThread + i) * kWave + lane;
-      // The appended token's row is not in memory yet.  It takes the place of the loaded one once, before
-      // the first head (a copy of the row for every pass costs 64 moves per wave with a group of four).
-      if (g0 == 0 && appending) {
-        if (t == L - 1) {
+      for (int i = 0; i < kScanTokPerThread; ++i) {
+        // keep the tokens in load order, so that each waits only for its own rows
+        if (g1 == 0) __builtin_amdgcn_sched_barrier(0);
+        const int t = t0 + (wave * kScanTokPerThread + i) * kWave + lane;
+        // The appended token's row is not in memory yet.  It takes the place of the loaded one once, before
+        // the first head (a copy of the row for every pass costs 64 moves per wave with a group of four).
+        if (g1 == 0 && appending) {
+          if (t == L - 1) {
 #pragma unroll
-          for (int wq = 0; wq < kRowWords; ++wq) rr[i][wq] = s_new[wq];
+            for (int wq = 0; wq < kRowWords; ++wq) rr[i][wq] = s_new[wq];
+          }
         }
-      }
-      // Groups whose query planes fit the vector registers (up to two heads at d = 96 and 128, four at 64, one from 160 on; three times as
-      // many with one-bit codes) mask their atomics alone (0.1 us of 12.9 for 32 planes of 9235 ragged tokens), others the whole step.
-      constexpr bool kMaskEach = kPlanesInVgprs;
-      if (kMaskEach || t < L) {
+        // Groups whose query planes fit the registers together (up to two heads at d = 96 and 128, four at 64, one from 160 on; three
+        // times as many with one-bit codes) mask their atomics alone (0.1 us of 12.9 for 32 planes of 9235 ragged tokens),
+        // others the whole step.
+        constexpr bool kMaskEach = kTogether == G;
+        if (kMaskEach || t < L) {
 #pragma unroll
-        for (int g = g0; g < g0 + kPassHeads && g < G; ++g) {
-          const uint32_t d = distance(rr[i], [&](int j, int wd) { return qp[g - g0][j][wd]; });
-          s_dt[wave][g - g0][i * kWave + lane] = (uint16_t)d;
-          if constexpr (kWideBins) {
-            if (!kMaskEach || t < L) atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + d, one);
-          } else {
-            // two 16-bit bins per word: 1 for an even distance, 0x10000 for an odd one
-            // (opaque halves: otherwise the compiler turns them into a compare and a select)
-            uint32_t pair = d >> 1, odd16 = (d & 1u) << 4;
-            asm("" : "+v"(pair), "+v"(odd16));
-            if (!kMaskEach || t < L) atomicAdd(hist_lane + g * (kHistReplicas * kHistWords) + pair, 1u << odd16);
+          for (int g = 0; g < kTogether; ++g) {
+            const uint32_t d = distance(rr[i], [&](int j, int wd) { return qp[g][j][wd]; });
+            s_dt[wave][g1 + g - g0][i * kWave + lane] = (uint16_t)d;
+            if constexpr (kWideBins) {
+              if (!kMaskEach || t < L) atomicAdd(hist_lane + (g1 + g) * (kHistReplicas * kHistWords) + d, one);
+            } else {
+              // two 16-bit bins per word: 1 for an even distance, 0x10000 for an odd one
+              // (opaque halves: otherwise the compiler turns them into a compare and a select)
+              uint32_t pair = d >> 1, odd16 = (d & 1u) << 4;
+              asm("" : "+v"(pair), "+v"(odd16));
+              if (!kMaskEach || t < L) atomicAdd(hist_lane + (g1 + g) * (kHistReplicas * kHistWords) + pair, 1u << odd16);
+            }
           }
         }
       }
