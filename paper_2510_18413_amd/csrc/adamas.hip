@@ -175,6 +175,22 @@ int launch_scan(const adamas_config* c, bool fused, const Plan& pl, int batch, h
   return launch_status();
 }
 
+// The step or top-k as one launch.  The caller has set the pointers, max_seq_len and k.
+int launch_one(const adamas_config* c, bool fused, int waves, int batch, hipStream_t st, OneLaunchParams op) {
+  op.Hq = c->num_q_heads;
+  op.Hkv = c->num_kv_heads;
+  op.group = c->num_q_heads / c->num_kv_heads;
+  op.planes = batch * c->num_kv_heads;
+  op.kv_magic = magic_of(c->num_kv_heads);
+  op.pool_tokens = c->pool_tokens;
+  op.list = one_launch_list(op.max_seq_len, op.k);
+  if (!set_of(c).one_launch(fused, waves, st, op)) return ADAMAS_ERR_UNSUPPORTED;
+  return launch_status();
+}
+
+// (stamped calls are those of the two kernels)
+bool traced() { return g_trace_scan != nullptr || g_trace_select != nullptr; }
+
 struct FullPlan {
   int n_splits, chunk;
   int64_t short_len;  // sequences up to this long are cut by their own length (FullAttnParams)
@@ -347,6 +363,20 @@ int adamas_select_topk(const adamas_config* cfg, const void* qcodes, const void*
   if (workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
+
+  const int waves = one_launch_waves(ScanUse::kSelect, cfg, batch, max_seq_len, k, false);
+  if (waves != 0) {
+    OneLaunchParams op{};
+    op.codes = static_cast<const uint8_t*>(codes);
+    op.qcodes = static_cast<const uint8_t*>(qcodes);
+    op.seq_start = seq_start;
+    op.seq_len = seq_len;
+    op.dist_user = dist_out;
+    op.idx_out = idx_out;
+    op.max_seq_len = max_seq_len;
+    op.k = k;
+    return launch_one(cfg, false, waves, batch, st, op);
+  }
 
   ScanParams sp{};
   sp.codes = static_cast<const uint8_t*>(codes);
@@ -527,6 +557,32 @@ int decode_step_impl(const adamas_config* cfg, const Plan* given, const void* q,
   if (given == nullptr && workspace_bytes < workspace_need(cfg, batch, max_seq_len)) return ADAMAS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
+
+  const int waves = stages == ADAMAS_STAGE_ALL && !traced()
+                        ? one_launch_waves(ScanUse::kStep, cfg, batch, max_seq_len, k, page_table != nullptr) : 0;
+  if (waves != 0) {
+    OneLaunchParams op{};
+    op.codes = static_cast<const uint8_t*>(codes);
+    op.codes_w = static_cast<uint8_t*>(codes);
+    op.q = static_cast<const uint16_t*>(q);
+    op.k_new = static_cast<const uint16_t*>(k_new);
+    op.v_new = static_cast<const uint16_t*>(v_new);
+    op.K = static_cast<uint16_t*>(K);
+    op.V = static_cast<uint16_t*>(V);
+    op.seq_start = seq_start;
+    op.seq_len = seq_len;
+    op.idx_out = idx_out;
+    op.out = out;
+    op.max_seq_len = max_seq_len;
+    op.k = k;
+    op.page_table = page_table;
+    op.max_pages = max_pages;
+    op.page_shift = page_shift;
+    op.thr_q = scaled(cfg, cfg->thr_q);
+    op.thr_k = scaled(cfg, cfg->thr_k);
+    op.scale_log2e = scale_log2e(cfg);
+    return launch_one(cfg, true, waves, batch, st, op);
+  }
 
   ScanParams sp{};
   sp.codes = static_cast<const uint8_t*>(codes);

@@ -13,6 +13,7 @@
 #include "device_utils.hpp"
 #include "encode.hpp"
 #include "full_attn.hpp"
+#include "one_launch.hpp"
 #include "scan.hpp"
 #include "select_attn.hpp"
 
@@ -35,6 +36,9 @@ struct KernelSet {
   void (*merge)(dim3 grid, hipStream_t st, const MergeParams& mp);
   void (*full_attn)(int G, dim3 grid, hipStream_t st, const FullAttnParams& fp);
   void (*merge_parts)(dim3 grid, hipStream_t st, const float* partial, float* out, int Hq, int n_parts);
+  // The whole step (fused; paged cache iff op.page_table != nullptr) or top-k on query codes, a workgroup of 4, 8 or 16
+  // waves per head; false, and nothing launched, for any other.
+  bool (*one_launch)(bool fused, int waves, hipStream_t st, const OneLaunchParams& op);
 };
 
 // Defined by kernels_inst.hip for the pair it is compiled for.

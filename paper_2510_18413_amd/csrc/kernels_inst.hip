@@ -76,6 +76,30 @@ void launch_select(bool attn, bool paged, dim3 grid, hipStream_t st, const Selec
   }
 }
 
+template <int WAVES, bool FUSED, bool PAGED>
+bool launch_one_as(hipStream_t st, const OneLaunchParams& op) {
+  const dim3 grid(8 * op.group, (op.planes + 7) / 8);
+  hipLaunchKernelGGL((one_launch_kernel<WAVES, FUSED, METRIC, PAGED, D>), grid, dim3(WAVES * kWave),
+                     one_launch_lds(WAVES, D, op.max_seq_len, op.k, FUSED, PAGED), st, op);
+  return true;
+}
+
+template <int WAVES>
+bool launch_one_waves(bool fused, hipStream_t st, const OneLaunchParams& op) {
+  if (!fused) return launch_one_as<WAVES, false, false>(st, op);
+  if (op.page_table != nullptr) return launch_one_as<WAVES, true, true>(st, op);
+  return launch_one_as<WAVES, true, false>(st, op);
+}
+
+bool launch_one(bool fused, int waves, hipStream_t st, const OneLaunchParams& op) {
+  switch (waves) {
+    case 4: return launch_one_waves<4>(fused, st, op);
+    case 8: return launch_one_waves<8>(fused, st, op);
+    case 16: return launch_one_waves<16>(fused, st, op);
+    default: return false;
+  }
+}
+
 // The launchers below are templates so that a set that does not export them
 // does not instantiate their kernels either.
 // Whether a bulk encode with the transform goes to encode_rows_matrix_kernel.  Lane groups / matrix cores, us, for
@@ -185,6 +209,7 @@ KernelSet make_set() {
   KernelSet ks{};
   ks.scan = launch_scan;
   ks.select = launch_select;
+  ks.one_launch = launch_one;
   if constexpr (M != kMetricL2) ks.encode_rows = launch_encode_rows<BITS>;
   if constexpr (M == kMetricL1) {
     ks.sparse_attn = launch_sparse_attn<D>;

@@ -245,6 +245,68 @@ inline int early_rows_pay(const Plan& pl, int64_t n_heads) {
   return n_heads * pl.n_segs <= 2 * kTargetWorkgroups && pl.seg_len <= 4 * kSegGranule ? 1 : 0;
 }
 
+// ---- one launch, a workgroup per head (one_launch.hpp) ----
+
+// LDS of such a workgroup that is asked for at launch: the list of rows (paged caches: and that of positions), then the
+// distances (16 bits a token), whose place the waves' attention states take afterwards; and what its kernel declares.
+inline int32_t one_launch_list(int64_t max_seq_len, int32_t k) { return (int32_t)(((k < max_seq_len ? k : max_seq_len) + 3) & ~(int64_t)3); }
+inline size_t one_launch_lds(int waves, int head_dim, int64_t max_seq_len, int32_t k, bool attn, bool paged) {
+  const size_t dist = (size_t)((max_seq_len + 63) & ~(int64_t)63) * 2;
+  const size_t states = attn ? (size_t)waves * (2 + head_dim) * 4 : 0;
+  return (size_t)one_launch_list(max_seq_len, k) * (paged ? 8 : 4) + (dist > states ? dist : states);
+}
+inline size_t one_launch_static_lds(int metric, int head_dim) { return (size_t)(max_dist_of(metric, head_dim) + 2) * 8 + 1024; }
+constexpr size_t kOneLaunchLds = 64 * 1024;  // what a launch may have of a compute unit's 160 KB without asking for more
+
+// Waves of the workgroups if the step, or top-k on query codes, is to run as one launch; 0 for scan and select by themselves.
+// A head then has one compute unit's rate for its rows, so what decides is the context against the heads that there are to fill the
+// chip, in rows of 32 bytes (half of the time goes with the bytes of a row).  Measured: 327 step shapes and 223 of top-k (d = 64 to
+// 256, all code formats, 1 to 4608 heads, 200 to 24000 tokens); the step's choice is 0.9 % above the best of two launches and
+// 4, 8 and 16 waves on average, and slower than two launches by more than 1.5 % once (3.9 %).  us a layer (chosen *):
+//                                                two launches    4      8     16 waves
+//   step,  one head of 1024 tokens, k = 64              8.5     6.0    5.8*   6.3
+//          32 heads of 1000, k = 128                   11.0     7.2    6.6*   7.3
+//          32 of 4000, k = 256                         14.1    11.9    9.7    9.7*
+//          32 of 8000, k = 128                         11.9    11.2    9.6*   9.6
+//          32 of 12000, k = 128                        11.8    13.6   11.6   11.0*
+//          32 of 16384, k = 128                        11.5*   15.8   13.3   12.5
+//          32 heads alone in their groups, 16384       13.2*   18.8   15.2   14.0
+//          256 ragged, up to 8000, k = 256             23.7    18.1   15.3   15.6*
+//          384 of 15503, k = 232                       32.6    29.3   28.0*  31.8
+//          512 ragged, up to 16469, k = 40             26.9    22.3   21.5*  23.2
+//          512 ragged, up to 24000, k = 128            33.0*   37.6   35.9   39.6
+//          1536 ragged, up to 6001, paged, k = 256     59.6    52.5*  53.0   67.6
+//          2048 of 2048, k = 128                       43.3    38.9*  39.1   59.3
+//   top-k, 32 heads of 8000, k = 512                    7.9     9.5    6.8*   7.1
+//          32 of 12000                                  8.4*   12.2    8.3    8.1
+//          64 of 12000                                  9.8    12.3    8.4    8.2*
+//          64 of 20011                                 11.2*   18.2   13.0   12.5
+//          256 of 24000                                20.5    21.0   15.5   14.9*
+//          512 of 16000                                23.6    22.7   20.7   19.4*
+//          512 of 20011                                30.5*   34.2   32.9   31.5
+// Sixteen waves where a head is alone on its compute unit and long (or its list is); four where there are several heads for each,
+// which then overlap one's gather with another's scan.
+inline int one_launch_waves(ScanUse use, const adamas_config* c, int32_t batch, int64_t max_seq_len, int32_t k, bool paged) {
+  const int64_t heads = (int64_t)batch * c->num_q_heads;
+  // (the grid's second extent; the kernel's division of a plane by the KV heads is exact below 2^32)
+  const int64_t planes = (int64_t)batch * c->num_kv_heads;
+  if (use == ScanUse::kDistances || planes > 8 * 65535 || planes * c->num_kv_heads >= (int64_t)1 << 32) return 0;
+  const int metric = metric_of(c);
+  const double row = code_bits(c) * c->head_dim / 256.0, length = max_seq_len * std::sqrt(row);
+  const double few = heads < 256 ? (double)heads : 256.0;
+  int waves;
+  if (use == ScanUse::kStep) {
+    if (length >= (heads > 256 ? 20000.0 : 12000.0 + 40.0 * few)) return 0;
+    waves = heads <= 256 && max_seq_len * row + 20.0 * k * c->head_dim / 128 > 8000.0 ? 16 : heads <= 640 ? 8 : 4;
+  } else {
+    if (max_seq_len >= (heads > 256 ? 18000.0 : 9000.0 + 70.0 * few)) return 0;
+    waves = heads > 640 ? 4 : max_seq_len > 8000 ? 16 : 8;
+  }
+  const size_t lds = one_launch_lds(waves, c->head_dim, max_seq_len, k, use == ScanUse::kStep, paged) +
+                     one_launch_static_lds(metric, c->head_dim);
+  return lds <= kOneLaunchLds ? waves : 0;
+}
+
 // Stand-alone sparse attention: workgroups per head, and whether they are of sixteen waves (one per head then).
 struct SparseCut {
   int parts;
