@@ -80,7 +80,9 @@ __global__ __launch_bounds__(WAVES * kWave) void one_launch_kernel(const OneLaun
   constexpr int kReplicas = 2;  // of the histogram, picked by lane
   constexpr int kHistBins = kBins + 1;  // the last one takes the lanes past the end
   constexpr int kHistWords = (kReplicas * kHistBins + 3) & ~3;
-  constexpr int U = 4;          // code rows in flight per lane
+  // Code rows in flight per lane.  Two of the longer ones: three-bit codes at d = 128 32.4 -> 31.3 us for 40 ragged sequences of 3000
+  // tokens, d = 256 33.8 -> 32.9 for 24, and with three-bit codes there four rows spill registers (87 us instead of 30 for 8 x 6000).
+  constexpr int U = kRowWords >= 12 ? 2 : 4;
   __shared__ __align__(16) uint32_t s_hist[kHistWords];
   __shared__ uint32_t s_q[3 * W];
   __shared__ uint32_t s_new[kRowWords];

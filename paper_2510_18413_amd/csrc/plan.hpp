@@ -292,12 +292,15 @@ inline int one_launch_waves(ScanUse use, const adamas_config* c, int32_t batch, 
   const int64_t planes = (int64_t)batch * c->num_kv_heads;
   if (use == ScanUse::kDistances || planes > 8 * 65535 || planes * c->num_kv_heads >= (int64_t)1 << 32) return 0;
   const int metric = metric_of(c);
-  const double row = code_bits(c) * c->head_dim / 256.0, length = max_seq_len * std::sqrt(row);
+  // (rows that only divide into pieces of four bytes take a load for each; two launches share them among the heads of a group)
+  const int row_bytes = c->head_dim / 8 * code_bits(c);
+  const double row = row_bytes / 32.0, length = max_seq_len * std::sqrt(row) * (row_bytes % 16 == 0 ? 1.0 : row_bytes % 8 == 0 ? 1.1 : 2.0);
   const double few = heads < 256 ? (double)heads : 256.0;
   int waves;
   if (use == ScanUse::kStep) {
-    if (length >= (heads > 256 ? 20000.0 : 12000.0 + 40.0 * few)) return 0;
+    if (length >= (heads <= 256 ? 12000.0 + 40.0 * few : row_bytes % 8 == 0 ? 20000.0 : 12000.0)) return 0;
     waves = heads <= 256 && max_seq_len * row + 20.0 * k * c->head_dim / 128 > 8000.0 ? 16 : heads <= 640 ? 8 : 4;
+    if (waves == 16 && row >= 3.0) waves = 8;  // (three-bit codes at d = 256 take more registers than sixteen waves may have)
   } else {
     if (max_seq_len >= (heads > 256 ? 18000.0 : 9000.0 + 70.0 * few)) return 0;
     waves = heads > 640 ? 4 : max_seq_len > 8000 ? 16 : 8;

@@ -194,6 +194,7 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   constexpr bool kAllTogether = G * QP * W <= 24;
   constexpr int kPassHeads = kAllTogether ? G : (24 / (QP * W) > 0 ? 24 / (QP * W) : 1);
   constexpr int kTogether = kAllTogether ? G : 1;
+  constexpr bool kScalarPlanes = !kAllTogether && QP * W + kScanTokPerThread * kRowWords > 96;
   // per wave: its 256 distances to each query head of a pass, in token order
   __shared__ __align__(16) uint16_t s_dt[WAVES][kPassHeads][kScanTokPerThread * kWave];
 
@@ -369,6 +370,8 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   // words of planes in scalar registers a wave takes more than 80, of which a compute unit holds 28 waves instead of
   // 32, one workgroup of sixteen instead of two (16 ragged sequences 41.5 -> 45.4 us a layer).  Up to 24 words
   // (the method's group of one or two) at once; larger groups one head after the other over the rows, which stay in registers.
+  // Three-bit codes at d = 256 keep them in scalar ones: with the rows they do not fit (24 ragged sequences of 10540 tokens, groups of six
+  // 33.9 us a layer, 44.1 in vector registers).
   // qp[g][j][wd]: plane j of word wd; for 2-bit codes j = 2 is lo ^ hi.
   uint32_t* hist_lane = s_hist + (lane & (kHistReplicas - 1)) * kHistWords;
   auto distance = [](const uint32_t (&row)[kRowWords], auto q) { return row_distance<METRIC, D>(row, q); };
@@ -385,7 +388,10 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
 #pragma unroll
         for (int j = 0; j < QP; ++j) {
 #pragma unroll
-          for (int wd = 0; wd < W; ++wd) qp[g][j][wd] = s_q[g1 + g][W * j + wd];
+          for (int wd = 0; wd < W; ++wd) {
+            qp[g][j][wd] = s_q[g1 + g][W * j + wd];
+            if constexpr (kScalarPlanes) qp[g][j][wd] = __builtin_amdgcn_readfirstlane(qp[g][j][wd]);
+          }
         }
       }
 #pragma unroll
