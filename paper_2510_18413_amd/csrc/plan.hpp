@@ -294,7 +294,8 @@ inline int one_launch_waves(ScanUse use, const adamas_config* c, int32_t batch, 
   const int metric = metric_of(c);
   // (rows that only divide into pieces of four bytes take a load for each; two launches share them among the heads of a group)
   const int row_bytes = c->head_dim / 8 * code_bits(c);
-  const double row = row_bytes / 32.0, length = max_seq_len * std::sqrt(row) * (row_bytes % 16 == 0 ? 1.0 : row_bytes % 8 == 0 ? 1.1 : 2.0);
+  const double row = row_bytes / 32.0, length = max_seq_len * std::sqrt(row) * (row_bytes % 16 == 0 ? 1.0 : row_bytes % 8 == 0 ? 1.1 : 2.0) +
+                                                k * c->head_dim / 128.0;
   const double few = heads < 256 ? (double)heads : 256.0;
   int waves;
   if (use == ScanUse::kStep) {
