@@ -394,6 +394,7 @@ __global__ __launch_bounds__(WAVES * kWave) void one_launch_kernel(const OneLaun
     }
   }
   __syncthreads();
+  // (before the gather, which waits for it: while the rows travel, or at the end, cost 0.1 us of 6.5)
   if (idx_row != nullptr)
     for (int i = tid; i < p.k; i += THREADS) idx_row[i] = i < kk ? s_pos[i] : -1;
   if constexpr (FUSED) {
@@ -401,7 +402,7 @@ __global__ __launch_bounds__(WAVES * kWave) void one_launch_kernel(const OneLaun
     float M, lsum, o;
     PhaseTrace trace;
     attention_rows<THREADS, D>(s_sel, kk, PAGED ? (int)p.pool_tokens : L, qv, p.K + row0, p.V + row0, p.scale_log2e,
-                               *reinterpret_cast<AttnShared<THREADS, D>*>(s_dist), M, lsum, o, trace);
+                               *reinterpret_cast<AttnShared<THREADS, D>*>(s_dist), M, lsum, o, trace, [] {});
     if (tid < D) p.out[head * D + tid] = lsum > 0.f ? o / lsum : 0.f;
   }
 }

@@ -178,7 +178,7 @@ __device__ __forceinline__ void combine_lane_groups(float& m, float& l, float (&
 // Entries of s_sel are clamped to [0, n_tokens) before use (n_tokens >= 1 when n > 0).
 // qv is the lane's piece of the query, from load_query_piece: the caller
 // requests it as early as it can, so that it does not arrive after the rows.
-// All threads must call it.
+// All threads must call it.  meanwhile: called once by every wave, when its first rows are on their way.
 template <int D>
 __device__ __forceinline__ uint4 load_query_piece(const uint16_t* __restrict__ q) {
   constexpr int LPR = HeadDim<D>::kRowGroup;
@@ -186,12 +186,12 @@ __device__ __forceinline__ uint4 load_query_piece(const uint16_t* __restrict__ q
   return gl < HeadDim<D>::kRowLanes ? *reinterpret_cast<const uint4*>(q + gl * 8) : make_uint4(0, 0, 0, 0);
 }
 
-template <int THREADS, int D>
+template <int THREADS, int D, typename F>
 __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int n_tokens, const uint4 qv,
                                                const uint16_t* __restrict__ Kp,
                                                const uint16_t* __restrict__ Vp, double scale_log2e,
                                                AttnShared<THREADS, D>& sh, float& M, float& lsum,
-                                               float& o, PhaseTrace& trace) {
+                                               float& o, PhaseTrace& trace, F meanwhile) {
   // Scores in fp64: products of bf16 values are exact, and so (for all practical
   // purposes) is their sum.  An fp32 dot product of 128 terms is off by about
   // 1e-5 in the exponent of a weight; where the weighted rows nearly cancel that
@@ -235,6 +235,7 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
   // otherwise put that wait between the requests of a batch where it comes too late: a round trip in every batch
   // (paged, 240 heads of 1160 rows: 81 us a step instead of 74).
   __builtin_amdgcn_s_waitcnt(0x0f70);
+  if (wave_grp >= n || (NW > 4 && wave_grp >= kGroups)) meanwhile();
   if (NW <= 4 || wave_grp < kGroups) {  // (not the waves that a short list leaves out)
     for (int b0 = 0; b0 + wave_grp < n; b0 += kGroups * U) {
       const int i0 = b0 + grp;
@@ -259,6 +260,7 @@ __device__ __forceinline__ void attention_rows(const int32_t* s_sel, int n, int 
           vv[u] = *reinterpret_cast<const uint4*>(Vp + off);
         }
       }
+      if (b0 == 0) meanwhile();
       auto partial = [&](int u) {
 #pragma clang fp contract(off)
         const uint4 k4 = kv[u];
@@ -666,6 +668,9 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
   trace.stamp(kSelThreshold, false);
   const uint32_t seg_pos0 = run_lt + min(run_eq, (uint32_t)r);
   int32_t* idx_row = p.idx_out != nullptr ? p.idx_out + head * p.k : nullptr;
+  // Contiguous caches gather by position: their list is what idx_out gets, and it gets it while the first rows travel (the gather waits
+  // for everything in flight before it, stores included).  A paged cache's list holds rows.
+  constexpr bool kIdxFromList = ATTN && !PAGED;
   // what the low bits of a stored distance are compared with
   const uint32_t y = BYTES ? (uint32_t)(T & 255) * 0x01010101u : (uint32_t)T * 0x00010001u;
 
@@ -853,7 +858,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
             // pos < kk always holds for consistent histograms; the checks keep a
             // corrupted workspace from turning into an out-of-bounds store.
             if (pos < (uint32_t)kk) {
-              if (idx_row != nullptr) idx_row[pos] = t + j;
+              if (!kIdxFromList && idx_row != nullptr) idx_row[pos] = t + j;
               // the gather list holds token positions, or pool rows for a paged cache
               if (ATTN && pos - seg_pos0 < (uint32_t)kMaxK)
                 s_sel[pos - seg_pos0] = PAGED ? (int32_t)(page_row0 + j) : t + j;
@@ -889,16 +894,30 @@ __global__ __launch_bounds__(THREADS) void select_kernel(const SelectParams p) {
   }
   };
   run_passes(std::integral_constant<int, BYTES ? CHUNK : 1>{});
-  if (seg == 0 && idx_row != nullptr)
-    for (int i = kk + tid; i < p.k; i += THREADS) idx_row[i] = -1;
+  auto pad_idx = [&]() {
+    if (seg == 0 && idx_row != nullptr)
+      for (int i = kk + tid; i < p.k; i += THREADS) idx_row[i] = -1;
+  };
+  if constexpr (!kIdxFromList) pad_idx();
 
   if constexpr (ATTN) {
     const int n_sel = min((int)(run_lt + min(run_eq, (uint32_t)r) - seg_pos0), kk);
+    auto write_idx = [&]() {
+      if constexpr (kIdxFromList) {
+        if (idx_row != nullptr) {
+          for (int i = tid; i < n_sel; i += THREADS) {
+            // (as in the emission: a corrupted workspace must not become a store out of bounds)
+            if (seg_pos0 + (uint32_t)i < (uint32_t)kk) idx_row[seg_pos0 + i] = s_sel[i];
+          }
+        }
+        pad_idx();
+      }
+    };
     __syncthreads();  // s_sel complete
     trace.stamp(kSelCompacted, false);  // (not waiting for the index stores)
     float M, lsum, o;
     attention_rows<THREADS, D>(s_sel, n_sel, (int)gather_rows, qv,
-                            p.K + row0, p.V + row0, p.scale_log2e, s_attn, M, lsum, o, trace);
+                            p.K + row0, p.V + row0, p.scale_log2e, s_attn, M, lsum, o, trace, write_idx);
     // the early requests have long returned; this only keeps them alive until here
 #pragma unroll
     for (int i = 0; i < 2 * kRowLines; ++i) asm volatile("" : : "v"(early[i]));
@@ -1014,7 +1033,7 @@ __global__ __launch_bounds__(THREADS) void sparse_attn_kernel(const AttnParams p
   float M, lsum, o;
   PhaseTrace trace;  // not recorded for the stand-alone kernel
   attention_rows<THREADS, D>(s_sel, (int)n, (int)min((int64_t)0x7fffffff, p.pool_tokens - start),
-                               qv, p.K + row0, p.V + row0, p.scale_log2e, s_attn, M, lsum, o, trace);
+                               qv, p.K + row0, p.V + row0, p.scale_log2e, s_attn, M, lsum, o, trace, [] {});
   if (tid < D) {
     if (gridDim.x == 1) {
       p.out[head * D + tid] = lsum > 0.f ? o / lsum : 0.f;
