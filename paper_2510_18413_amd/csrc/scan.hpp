@@ -85,12 +85,14 @@ enum ScanPhase {
   kScanEnd           // histogram flushed and acknowledged
 };
 
+// (The compiler's own lane write and no inline assembly: a vector instruction that writes a scalar register needs two wait states before
+// another one reads it, which the compiler keeps between instructions that it knows.)
+extern "C" __device__ uint32_t write_lane(uint32_t x, uint32_t lane, uint32_t v) __asm("llvm.amdgcn.writelane.i32");
 // v with lane I's value replaced by the wave-uniform x, whether that lane is active or not: only where the wave branched as a whole, by
 // a scalar condition.  (A branch by lanes may be run through with none of them active, and v's register hold another path's value.)
 template <int I>
 __device__ __forceinline__ uint32_t set_lane(uint32_t v, uint32_t x) {
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(I));
-  return v;
+  return write_lane(x, I, v);
 }
 
 // An encoded vector from its wave (every lane holds all of it, w[p][g]: plane p of word g) to LDS, a word per lane: twelve lane
