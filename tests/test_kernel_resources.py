@@ -1,0 +1,27 @@
+"""What the kernels of the built library take of a compute unit, where a register more costs a workgroup (tests/kernel_resources.py)."""
+
+import re
+
+import pytest
+
+import kernel_resources as R
+
+METRIC = {"method": 0, "squared differences": 1, "one bit": 2, "three bits": 3}
+LARGEST = {"method": 3, "squared differences": 9, "one bit": 1, "three bits": 7}   # distance per dimension
+
+
+def instances(pattern):
+    import re
+    found = {n: k for n, k in R.kernels().items() if re.fullmatch(pattern, n)}
+    assert found, pattern
+    return found
+
+
+@pytest.mark.parametrize("metric,d", [(m, d) for m in METRIC for d in (64, 96, 128) if (m, d) != ("squared differences", 128)])
+def test_six_workgroups_of_the_select_kernel_fit_a_compute_unit(metric, d):
+    """Contiguous caches, with attention: 256 threads each, so six waves per SIMD.  (Not where the histograms of sixteen tiles are
+    longer than a thread per pair of bins takes: these need 90 registers before the attention.)"""
+    wide = LARGEST[metric] * d > 511
+    tiles = "[48]" if wide else r"\d+"
+    for name, k in instances(r"select_kernel<256, true, %d, false, %d, \d+, %s>" % (METRIC[metric], d, tiles)).items():
+        assert R.waves_per_simd(k) >= 6 and 6 * k.lds <= 160 * 1024 and k.scratch == 0, (name, k)
