@@ -25,3 +25,14 @@ def test_six_workgroups_of_the_select_kernel_fit_a_compute_unit(metric, d):
     tiles = "[48]" if wide else r"\d+"
     for name, k in instances(r"select_kernel<256, true, %d, false, %d, \d+, %s>" % (METRIC[metric], d, tiles)).items():
         assert R.waves_per_simd(k) >= 6 and 6 * k.lds <= 160 * 1024 and k.scratch == 0, (name, k)
+
+
+def fused_scans(group, waves, metric, d):
+    return instances(r"scan_kernel<%d, true, %d, %d, (?:true|false), %d>" % (group, waves, METRIC[metric], d))
+
+
+@pytest.mark.parametrize("group", range(3, 8))
+def test_two_workgroups_of_the_squared_difference_scan_fit_a_compute_unit(group):
+    """Sixteen waves each, d = 128: 64 vector registers."""
+    for name, k in fused_scans(group, 16, "squared differences", 128).items():
+        assert k.vgprs <= 64 and k.scratch == 0, (name, k)
