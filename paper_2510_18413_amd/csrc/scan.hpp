@@ -199,8 +199,10 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   constexpr int QP = BITS == 2 ? 3 : BITS;
   constexpr bool kAllTogether = G * QP * W <= 24;
   constexpr int kPassHeads = kAllTogether ? G : (24 / (QP * W) > 0 ? 24 / (QP * W) : 1);
-  constexpr int kTogether = kAllTogether ? G : 1;
-  constexpr bool kScalarPlanes = !kAllTogether && QP * W + kScanTokPerThread * kRowWords > 96;
+  constexpr int kScanRowWords = kScanTokPerThread * kRowWords, kHeadWords = QP * W + kScanRowWords;
+  constexpr bool kScalarPlanes = !kAllTogether && (kHeadWords > 96 || (!FUSED && kHeadWords <= 68 && (BITS == 3 || kHeadWords >= 60)));
+  constexpr int kTogether =
+      kAllTogether ? G : kScalarPlanes || kPassHeads * QP * W + kScanRowWords <= (BITS == 3 ? 44 : 48) ? kPassHeads : 1;
   // per wave: its 256 distances to each query head of a pass, in token order
   __shared__ __align__(16) uint16_t s_dt[WAVES][kPassHeads][kScanTokPerThread * kWave];
 
@@ -375,9 +377,13 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
   // time of one without as soon as a SIMD has a second wave (exclusive or, and, three-input logic: 4.2 and 2.4 clocks), and with 24
   // words of planes in scalar registers a wave takes more than 80, of which a compute unit holds 28 waves instead of
   // 32, one workgroup of sixteen instead of two (16 ragged sequences 41.5 -> 45.4 us a layer).  Up to 24 words
-  // (the method's group of one or two) at once; larger groups one head after the other over the rows, which stay in registers.
-  // Three-bit codes at d = 256 keep them in scalar ones: with the rows they do not fit (24 ragged sequences of 10540 tokens, groups of six
-  // 33.9 us a layer, 44.1 in vector registers).
+  // (the method's group of one or two) at once; larger groups the heads of a pass at once where their planes and the rows leave a wave
+  // within 64 registers, else one head after the other over the rows, which stay in registers.  (d = 96, groups of four: one by one
+  // 27.4 us for 24 ragged sequences of 24000 tokens, two by two 25.8; d = 64, groups of eight 26.9 and 25.1.)
+  // Scalar registers hold them where they do not fit next to the rows, or cost a workgroup: three-bit codes at d = 256 (24 ragged
+  // sequences of 10540 tokens, groups of six 33.9 us a layer, 44.1 in vector registers), and without the encode, which takes most, three-bit codes up to
+  // d = 128 and two-bit ones at 192 (top-k of 8 sequences of 24000 tokens, three bits at d = 128, groups of three 31.8 us in vector
+  // registers, 30.5; d = 192, groups of two 27.0 and 26.3).
   // qp[g][j][wd]: plane j of word wd; for 2-bit codes j = 2 is lo ^ hi.
   uint32_t* hist_lane = s_hist + (lane & (kHistReplicas - 1)) * kHistWords;
   auto distance = [](const uint32_t (&row)[kRowWords], auto q) { return row_distance<METRIC, D>(row, q); };
@@ -390,7 +396,7 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
     for (int g1 = g0; g1 < g0 + kPassHeads && g1 < G; g1 += kTogether) {
       uint32_t qp[kTogether][QP][W];
 #pragma unroll
-      for (int g = 0; g < kTogether; ++g) {
+      for (int g = 0; g < kTogether && g1 + g < G; ++g) {
 #pragma unroll
         for (int j = 0; j < QP; ++j) {
 #pragma unroll
@@ -419,7 +425,7 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
         constexpr bool kMaskEach = kTogether == G;
         if (kMaskEach || t < L) {
 #pragma unroll
-          for (int g = 0; g < kTogether; ++g) {
+          for (int g = 0; g < kTogether && g1 + g < G; ++g) {
             const uint32_t d = distance(rr[i], [&](int j, int wd) { return qp[g][j][wd]; });
             s_dt[wave][g1 + g - g0][i * kWave + lane] = (uint16_t)d;
             if constexpr (kWideBins) {

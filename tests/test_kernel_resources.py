@@ -36,3 +36,10 @@ def test_two_workgroups_of_the_squared_difference_scan_fit_a_compute_unit(group)
     """Sixteen waves each, d = 128: 64 vector registers."""
     for name, k in fused_scans(group, 16, "squared differences", 128).items():
         assert k.vgprs <= 64 and k.scratch == 0, (name, k)
+
+
+@pytest.mark.parametrize("metric,d,groups,waves", [("three bits", 128, "[3-8]", 6), ("method", 192, "[2-8]", 6), ("squared differences", 192, "[2-7]", 6)])
+def test_three_workgroups_of_the_scan_of_query_codes_fit_a_compute_unit(metric, d, groups, waves):
+    """Eight waves each: query planes in scalar registers where they would cost the third workgroup."""
+    for name, k in instances(r"scan_kernel<%s, false, 8, %d, false, %d>" % (groups, METRIC[metric], d)).items():
+        assert R.waves_per_simd(k) >= waves and k.scratch == 0, (name, k)
