@@ -176,8 +176,20 @@ __device__ __forceinline__ uint32_t row_distance(const uint32_t (&row)[Dist<METR
 
 // WAVES = wavefronts per workgroup (4, 8 or 16): the tile is WAVES * 256 tokens.
 // D = head dimension: W = D / 32 words per code row.
+// Waves per SIMD that the registers of a fused workgroup of three-bit codes have to leave room for, where the compiler takes a few more
+// than that by itself: at d = 256 130 vector registers, with which a compute unit holds one workgroup of eight waves instead of two (16
+// sequences of 17000 tokens, groups of four: 121.6 us a layer, 102.8 with two); at d = 64, groups of two, 85 scalar ones, of which
+// eight waves may have 80 (scan of 24 ragged sequences of 24000 tokens 24.5 us, 21.6 with them).  (Groups of one and eight
+// at d = 256 need more than a few.)
+template <int G, int WAVES, int METRIC, int D>
+constexpr int kScanWavesPerSimd = METRIC != kMetricB3                       ? WAVES / 4
+                                  : D == 64 && G == 2 && WAVES == 16          ? 8
+                                  : D == 256 && G > 1 && G < 8 && WAVES == 8 ? 4
+                                                                             : WAVES / 4;
 template <int G, bool FUSED, int WAVES, int METRIC, bool PAGED, int D>
-__global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p) {
+__global__ __launch_bounds__(WAVES * kWave)
+__attribute__((amdgpu_waves_per_eu(FUSED ? kScanWavesPerSimd<G, WAVES, METRIC, D> : WAVES / 4)))
+void scan_kernel(const ScanParams p) {
   static_assert(FUSED || !PAGED, "the paged layout is served by the fused step only");
   using Fmt = Dist<METRIC, D>;
   constexpr int kNumBins = Fmt::kBins;
@@ -390,6 +402,10 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
 
   uint32_t one = 1;  // (opaque: otherwise written anew for every use)
   asm("" : "+v"(one));
+  // Three-bit codes from d = 160 on spill in workgroups of sixteen waves: the tokens' numbers are made again at their use, not kept (d = 160,
+  // groups of three, 24 ragged sequences of 24000 tokens: 85.7 -> 81.4 us; of six 123.2 -> 115.4).
+  int of_wave = lane;
+  if constexpr (FUSED && BITS == 3 && WAVES == 16 && D >= 160) asm("" : "+v"(of_wave));
 #pragma unroll
   for (int g0 = 0; g0 < G; g0 += kPassHeads) {
 #pragma unroll
@@ -410,7 +426,7 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_kernel(const ScanParams p)
       for (int i = 0; i < kScanTokPerThread; ++i) {
         // keep the tokens in load order, so that each waits only for its own rows
         if (g1 == 0) __builtin_amdgcn_sched_barrier(0);
-        const int t = t0 + (wave * kScanTokPerThread + i) * kWave + lane;
+        const int t = t0 + (wave * kScanTokPerThread + i) * kWave + of_wave;
         // The appended token's row is not in memory yet.  It takes the place of the loaded one once, before
         // the first head (a copy of the row for every pass costs 64 moves per wave with a group of four).
         if (g1 == 0 && appending) {

@@ -43,3 +43,13 @@ def test_three_workgroups_of_the_scan_of_query_codes_fit_a_compute_unit(metric, 
     """Eight waves each: query planes in scalar registers where they would cost the third workgroup."""
     for name, k in instances(r"scan_kernel<%s, false, 8, %d, false, %d>" % (groups, METRIC[metric], d)).items():
         assert R.waves_per_simd(k) >= waves and k.scratch == 0, (name, k)
+
+
+@pytest.mark.parametrize("group", range(2, 8))
+def test_two_workgroups_of_the_three_bit_scan_fit_a_compute_unit(group):
+    """Eight waves each, d = 256: 128 vector registers.  And groups of two at d = 64: 80 scalar registers for eight waves per SIMD."""
+    for name, k in fused_scans(group, 8, "three bits", 256).items():
+        assert k.vgprs <= 128 and k.scratch == 0, (name, k)
+    if group == 2:
+        for name, k in fused_scans(2, 16, "three bits", 64).items():
+            assert k.vgprs <= 64 and k.sgprs <= 80 and k.scratch == 0, (name, k)
