@@ -364,7 +364,7 @@ int adamas_select_topk(const adamas_config* cfg, const void* qcodes, const void*
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
 
-  const int waves = one_launch_waves(ScanUse::kSelect, cfg, batch, max_seq_len, k, false);
+  const int waves = one_launch_waves(ScanUse::kSelect, cfg, batch, max_seq_len, k, false, pl);
   if (waves != 0) {
     OneLaunchParams op{};
     op.codes = static_cast<const uint8_t*>(codes);
@@ -559,7 +559,7 @@ int decode_step_impl(const adamas_config* cfg, const Plan* given, const void* q,
   clear_stale_error();
 
   const int waves = stages == ADAMAS_STAGE_ALL && !traced()
-                        ? one_launch_waves(ScanUse::kStep, cfg, batch, max_seq_len, k, page_table != nullptr) : 0;
+                        ? one_launch_waves(ScanUse::kStep, cfg, batch, max_seq_len, k, page_table != nullptr, pl) : 0;
   if (waves != 0) {
     OneLaunchParams op{};
     op.codes = static_cast<const uint8_t*>(codes);

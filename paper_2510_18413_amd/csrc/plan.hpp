@@ -33,6 +33,7 @@ struct Plan {
   int metric;        // code format + distance estimator (struct Dist)
   int head_dim;      // one of ADAMAS_FOR_EACH_HEAD_DIM (kernel_set.hpp)
   int g_shift;       // 2^g_shift scan workgroups per (tile, KV head), each with a share of the query group
+  double cost;       // of the cut that choose_cut took (scan_cost)
   int64_t dist_stride;
   size_t off_dist, off_high, off_hist, off_partial, total;
 };
@@ -175,10 +176,9 @@ inline int heads_per_part(int group, int g_shift) {
   return g_shift >= 0 && g_shift <= 3 && group % (1 << g_shift) == 0 ? group >> g_shift : 0;
 }
 
-// Sets tile_tokens and g_shift.
+// Sets tile_tokens, g_shift and cost.
 inline void choose_cut(Plan* pl, ScanUse use, int group, int64_t planes, int64_t max_seq_len) {
   auto n_tiles_of = [&](int tile) { return (max_seq_len + tile - 1) / tile; };
-  double best = 0.0;
   for (int tile = 4096; tile >= 1024; tile /= 2) {
     if (tile > 1024 && tile >= 2 * max_seq_len) continue;
     // never more tiles than two per compute unit in exchange for smaller ones
@@ -188,8 +188,8 @@ inline void choose_cut(Plan* pl, ScanUse use, int group, int64_t planes, int64_t
       if (shift > 0 && n_wg > kTargetWorkgroups) break;
       const double cost =
           scan_cost(use, pl->metric, pl->head_dim, n_wg, n_tiles_of(tile), tile, group, 1 << shift);
-      if (pl->tile_tokens == 0 || cost < best) {
-        best = cost;
+      if (pl->tile_tokens == 0 || cost < pl->cost) {
+        pl->cost = cost;
         pl->tile_tokens = tile;
         pl->g_shift = shift;
       }
@@ -258,16 +258,76 @@ inline size_t one_launch_lds(int waves, int head_dim, int64_t max_seq_len, int32
 inline size_t one_launch_static_lds(int metric, int head_dim) { return (size_t)(max_dist_of(metric, head_dim) + 2) * 8 + 1024; }
 constexpr size_t kOneLaunchLds = 64 * 1024;  // what a launch may have of a compute unit's 160 KB without asking for more
 
-// Waves of the workgroups if the step, or top-k on query codes, is to run as one launch; 0 for scan and select by themselves.
+// Waves of a SIMD that the registers of one_launch_kernel leave room for.
+inline int one_launch_waves_per_simd(bool attn, int metric, int d) {
+  const bool three = metric == kMetricB3, one = metric == kMetricB1;
+  if (attn) return three && d == 256 ? 3 : d == 160 || (three && d >= 160) ? 4 : (d == 256 && !one) || (three && d == 96) ? 5 : 6;
+  if (three) return d == 256 ? 4 : d >= 160 ? 5 : d == 96 ? 6 : 8;
+  return (d == 160 || d == 256) && !one ? 7 : 8;
+}
+
+// The parts of a call that its time in one launch and in two goes with; terms and weights (us) are a least-squares fit to uniform
+// lengths of 9000 calls drawn over d = 64 to 256, all code formats, groups of 1 to 8, 1 to 6000 heads, 200 to 31500
+// tokens; two thirds of them lie within 11 % of it.
+struct CallSize {
+  bool step;
+  int metric, head_dim, words;        // of a code row, 32 bits each
+  double heads, planes, group, length, k;
+  double lines;                       // cache lines that the loads of 64 rows touch: a row's pieces each reach for all of them
+  double code_mb, gather_mb;          // from memory, 10^6 bytes
+};
+inline CallSize call_size(ScanUse use, const adamas_config* c, int32_t batch, int64_t max_seq_len, int32_t k) {
+  const int row = c->head_dim / 8 * code_bits(c), piece = row % 16 == 0 ? 16 : row % 8 == 0 ? 8 : 4;
+  CallSize s{};
+  s.step = use == ScanUse::kStep;
+  s.metric = metric_of(c);
+  s.head_dim = c->head_dim;
+  s.words = row / 4;
+  s.heads = (double)batch * c->num_q_heads;
+  s.planes = (double)batch * c->num_kv_heads;
+  s.group = c->num_q_heads / c->num_kv_heads;
+  s.length = (double)max_seq_len;
+  s.k = k < max_seq_len ? (double)k : (double)max_seq_len;
+  s.lines = row / piece * (64.0 * row / 128);
+  s.code_mb = s.planes * s.length * row * 1e-6;
+  s.gather_mb = s.step ? s.heads * s.k * 4 * s.head_dim * 1e-6 : 0.0;
+  return s;
+}
+// Whole rounds of work while there are few, the average and the uneven last one beyond.
+inline double rounds_of(double x) { return x <= 3.0 ? std::ceil(x) : x + 0.5; }
+
+// One launch: a head has its compute unit's rate for its rows.  The planes of an XCD (every eighth one) share its 32 units; what LDS or
+// registers do not let in at once starts when another workgroup ends.
+inline double one_launch_us(const CallSize& s, int waves, size_t lds) {
+  const double share = rounds_of(std::ceil(s.planes / 8) * s.group / 32);          // workgroups of a compute unit
+  const double by_lds = std::floor(160.0 * 1024 / (lds + 512.0));
+  const double by_waves = std::floor(one_launch_waves_per_simd(s.step, s.metric, s.head_dim) * 4.0 / waves);
+  const double generations = std::fmax(1.0, rounds_of(share / std::fmax(1.0, std::fmin(by_lds, by_waves))));
+  const double steps = s.length / 64, metric = s.metric == kMetricB3 ? 1.39 : s.metric == kMetricL2 ? 1.25 : 1.0;
+  double us = 3.41 + 0.053 * share * waves + 1.5 * (generations - 1.0) + 0.108 * generations * steps / waves +
+              share * steps * (0.000809 * metric * s.words + 0.000254 * s.lines) + 0.14 * s.code_mb;
+  if (s.step) us += 1.74 + 0.0555 * s.gather_mb + s.k * s.head_dim * 1e-3 * (0.054 * share + 0.364 * generations / waves);
+  return us;
+}
+// Two: the scan is spread over the chip and its rows shared by the heads of a group, and a second kernel waits for it.
+inline double two_launch_us(const CallSize& s, const Plan& pl) {
+  const double tiles = s.planes * pl.n_tiles * (1 << pl.g_shift), wide = s.heads * pl.n_segs;
+  double us = 5.68 + (s.step ? 0.204 : 0.272) * (s.metric == kMetricB3 ? 1.45 : 1.0) * pl.cost * s.words / 8 +
+              0.0000945 * rounds_of(tiles / kTargetWorkgroups) * pl.tile_tokens / 64 * s.lines + 0.143 * s.code_mb +
+              0.971 * std::fmax(1.0, wide / 512);
+  if (s.metric == kMetricL2) us += 0.597 * s.heads * pl.n_tiles / 256;
+  if (s.step) us += 1.5 + 0.126 * s.gather_mb + 0.152 * s.k * s.head_dim * 1e-3 / pl.n_segs + (pl.n_segs > 1 ? 1.27 * wide / 256 : 0.0);
+  return us;
+}
+
+// Waves of the workgroups if the step, or top-k on query codes, is to run as one launch; 0 for scan and select by themselves (pl).
 // A head then has one compute unit's rate for its rows, so what decides is the context against the heads that there are to fill the
-// chip, in rows of 32 bytes (half of the time goes with the bytes of a row).  Measured: 327 step shapes and 223 of top-k (d = 64 to
-// 256, all code formats, 1 to 4608 heads, 200 to 24000 tokens); the step's choice is 0.9 % above the best of two launches and
-// 4, 8 and 16 waves on average, and slower than two launches by more than 1.5 % once (3.9 %).  us a layer (chosen *):
+// chip, in rows of 32 bytes (half of the time goes with the bytes of a row).  us a layer (chosen *):
 //                                                two launches    4      8     16 waves
 //   step,  one head of 1024 tokens, k = 64              8.5     6.0    5.8*   6.3
 //          32 heads of 1000, k = 128                   11.0     7.2    6.6*   7.3
 //          32 of 4000, k = 256                         14.1    11.9    9.7    9.7*
-//          32 of 8000, k = 128                         11.9    11.2    9.6*   9.6
+//          32 of 8000, k = 128                         11.9    11.2    9.6    9.6*
 //          32 of 12000, k = 128                        11.8    13.6   11.6   11.0*
 //          32 of 16384, k = 128                        11.5*   15.8   13.3   12.5
 //          32 heads alone in their groups, 16384       13.2*   18.8   15.2   14.0
@@ -286,7 +346,12 @@ constexpr size_t kOneLaunchLds = 64 * 1024;  // what a launch may have of a comp
 //          512 of 20011                                30.5*   34.2   32.9   31.5
 // Sixteen waves where a head is alone on its compute unit and long (or its list is); four where there are several heads for each,
 // which then overlap one's gather with another's scan.
-inline int one_launch_waves(ScanUse use, const adamas_config* c, int32_t batch, int64_t max_seq_len, int32_t k, bool paged) {
+// These borders hold for the method at d = 128.  Elsewhere the loads of a longer row take a compute unit several times as long (rows of 64
+// bytes touch four times the lines of 32), more workgroups may be due than LDS or registers let in at once, and groups give two
+// launches an edge: there the fit has to agree, within what it is off by (up to sixteen heads the step's borders are right more often).  Of
+// 9000 calls drawn over all sizes and formats 321 take over 5 % longer than two launches where the borders alone decide (up to 2.4
+// times), 132 (up to 1.4) with the fit, and all together take 0.786 of two launches' time; of 440 drawn near the borders 76 and 20.
+inline int one_launch_waves(ScanUse use, const adamas_config* c, int32_t batch, int64_t max_seq_len, int32_t k, bool paged, const Plan& pl) {
   const int64_t heads = (int64_t)batch * c->num_q_heads;
   // (the grid's second extent; the kernel's division of a plane by the KV heads is exact below 2^32)
   const int64_t planes = (int64_t)batch * c->num_kv_heads;
@@ -308,7 +373,10 @@ inline int one_launch_waves(ScanUse use, const adamas_config* c, int32_t batch, 
   }
   const size_t lds = one_launch_lds(waves, c->head_dim, max_seq_len, k, use == ScanUse::kStep, paged) +
                      one_launch_static_lds(metric, c->head_dim);
-  return lds <= kOneLaunchLds ? waves : 0;
+  if (lds > kOneLaunchLds) return 0;
+  if (use == ScanUse::kStep && heads <= 16) return waves;
+  const CallSize size = call_size(use, c, batch, max_seq_len, k);
+  return one_launch_us(size, waves, lds) < two_launch_us(size, pl) * (use == ScanUse::kStep ? 1.1 : 1.05) ? waves : 0;
 }
 
 // Stand-alone sparse attention: workgroups per head, and whether they are of sixteen waves (one per head then).

@@ -52,6 +52,31 @@ def test_the_form_that_was_measured_as_the_best_is_chosen(heads, kv, batch, L, k
     assert waves(config(heads, kv), batch, L, k, use) == want
 
 
+# Calls that one launch takes longer for than two: head dimension, bits, heads, KV heads, sequences, context, k, page, use; us as one, as two
+SLOWER = [((64, 1), (48, 8, 14, 26137, 491, 0, STEP), 57.4, 40.2), ((64, 1), (64, 8, 33, 23812, 16, 64, STEP), 76.6, 55.1),
+          ((64, 2), (96, 16, 8, 27440, 355, 0, STEP), 59.4, 43.3), ((64, 2), (8, 1, 139, 21187, 25, 0, STEP), 44.8, 34.7),
+          ((64, 2), (6, 2, 534, 25990, 42, 0, STEP), 178.1, 137.7), ((160, 1), (256, 32, 12, 7350, 61, 0, STEP), 86.3, 66.3),
+          ((128, 1), (16, 4, 41, 25530, 331, 64, STEP), 56.2, 45.0), ((96, 1), (112, 16, 12, 16330, 41, 0, TOPK), 44.7, 26.8),
+          ((96, 3), (24, 8, 1, 8925, 18, 0, TOPK), 16.8, 10.6), ((256, 2), (48, 16, 2, 15190, 910, 0, TOPK), 25.6, 17.1),
+          ((160, 1), (64, 8, 5, 17395, 819, 0, TOPK), 27.5, 18.5), ((96, 3), (32, 8, 44, 7100, 394, 0, TOPK), 72.2, 50.2),
+          ((96, 2), (7, 1, 408, 16330, 870, 0, TOPK), 98.4, 73.2), ((160, 2), (64, 8, 2, 13312, 36, 0, TOPK), 13.6, 10.9)]
+
+
+@pytest.mark.parametrize("code,call,one,two", SLOWER)
+def test_calls_that_one_launch_takes_longer_for_run_as_two(code, call, one, two):
+    heads, kv, batch, L, k, page, use = call
+    assert one > two and waves(config(heads, kv, *code), batch, L, k, use, page > 0) == 0
+
+
+def test_the_rule_knows_how_many_waves_the_registers_leave_room_for():
+    import kernel_resources as R
+    for metric in range(4):
+        for d in (64, 96, 128, 160, 192, 256):
+            for fused, paged in ((True, False), (True, True), (False, False)):
+                k = R.kernels()["one_launch_kernel<8, %s, %d, %s, %d>" % (str(fused).lower(), metric, str(paged).lower(), d)]
+                assert _lib().one_launch_waves_per_simd(int(fused), metric, d) <= R.waves_per_simd(k), (metric, d, fused, k)
+
+
 def test_a_launch_never_asks_for_more_lds_than_it_may_have_or_a_grid_that_does_not_exist():
     for d, bits, variant in [(64, 1, 0), (128, 2, 0), (128, 2, A.VARIANT_L2), (256, 3, 0), (256, 2, A.VARIANT_L2)]:
         for heads, kv in [(1, 1), (32, 8), (64, 64)]:
