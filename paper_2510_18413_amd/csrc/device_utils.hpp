@@ -295,7 +295,7 @@ __device__ __forceinline__ float row_max_f32(float v) {
   return fmaxf(v, dpp_f32<kDppRowMirror>(v));
 }
 
-// The same for doubles (two 32-bit moves per step).
+// The same move for doubles (two 32-bit ones).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
   const uint64_t b = __builtin_bit_cast(uint64_t, v);
@@ -303,15 +303,6 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xf, 0xf, true);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-template <int LANES>
-__device__ __forceinline__ double lanes_sum_f64(double v) {
-  v += dpp_f64<kDppQuadXor1>(v);
-  v += dpp_f64<kDppQuadXor2>(v);
-  v += dpp_f64<kDppRowHalfMirror>(v);
-  if constexpr (LANES >= 16) v += dpp_f64<kDppRowMirror>(v);
-  if constexpr (LANES >= 32) v += __shfl_xor(v, 16, kWave);
-  return v;
 }
 
 // One step of a sum over lanes for two values at once: a lane keeps the second one if `second`, the first one otherwise, and adds its

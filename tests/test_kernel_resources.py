@@ -53,3 +53,9 @@ def test_two_workgroups_of_the_three_bit_scan_fit_a_compute_unit(group):
     if group == 2:
         for name, k in fused_scans(2, 16, "three bits", 64).items():
             assert k.vgprs <= 64 and k.sgprs <= 80 and k.scratch == 0, (name, k)
+
+
+def test_the_one_launch_is_built_without_spills_and_where_the_rule_can_ask_for_it():
+    for name, k in instances(r"one_launch_kernel<.*>").items():
+        assert k.spilled == 0 and k.scratch == 0, (name, k)
+    assert not [n for n in R.kernels() if re.fullmatch(r"one_launch_kernel<16, true, 3, \w+, 256>", n)]
