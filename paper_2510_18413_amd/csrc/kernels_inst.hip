@@ -19,7 +19,13 @@ constexpr int kSelThreads = 256;
 template <int G, bool FUSED, bool PAGED>
 bool launch_scan_tile(int tile_tokens, dim3 grid, hipStream_t st, const ScanParams& sp) {
   switch (tile_tokens) {
-    case 1024: hipLaunchKernelGGL((scan_kernel<G, FUSED, 4, METRIC, PAGED, D>), grid, dim3(256), 0, st, sp); return true;
+    case 1024:  // (choose_cut: not for the step)
+      if constexpr (FUSED) {
+        return false;
+      } else {
+        hipLaunchKernelGGL((scan_kernel<G, false, 4, METRIC, PAGED, D>), grid, dim3(256), 0, st, sp);
+        return true;
+      }
     case 2048: hipLaunchKernelGGL((scan_kernel<G, FUSED, 8, METRIC, PAGED, D>), grid, dim3(512), 0, st, sp); return true;
     case 4096: hipLaunchKernelGGL((scan_kernel<G, FUSED, 16, METRIC, PAGED, D>), grid, dim3(1024), 0, st, sp); return true;
     default: return false;

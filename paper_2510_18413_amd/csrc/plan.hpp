@@ -118,29 +118,27 @@ enum class ScanUse { kStep, kSelect, kDistances };
 // in memory elsewhere.  The select kernel loads the histograms of kHistBatch tiles at once and pays for each further batch.
 //
 // Measured (us a layer, 32 query heads, d = 128; tile / parts of the group, chosen *; the median spreads by 0.1):
+//                                        2048/1 2048/2 2048/4 4096/1 4096/2 4096/4
+//   step,  1 sequence of 16384, group of 4 12.9   11.8   11.4*  14.1   12.4   11.7
+//          1 of 20000                      13.1   12.1*  13.7   14.4   12.6   12.6
+//          1 of 24576                      13.1   12.2*  13.0   14.2   12.5   13.1
+//          1 of 32768                      13.5   12.5   12.8   14.2   12.5   11.8*
+//          1 of 32771                      14.3   15.1   16.3   14.9   13.4*  15.7
+//          1 of 65540                      20.0   19.6          17.8*  20.1   22.4
+//          1 of 100000                     21.9   23.4          19.2*  22.0   28.1
+//          2 of 20011                      14.2   15.2   16.6   15.4   14.0*  16.4
+//          4 of 60000                      29.3                 27.7*  35.1
+//          16 of 17408                     35.2*                35.5
+//          16 ragged, up to 32768          40.6                 40.1*
+//          1 of 32768, group of 1          15.7*                15.6
+//          4 of 32768, group of 1          39.6                 38.4*
 //                                        1024/1 1024/2 1024/4 2048/1 2048/2 2048/4 4096/1 4096/2 4096/4
-//   step,  1 sequence of 4000, group of 4  13.0   11.9   11.5   12.9   11.7   11.4*  14.2   12.5   11.7
-//          1 of 16384                      13.2   12.1   12.0   12.9   11.8   11.4*  14.1   12.4   11.7
-//          1 of 20000                      13.8   13.8   13.7   13.1   12.1*  13.7   14.4   12.6   12.6
-//          1 of 24576                      14.1   13.5   13.3   13.1   12.2*  13.0   14.2   12.5   13.1
-//          1 of 32768                      14.5   14.1   14.5   13.5   12.5   12.8   14.2   12.5   11.8*
-//          1 of 32771                      16.1   16.3          14.3   15.1   16.3   14.9   13.4*  15.7
-//          1 of 65540                      21.5                 20.0   19.6          17.8*  20.1   22.4
-//          1 of 100000                     25.4                 21.9   23.4          19.2*  22.0   28.1
-//          2 of 20011                      16.4   16.3          14.2   15.2   16.6   15.4   14.0*  16.4
-//          4 of 8000                       15.0   14.5   14.9   14.8   13.9*  14.4   15.9   14.3   15.5
-//          8 of 4000                       15.8   15.7   15.8   15.9   14.7*  16.5   17.0   14.9   16.4
-//          4 of 60000                      32.4                 29.3                 27.7*  35.1
-//          16 of 17408                     36.3                 35.2*                35.5
-//          16 ragged, up to 32768          42.2                 40.6                 40.1*
-//          41 of 2560                      33.3                 33.4*                34.0   36.9
-//          48 ragged, up to 6001           42.2                 41.7*                43.8
-//          1 of 32768, group of 1          17.1                 15.7*                15.6
-//          4 of 32768, group of 1          40.3                 39.6                 38.4*
 //   top-k, 1 of 4000, group of 4            7.7    7.1    6.7*   8.0    7.5    7.1    9.3    8.1    8.0
 //          2 of 20011                      12.2   12.0          10.5   11.1   12.8   11.0   10.2*  12.7
 //          16 of 3000                      11.2   11.3          10.5*  11.1   14.4   10.9   11.7   13.7
 //   distances, 4 of 8000, group of 2        4.7    4.4           4.9    5.4           5.4    5.4
+// The step has no tiles of 1024 tokens: short contexts, where they would pay (1 of 4000: 13.0, 11.9 and 11.5), run as one launch
+// (one_launch_waves), and so do the shorter ones of the calls of top-k.
 // With three-bit codes the sixteen-wave workgroups of the step spill registers from d = 160 on (1 sequence of 32771, d = 256, group
 // of 1: 54.0, 49.2*, 59.8 with tiles of 1024, 2048 and 4096).  Over 972 shapes (d = 64 to 256, groups of 1 to 8, all code
 // formats, paged or not) the step's choice is 0.5 % above the best cut on average, top-k's 1.3 and that of the distances alone 3.0;
@@ -157,7 +155,7 @@ inline double scan_cost(ScanUse use, int metric, int head_dim, int64_t n_wg, int
   if (n_tiles % 8 != 0) per_wave += 0.25 * (parts - 1) / parts;
   if (step) per_wave += 2.0 * heads / wg_waves;
   // small workgroups clear and flush as many histograms for fewer tokens
-  if (wg_waves == 4) per_wave *= step ? 1.25 : 1.08;
+  if (wg_waves == 4) per_wave *= 1.08;
   if (wg_waves == 16 && !step && group > 1) per_wave *= 0.8;
   if (wg_waves == 16 && metric == kMetricB3 && head_dim >= 160) per_wave *= 1.06;
   // One head per row is bound by memory.  Where tiles of 4096 give every compute unit one workgroup, tiles of 2048 give it two, which
@@ -179,8 +177,9 @@ inline int heads_per_part(int group, int g_shift) {
 // Sets tile_tokens, g_shift and cost.
 inline void choose_cut(Plan* pl, ScanUse use, int group, int64_t planes, int64_t max_seq_len) {
   auto n_tiles_of = [&](int tile) { return (max_seq_len + tile - 1) / tile; };
-  for (int tile = 4096; tile >= 1024; tile /= 2) {
-    if (tile > 1024 && tile >= 2 * max_seq_len) continue;
+  const int smallest = use == ScanUse::kStep ? 2048 : 1024;
+  for (int tile = 4096; tile >= smallest; tile /= 2) {
+    if (tile > smallest && tile >= 2 * max_seq_len) continue;
     // never more tiles than two per compute unit in exchange for smaller ones
     if (tile == 1024 && pl->tile_tokens != 0 && planes * n_tiles_of(2048) >= kTargetWorkgroups) break;
     for (int shift = 0; shift <= 2 && heads_per_part(group, shift) != 0; ++shift) {

@@ -174,7 +174,7 @@ __device__ __forceinline__ uint32_t row_distance(const uint32_t (&row)[Dist<METR
   }
 }
 
-// WAVES = wavefronts per workgroup (4, 8 or 16): the tile is WAVES * 256 tokens.
+// WAVES = wavefronts per workgroup (8 or 16, without the encode also 4): the tile is WAVES * 256 tokens.
 // D = head dimension: W = D / 32 words per code row.
 // Waves per SIMD that the registers of a fused workgroup of three-bit codes have to leave room for, where the compiler takes a few more
 // than that by itself: at d = 256 130 vector registers, with which a compute unit holds one workgroup of eight waves instead of two (16

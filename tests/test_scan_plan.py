@@ -14,7 +14,7 @@ def test_every_cut_divides_the_group_and_covers_the_context(heads, kv, d):
         for L in (1, 63, 1024, 1025, 4097, 32771, 200001, 1 << 20):
             for use in (P.STEP, P.TOPK, P.DISTANCES, P.STATIC):
                 c = P.cut(P.config(heads, kv, head_dim=d), batch, L, use)
-                assert c.tile in (1024, 2048, 4096) and (heads // kv) % c.parts == 0
+                assert c.tile in ((2048, 4096) if use in (P.STEP, P.STATIC) else (1024, 2048, 4096)) and (heads // kv) % c.parts == 0
                 assert (c.n_tiles - 1) * c.tile < L <= c.n_tiles * c.tile
                 assert c.scratch <= A.adamas_workspace_bytes(P.config(heads, kv, head_dim=d), batch, L, 64)
 
@@ -48,7 +48,8 @@ def test_a_workspace_for_the_largest_call_serves_the_smaller_ones(heads, kv, kw)
         assert max(need(8, L) for L in range(28800, 30721, 128)) <= need(8, 32768)
 
 
-# The shapes that the plan was measured at (see scan_cost): use, heads, KV heads, batch, context, (tile, parts) chosen
+# The shapes that the plan was measured at (see scan_cost; calls of the shorter ones run as one launch, and have these cuts where a
+# profiling call cuts them in two): use, heads, KV heads, batch, context, (tile, parts) chosen
 MEASURED = [
     (P.STEP, 32, 8, 1, 4000, (2048, 4)), (P.STEP, 32, 8, 1, 16384, (2048, 4)), (P.STEP, 32, 8, 1, 20000, (2048, 2)),
     (P.STEP, 32, 8, 1, 24576, (2048, 2)), (P.STEP, 32, 8, 1, 32768, (4096, 4)), (P.STEP, 32, 8, 1, 32771, (4096, 2)),
@@ -92,6 +93,8 @@ def test_the_launcher_takes_only_cuts_that_have_a_kernel():
     for fused in (False, True):
         for heads, tile in [(0, 2048), (9, 2048), (-1, 4096), (16, 1024), (1, 0), (4, 512), (8, 8192)]:
             assert scan(fused, heads, tile, 1 | 1 << 32, 1, None, params) is False, (fused, heads, tile)
+    for heads in range(1, 9):           # the step's smallest tiles are of 2048 tokens
+        assert scan(True, heads, 1024, 1 | 1 << 32, 1, None, params) is False, heads
 
 
 @pytest.mark.parametrize("heads,k,d,parts", [
