@@ -17,3 +17,10 @@ def oracle():
     import oracle as _oracle
     _oracle.build()
     return _oracle
+
+
+@pytest.fixture(params=[0, 32768], ids=["", "two kernels"])
+def bound(request):
+    """max_seq_len of the calls where it is more than the longest sequence.  At 0 a short context runs as one launch; from 32768 on
+    every call runs as scan and select kernels, whatever its lengths (test_one_launch.py)."""
+    return request.param

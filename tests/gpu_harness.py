@@ -10,6 +10,21 @@ import paper_2510_18413_amd as A
 SM_SCALE = 1.0 / np.sqrt(128.0)
 ATTN_TOL = 2e-3   # max relative error of the attention output against the oracle
 
+POISON = 0xA5
+
+
+def two_kernels(workspace) -> bool:
+    """Whether calls since the workspace was poisoned ran as scan and select kernels, which hand distances over in it (sequences that
+    are all empty aside); one launch has no scratch."""
+    return bool((workspace != POISON).any())
+
+
+def page_table(table, page, max_len) -> torch.Tensor:
+    """The table on the device, with columns for max_len tokens."""
+    wide = np.full((len(table), max(table.shape[1], -(-max_len // page))), -1, dtype=np.int32)
+    wide[:, :table.shape[1]] = table
+    return torch.from_numpy(wide).cuda()
+
 
 def dev_bf16(a: np.ndarray) -> torch.Tensor:
     return torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).view(torch.bfloat16).cuda()
@@ -26,8 +41,8 @@ def host_dist(t: torch.Tensor) -> np.ndarray:
 class DeviceCase:
     """Device copies of a DecodeCase plus config, workspace and output buffers."""
 
-    def __init__(self, case, k, encode=True, variant=0, code_bits=0, thresholds=None):
-        self.case, self.k = case, k
+    def __init__(self, case, k, encode=True, variant=0, code_bits=0, thresholds=None, bound=0):
+        self.case, self.k, self.bound = case, k, bound
         self.thresholds = case.thresholds if thresholds is None else thresholds
         self.head_dim = int(case.q.shape[-1])
         self.cfg = A.Config.make(case.Hq, case.Hkv, case.pool_tokens, thr_k=self.thresholds,
@@ -39,13 +54,13 @@ class DeviceCase:
         self.v_new = None if case.v_new is None else dev_bf16(case.v_new)
         self.seq_start = torch.from_numpy(case.seq_start).cuda()
         self.seq_len = torch.from_numpy(case.seq_len).cuda()
-        self.max_len = max(case.max_seq_len, 1)
+        self.max_len = max(case.max_seq_len, 1, bound)
         self.codes = torch.zeros(case.Hkv, case.pool_tokens, self.cfg.code_row_bytes,
                                  dtype=torch.uint8, device="cuda")
         nbytes = A.adamas_workspace_bytes(self.cfg, case.B, self.max_len, k)
         assert nbytes > 0
         # poison the workspace: the library must not rely on its contents
-        self.workspace = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        self.workspace = torch.full((nbytes,), POISON, dtype=torch.uint8, device="cuda")
         self.out = torch.full((case.B, case.Hq, self.head_dim), float("nan"), device="cuda")
         self.idx = torch.full((case.B, case.Hq, k), -7, dtype=torch.int32, device="cuda")
         if encode:
@@ -57,6 +72,8 @@ class DeviceCase:
                              k_new=self.k_new, v_new=self.v_new,
                              idx_out=self.idx if with_idx else None)
         torch.cuda.synchronize()
+        if self.bound and self.case.max_seq_len > 0:
+            assert two_kernels(self.workspace), "ran as one launch"
         return self.out.cpu().numpy(), self.idx.cpu().numpy()
 
 

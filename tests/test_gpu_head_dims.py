@@ -24,18 +24,18 @@ def H():
     return gpu_harness
 
 
-def run_all_stages(H, oracle, hd, bits, variant, seed, B, Hq, Hkv, lens, k, append):
+def run_all_stages(H, oracle, hd, bits, variant, seed, B, Hq, Hkv, lens, k, append, bound=0):
     import paper_2510_18413_amd as A
     G = Hq // Hkv
     thr = THR[bits]
     hadamard = not (variant & A.VARIANT_NO_HADAMARD)
     squared = bool(variant & A.VARIANT_L2)
     print("head_dim", hd, "bits", bits, "variant", variant, "B/Hq/Hkv", B, Hq, Hkv, "lens", lens,
-          "k", k, "append", append, flush=True)
+          "k", k, "append", append, "bound", bound, flush=True)
     case = synth.make_case("hd", seed, B, Hq, Hkv, lens, [0],
                            lambda b, L, h, rng: rng.choice(L, (G, min(1, L // G)), replace=False),
                            append=append, head_dim=hd)
-    d = H.DeviceCase(case, k, variant=variant, code_bits=0 if bits == 2 else bits, thresholds=thr)
+    d = H.DeviceCase(case, k, variant=variant, code_bits=0 if bits == 2 else bits, thresholds=thr, bound=bound)
     row_bytes = hd // 8 * bits
     assert d.codes.shape[-1] == row_bytes
     with oracle.head_dim(hd):
@@ -63,16 +63,20 @@ def run_all_stages(H, oracle, hd, bits, variant, seed, B, Hq, Hkv, lens, k, appe
     if append:
         assert np.array_equal(d.codes.cpu().numpy(), rows), "appended code rows"
         assert np.array_equal(H.host_u16(d.K), K) and np.array_equal(H.host_u16(d.V), V)
-    dist = torch.full((B, Hq, d.max_len), 0xFFFF, dtype=torch.uint16, device="cuda")
-    idx2 = torch.full((B, Hq, k), -7, dtype=torch.int32, device="cuda")
-    A.adamas_select_topk(d.cfg, qcodes, d.codes, d.seq_start, d.seq_len, k, idx2, d.max_len,
-                         d.workspace, dist_out=dist)
-    torch.cuda.synchronize()
-    got = H.host_dist(dist)
-    for b in range(B):
-        L = int(case.seq_len[b])
-        assert np.array_equal(got[b, :, :L], ref_dist[b, :, :L]), "distances"
-    assert np.array_equal(idx2.cpu().numpy(), ref_idx), "stand-alone top-k"
+    # (top-k runs as two kernels, on tiles of 1024 tokens, from 10240 tokens on already)
+    for max_len in sorted({d.max_len, max([10240] + lens) if bound else d.max_len}):
+        d.workspace.fill_(H.POISON)
+        dist = torch.full((B, Hq, max_len), 0xFFFF, dtype=torch.uint16, device="cuda")
+        idx2 = torch.full((B, Hq, k), -7, dtype=torch.int32, device="cuda")
+        A.adamas_select_topk(d.cfg, qcodes, d.codes, d.seq_start, d.seq_len, k, idx2, max_len,
+                             d.workspace, dist_out=dist)
+        torch.cuda.synchronize()
+        assert not bound or H.two_kernels(d.workspace)
+        got = H.host_dist(dist)
+        for b in range(B):
+            L = int(case.seq_len[b])
+            assert np.array_equal(got[b, :, :L], ref_dist[b, :, :L]), "distances"
+        assert np.array_equal(idx2.cpu().numpy(), ref_idx), "stand-alone top-k"
 
 
 SHAPES = [
@@ -85,20 +89,20 @@ SHAPES = [
 
 @pytest.mark.parametrize("hd", [64, 256, 96, 160, 192])
 @pytest.mark.parametrize("bits,variant", [(2, 2), (2, 3), (1, 0), (3, 0), (3, 1)])
-def test_head_dim_with_every_switch(H, oracle, hd, bits, variant):
+def test_head_dim_with_every_switch(H, oracle, bound, hd, bits, variant):
     for i, (B, Hq, Hkv, lens, k, append) in enumerate(SHAPES):
         run_all_stages(H, oracle, hd, bits, variant, 3000 + 10 * hd + 3 * bits + variant + i,
-                       B, Hq, Hkv, lens, k, append)
+                       B, Hq, Hkv, lens, k, append, bound)
 
 
 @pytest.mark.parametrize("hd", [96, 160, 192])
-def test_head_dims_two_to_the_n_times_12_and_20(H, oracle, hd):
+def test_head_dims_two_to_the_n_times_12_and_20(H, oracle, bound, hd):
     """The method itself (Hadamard transform H_{2^n} (x) H_m with Paley's H_12 / H_20, 2-bit
     codes, Eq. 6) at d = 96, 160, 192: every stage against the oracle, several shapes."""
     for i, (B, Hq, Hkv, lens, k, append) in enumerate(SHAPES + [(1, 4, 4, [20000], 256, True),
                                                                  (2, 6, 2, [1, 700], 16, False)]):
-        run_all_stages(H, oracle, hd, 2, 0, 5000 + 10 * hd + i, B, Hq, Hkv, lens, k, append)
-    run_all_stages(H, oracle, hd, 2, 1, 5900 + hd, 2, 4, 2, [3000, 129], 64, True)   # without the transform
+        run_all_stages(H, oracle, hd, 2, 0, 5000 + 10 * hd + i, B, Hq, Hkv, lens, k, append, bound)
+    run_all_stages(H, oracle, hd, 2, 1, 5900 + hd, 2, 4, 2, [3000, 129], 64, True, bound)   # without the transform
 
 
 @pytest.mark.parametrize("hd", [96, 160, 192])
@@ -128,13 +132,13 @@ def test_head_dims_two_to_the_n_times_m_values_on_thresholds(H, oracle, hd):
         assert np.array_equal(codes.cpu().numpy(), rows), v
 
 
-def test_group_of_eight_at_head_dim_256(H, oracle):
-    run_all_stages(H, oracle, 256, 2, 0, 3900, 1, 16, 2, [6000], 200, True)
+def test_group_of_eight_at_head_dim_256(H, oracle, bound):
+    run_all_stages(H, oracle, 256, 2, 0, 3900, 1, 16, 2, [6000], 200, True, bound)
 
 
 @pytest.mark.parametrize("hd", [64, 256, 96, 160, 192])
 @pytest.mark.parametrize("bits,squared", [(1, False), (3, False), (2, True), (2, False)])
-def test_head_dim_largest_distance(H, oracle, hd, bits, squared):
+def test_head_dim_largest_distance(H, oracle, bound, hd, bits, squared):
     """Lowest against highest code in every coefficient: the largest distance of the metric."""
     import paper_2510_18413_amd as A
     case = synth.make_case("far", 3950, 1, 1, 1, [2000], [0],
@@ -144,7 +148,7 @@ def test_head_dim_largest_distance(H, oracle, hd, bits, squared):
     case.q[:] = 0
     case.q[0, 0, 0] = int(synth.f32_to_bf16_bits(np.float32([-64.0]))[0])   # every coefficient -64
     d = H.DeviceCase(case, 16, variant=A.VARIANT_L2 if squared else 0,
-                     code_bits=0 if bits == 2 else bits, thresholds=THR[bits])
+                     code_bits=0 if bits == 2 else bits, thresholds=THR[bits], bound=bound)
     qcodes = torch.zeros(1, 1, hd // 8 * bits, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(d.cfg, d.q, qcodes)
     dist = torch.zeros(1, 1, 2000, dtype=torch.uint16, device="cuda")

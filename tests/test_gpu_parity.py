@@ -195,10 +195,10 @@ def test_encode_extreme_magnitudes(H, oracle):
     (1, 8, 1, [9000], 100),          # group 8
     (1, 2, 2, [70000], 1024),        # 18 segments -> longer segments, several passes
 ])
-def test_distance_and_topk_bit_exact(H, oracle, B, Hq, Hkv, lens, k):
+def test_distance_and_topk_bit_exact(H, oracle, bound, B, Hq, Hkv, lens, k):
     import paper_2510_18413_amd as A
     case = small_case(200 + Hq + B, B, Hq, Hkv, lens)
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     qcodes = torch.zeros(B, Hq, 32, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(d.cfg, d.q, qcodes)
     dist = torch.full((B, Hq, d.max_len), 0xFFFF, dtype=torch.uint16, device="cuda")
@@ -217,7 +217,7 @@ def test_distance_and_topk_bit_exact(H, oracle, B, Hq, Hkv, lens, k):
     assert np.array_equal(d.idx.cpu().numpy(), ref["idx"])
 
 
-def test_topk_ties_everywhere(H, oracle):
+def test_topk_ties_everywhere(H, oracle, bound):
     """All keys identical: every distance equal, so the rule 'lowest position first' decides
     everything; then two distance levels with the boundary inside the second."""
     import paper_2510_18413_amd as A
@@ -226,7 +226,7 @@ def test_topk_ties_everywhere(H, oracle):
     case.K[0, 4500:4600] = synth.f32_to_bf16_bits(
         synth.bf16_bits_to_f32(case.q[0, 0]))                  # 100 near-exact matches of head 0
     for k in (1, 37, 100, 101, 4096):
-        d = H.DeviceCase(case, k)
+        d = H.DeviceCase(case, k, bound=bound)
         qcodes = torch.zeros(1, 2, 32, dtype=torch.uint8, device="cuda")
         A.adamas_encode_query(d.cfg, d.q, qcodes)
         A.adamas_select_topk(d.cfg, qcodes, d.codes, d.seq_start, d.seq_len, k, d.idx, d.max_len,
@@ -236,11 +236,11 @@ def test_topk_ties_everywhere(H, oracle):
         assert np.array_equal(d.idx.cpu().numpy(), ref["idx"]), k
 
 
-def test_topk_k_at_least_length_and_empty(H, oracle):
+def test_topk_k_at_least_length_and_empty(H, oracle, bound):
     import paper_2510_18413_amd as A
     case = small_case(302, 3, 2, 2, [0, 5, 300], needles=0)
     k = 300
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     qcodes = torch.zeros(3, 2, 32, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(d.cfg, d.q, qcodes)
     A.adamas_select_topk(d.cfg, qcodes, d.codes, d.seq_start, d.seq_len, k, d.idx, d.max_len,
@@ -365,9 +365,9 @@ def test_stream_read_probe_touches_nothing(H, oracle):
     (1, 8, 1, [20000], 4096, True),
     (1, 2, 2, [70000], 1024, False),
 ])
-def test_decode_step_matches_oracle(H, oracle, B, Hq, Hkv, lens, k, append):
+def test_decode_step_matches_oracle(H, oracle, bound, B, Hq, Hkv, lens, k, append):
     case = small_case(500 + B + Hq, B, Hq, Hkv, lens, append=append)
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     out, idx = d.decode_step()
     ref = H.oracle_step(case, k, want_dist=False)
     assert np.array_equal(idx, ref["idx"])
@@ -380,12 +380,12 @@ def test_decode_step_matches_oracle(H, oracle, B, Hq, Hkv, lens, k, append):
         assert np.array_equal(H.host_u16(d.V), ref["V"])
         assert np.array_equal(d.codes.cpu().numpy(), ref["rows"])
     # same call without the index output, on a fresh poisoned workspace: same attention result
-    d2 = H.DeviceCase(case, k)
+    d2 = H.DeviceCase(case, k, bound=bound)
     out2, _ = d2.decode_step(with_idx=False)
     assert np.array_equal(out, out2)
 
 
-def test_decode_step_prologue_on_vectors_within_rounding_of_a_threshold(H, oracle):
+def test_decode_step_prologue_on_vectors_within_rounding_of_a_threshold(H, oracle, bound):
     """The decode step encodes its queries and the appended keys in its own prologue, one vector
     per wave (exact sums in double precision).  Queries and new keys here are the vectors of near_threshold_cases, some of whose coefficients lie within a
     rounding of a threshold (plain single precision misjudges them).  The appended code rows must
@@ -402,7 +402,7 @@ def test_decode_step_prologue_on_vectors_within_rounding_of_a_threshold(H, oracl
         case.k_new = np.ascontiguousarray(bits[kn].reshape(B, Hkv, 128))
         case.q = np.ascontiguousarray(bits[qs].reshape(B, Hq, 128))
         case.thresholds = thr
-        d = H.DeviceCase(case, 48)
+        d = H.DeviceCase(case, 48, bound=bound)
         out, idx = d.decode_step()
         ref = H.oracle_step(case, 48, want_dist=False)
         assert np.array_equal(d.codes.cpu().numpy(), ref["rows"]), trial
@@ -410,9 +410,9 @@ def test_decode_step_prologue_on_vectors_within_rounding_of_a_threshold(H, oracl
         assert H.attn_rel_err(out, ref["out"]) <= H.ATTN_TOL
 
 
-def test_decode_step_repeatable_and_workspace_reusable(H, oracle):
+def test_decode_step_repeatable_and_workspace_reusable(H, oracle, bound):
     case = small_case(601, 2, 8, 2, [3000, 9000])
-    d = H.DeviceCase(case, 128)
+    d = H.DeviceCase(case, 128, bound=bound)
     first = d.decode_step()
     for _ in range(3):
         again = d.decode_step()
@@ -515,19 +515,19 @@ def test_plain_c_client_of_the_abi(H, oracle):
     assert "C ABI client: OK" in r.stdout
 
 
-def test_appended_token_is_a_candidate(H, oracle):
+def test_appended_token_is_a_candidate(H, oracle, bound):
     case = small_case(602, 1, 2, 2, [4097], append=True)     # new token alone in the 2nd segment
     case.q[0, 0] = case.k_new[0, 0]
-    d = H.DeviceCase(case, 8)
+    d = H.DeviceCase(case, 8, bound=bound)
     out, idx = d.decode_step()
     assert 4096 in idx[0, 0].tolist()
     ref = H.oracle_step(case, 8, want_dist=False)
     assert np.array_equal(idx, ref["idx"]) and H.attn_rel_err(out, ref["out"]) <= H.ATTN_TOL
 
 
-def test_invalid_device_lengths_are_treated_as_empty(H, oracle):
+def test_invalid_device_lengths_are_treated_as_empty(H, oracle, bound):
     case = small_case(603, 2, 2, 2, [500, 600], needles=0)
-    d = H.DeviceCase(case, 16)
+    d = H.DeviceCase(case, 16, bound=bound)
     d.seq_len = torch.tensor([500, 10 ** 6], dtype=torch.int32, device="cuda")   # beyond max/pool
     out, idx = d.decode_step()
     assert np.all(idx[1] == -1) and np.all(out[1] == 0)
@@ -545,12 +545,12 @@ def test_invalid_device_lengths_are_treated_as_empty(H, oracle):
     (3, 4, 4, [0, 5000, 9000], 256, False),
     (1, 8, 1, [20000], 1024, True),
 ])
-def test_variant_decode_step_matches_oracle(H, oracle, variant, B, Hq, Hkv, lens, k, append):
+def test_variant_decode_step_matches_oracle(H, oracle, bound, variant, B, Hq, Hkv, lens, k, append):
     """Every stage of the step under the ablation switches: code bytes, distances (through
     adamas_select_topk's optional output), indices bit for bit; attention within tolerance."""
     import paper_2510_18413_amd as A
     case = small_case(800 + variant + Hq, B, Hq, Hkv, lens, append=append)
-    d = H.DeviceCase(case, k, variant=variant)
+    d = H.DeviceCase(case, k, variant=variant, bound=bound)
     hadamard = not (variant & A.VARIANT_NO_HADAMARD)
     _, rows0 = oracle.encode(case.K, case.thresholds, hadamard=hadamard)
     assert np.array_equal(d.codes.cpu().numpy(), rows0)                   # bulk key encode
@@ -579,7 +579,7 @@ def test_variant_decode_step_matches_oracle(H, oracle, variant, B, Hq, Hkv, lens
     assert np.array_equal(idx2.cpu().numpy(), ref["idx"])
 
 
-def test_variant_l2_extreme_distances(H, oracle):
+def test_variant_l2_extreme_distances(H, oracle, bound):
     """All-0 against all-3 codes: 1152, the largest squared distance, and ties everywhere."""
     import paper_2510_18413_amd as A
     case = small_case(850, 1, 1, 1, [3000], needles=0)
@@ -587,7 +587,7 @@ def test_variant_l2_extreme_distances(H, oracle):
     case.K[0, :, 0] = int(synth.f32_to_bf16_bits(np.float32([64.0]))[0])    # every coefficient = +64
     case.q[:] = 0
     case.q[0, 0, 0] = int(synth.f32_to_bf16_bits(np.float32([-64.0]))[0])   # every coefficient = -64
-    d = H.DeviceCase(case, 32, variant=A.VARIANT_L2)
+    d = H.DeviceCase(case, 32, variant=A.VARIANT_L2, bound=bound)
     out, idx = d.decode_step()
     ref = H.oracle_step(case, 32, want_dist=True, variant=A.VARIANT_L2)
     assert int(ref["dist"].max()) == 1152
@@ -628,14 +628,14 @@ BITS_THR = {1: (0.0,), 3: (-1.5, -1.0, -0.5, 0.0, 0.5, 1.0, 1.5)}
     (1, 8, 1, [20000], 1024, True, 0),
     (1, 6, 2, [2500], 32, True, 1),
 ])
-def test_code_bits_decode_step_matches_oracle(H, oracle, bits, B, Hq, Hkv, lens, k, append, variant):
+def test_code_bits_decode_step_matches_oracle(H, oracle, bound, bits, B, Hq, Hkv, lens, k, append, variant):
     """1-bit and 3-bit codes through every stage: code bytes of keys and queries, distances,
     indices bit for bit; attention within tolerance; appended rows in the cache."""
     import paper_2510_18413_amd as A
     thr = BITS_THR[bits]
     hadamard = not (variant & A.VARIANT_NO_HADAMARD)
     case = small_case(1000 + 10 * bits + Hq, B, Hq, Hkv, lens, append=append)
-    d = H.DeviceCase(case, k, variant=variant, code_bits=bits, thresholds=thr)
+    d = H.DeviceCase(case, k, variant=variant, code_bits=bits, thresholds=thr, bound=bound)
     assert d.codes.shape[-1] == 16 * bits
     _, rows0 = oracle.encode_bits(case.K, thr, bits, hadamard=hadamard)
     assert np.array_equal(d.codes.cpu().numpy(), rows0)
@@ -668,7 +668,7 @@ def test_code_bits_decode_step_matches_oracle(H, oracle, bits, B, Hq, Hkv, lens,
 
 
 @pytest.mark.parametrize("bits", [1, 3])
-def test_code_bits_extreme_distances(H, oracle, bits):
+def test_code_bits_extreme_distances(H, oracle, bound, bits):
     """Lowest against highest code everywhere: the largest distance, (2^bits - 1) * 128."""
     import paper_2510_18413_amd as A
     case = small_case(1050, 1, 1, 1, [2000], needles=0)
@@ -676,7 +676,7 @@ def test_code_bits_extreme_distances(H, oracle, bits):
     case.K[0, :, 0] = int(synth.f32_to_bf16_bits(np.float32([64.0]))[0])
     case.q[:] = 0
     case.q[0, 0, 0] = int(synth.f32_to_bf16_bits(np.float32([-64.0]))[0])
-    d = H.DeviceCase(case, 16, code_bits=bits, thresholds=BITS_THR[bits])
+    d = H.DeviceCase(case, 16, code_bits=bits, thresholds=BITS_THR[bits], bound=bound)
     qcodes = torch.zeros(1, 1, 16 * bits, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(d.cfg, d.q, qcodes)
     dist = torch.zeros(1, 1, 2000, dtype=torch.uint16, device="cuda")
@@ -687,7 +687,7 @@ def test_code_bits_extreme_distances(H, oracle, bits):
     assert idx[0, 0].tolist() == list(range(16))
 
 
-def test_code_bits_with_paged_cache(H, oracle):
+def test_code_bits_with_paged_cache(H, oracle, bound):
     """3-bit codes on a paged cache: the two switches compose."""
     import paper_2510_18413_amd as A
     thr = BITS_THR[3]
@@ -697,11 +697,12 @@ def test_code_bits_with_paged_cache(H, oracle):
     Kd, Vd, qd = H.dev_bf16(pc.K), H.dev_bf16(pc.V), H.dev_bf16(case.q)
     codes = torch.zeros(2, pc.pool_tokens, 48, dtype=torch.uint8, device="cuda")
     A.adamas_encode_keys(cfg, Kd, codes, 0, pc.pool_tokens)
-    ws = torch.empty(A.adamas_workspace_bytes(cfg, 2, 3000, 64), dtype=torch.uint8, device="cuda")
+    max_len = max(3000, bound)
+    ws = torch.empty(A.adamas_workspace_bytes(cfg, 2, max_len, 64), dtype=torch.uint8, device="cuda")
     out = torch.zeros(2, 4, 128, device="cuda")
     idx = torch.zeros(2, 4, 64, dtype=torch.int32, device="cuda")
-    A.adamas_decode_step_paged(cfg, qd, Kd, Vd, codes, torch.from_numpy(pc.page_table).cuda(), 128,
-                               torch.from_numpy(case.seq_len).cuda(), 64, out, 3000, ws,
+    A.adamas_decode_step_paged(cfg, qd, Kd, Vd, codes, H.page_table(pc.page_table, 128, max_len), 128,
+                               torch.from_numpy(case.seq_len).cuda(), 64, out, max_len, ws,
                                k_new=H.dev_bf16(case.k_new), v_new=H.dev_bf16(case.v_new),
                                idx_out=idx)
     torch.cuda.synchronize()
@@ -725,7 +726,7 @@ def test_code_bits_with_paged_cache(H, oracle):
     (1, 8, 1, [20000], 1024, 1024, True),
     (2, 6, 2, [70000, 129], 512, 128, False),
 ])
-def test_paged_decode_step_matches_oracle(H, oracle, variant, B, Hq, Hkv, lens, k, page, append):
+def test_paged_decode_step_matches_oracle(H, oracle, bound, variant, B, Hq, Hkv, lens, k, page, append):
     """The step on a cache scattered over randomly placed pages: indices (token positions) bit
     for bit, attention within tolerance, and the appended row in the right physical page while
     every other pool row stays as it was."""
@@ -739,9 +740,9 @@ def test_paged_decode_step_matches_oracle(H, oracle, variant, B, Hq, Hkv, lens, 
     vnd = None if case.v_new is None else H.dev_bf16(case.v_new)
     codes = torch.zeros(Hkv, pc.pool_tokens, 32, dtype=torch.uint8, device="cuda")
     A.adamas_encode_keys(cfg, Kd, codes, 0, pc.pool_tokens)
-    table = torch.from_numpy(pc.page_table).cuda()
     seq_len = torch.from_numpy(case.seq_len).cuda()
-    max_len = max(case.max_seq_len, 1)
+    max_len = max(case.max_seq_len, 1, bound)
+    table = H.page_table(pc.page_table, page, max_len)
     ws = torch.full((A.adamas_workspace_bytes(cfg, B, max_len, k),), 0xA5, dtype=torch.uint8,
                     device="cuda")
     out = torch.full((B, Hq, 128), float("nan"), device="cuda")
@@ -749,6 +750,7 @@ def test_paged_decode_step_matches_oracle(H, oracle, variant, B, Hq, Hkv, lens, 
     A.adamas_decode_step_paged(cfg, qd, Kd, Vd, codes, table, page, seq_len, k, out, max_len, ws,
                                k_new=knd, v_new=vnd, idx_out=idx)
     torch.cuda.synchronize()
+    assert not bound or H.two_kernels(ws)
     Kr, Vr = pc.K.copy(), pc.V.copy()
     _, rows = oracle.encode(Kr, case.thresholds, hadamard=hadamard)
     ref_out, ref_idx = oracle.decode_step_paged(
@@ -761,7 +763,7 @@ def test_paged_decode_step_matches_oracle(H, oracle, variant, B, Hq, Hkv, lens, 
     assert np.array_equal(codes.cpu().numpy(), rows)
 
 
-def test_paged_step_clamps_page_numbers_outside_the_pool(H, oracle):
+def test_paged_step_clamps_page_numbers_outside_the_pool(H, oracle, bound):
     """A page table with entries beyond the pool must not fault: rows come from clamped pages."""
     import paper_2510_18413_amd as A
     case = small_case(950, 1, 2, 2, [1000], needles=0)
@@ -772,17 +774,18 @@ def test_paged_step_clamps_page_numbers_outside_the_pool(H, oracle):
     A.adamas_encode_keys(cfg, Kd, codes, 0, pc.pool_tokens)
     bad = pc.page_table.copy()
     bad[0, 3], bad[0, 7] = 10 ** 6, -5
-    ws = torch.empty(A.adamas_workspace_bytes(cfg, 1, 1000, 32), dtype=torch.uint8, device="cuda")
+    max_len = max(1000, bound)
+    ws = torch.empty(A.adamas_workspace_bytes(cfg, 1, max_len, 32), dtype=torch.uint8, device="cuda")
     out = torch.zeros(1, 2, 128, device="cuda")
     idx = torch.zeros(1, 2, 32, dtype=torch.int32, device="cuda")
-    A.adamas_decode_step_paged(cfg, qd, Kd, Vd, codes, torch.from_numpy(bad).cuda(), 64,
-                               torch.from_numpy(case.seq_len).cuda(), 32, out, 1000, ws, idx_out=idx)
+    A.adamas_decode_step_paged(cfg, qd, Kd, Vd, codes, H.page_table(bad, 64, max_len), 64,
+                               torch.from_numpy(case.seq_len).cuda(), 32, out, max_len, ws, idx_out=idx)
     torch.cuda.synchronize()
     got = idx.cpu().numpy()
     assert np.all((got >= 0) & (got < 1000)) and np.all(np.isfinite(out.cpu().numpy()))
 
 
-def test_decode_step_random_shapes(H, oracle):
+def test_decode_step_random_shapes(H, oracle, bound):
     """Seeded sweep over batch, group size, lengths, budgets, thresholds, scale and append:
     every case against the oracle."""
     import paper_2510_18413_amd as A
@@ -804,7 +807,7 @@ def test_decode_step_random_shapes(H, oracle):
         thr = [(-1.0, 0.0, 1.0), (-0.3, 0.4, 2.5), (-2.0, -1.0, -0.5)][case_no % 3]
         case.thresholds = thr
         scale = [0.0, 0.05, 0.2][case_no % 3]
-        d = H.DeviceCase(case, k)
+        d = H.DeviceCase(case, k, bound=bound)
         d.cfg = A.Config.make(case.Hq, case.Hkv, case.pool_tokens, thr_k=thr, sm_scale=scale)
         A.adamas_encode_keys(d.cfg, d.K, d.codes, 0, case.pool_tokens)
         out, idx = d.decode_step()
@@ -879,10 +882,10 @@ def test_head_dim_values_on_thresholds(H, oracle, hd):
     (256, 1, 6, 2, [9000], 100),           # group 3
     (256, 1, 2, 2, [70000], 1024),
 ])
-def test_head_dim_distance_and_topk_bit_exact(H, oracle, hd, B, Hq, Hkv, lens, k):
+def test_head_dim_distance_and_topk_bit_exact(H, oracle, bound, hd, B, Hq, Hkv, lens, k):
     import paper_2510_18413_amd as A
     case = small_case(920 + hd + Hq + B, B, Hq, Hkv, lens, head_dim=hd)
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     qcodes = torch.zeros(B, Hq, hd // 4, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(d.cfg, d.q, qcodes)
     dist = torch.full((B, Hq, d.max_len), 0xFFFF, dtype=torch.uint16, device="cuda")
@@ -902,7 +905,7 @@ def test_head_dim_distance_and_topk_bit_exact(H, oracle, hd, B, Hq, Hkv, lens, k
 
 
 @pytest.mark.parametrize("hd", [64, 256])
-def test_head_dim_extreme_distances(H, oracle, hd):
+def test_head_dim_extreme_distances(H, oracle, bound, hd):
     """All codes 3 against all codes 0: the largest distance 3d must survive the 16-bit
     distance, the histogram bins and the threshold search."""
     import paper_2510_18413_amd as A
@@ -917,7 +920,7 @@ def test_head_dim_extreme_distances(H, oracle, hd):
     case.K[0, 2000:2100] = synth.f32_to_bf16_bits(e0)       # distance 0
     del big
     k = 2950                                                # reaches into the 3d bin
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     qcodes = torch.zeros(1, 1, hd // 4, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(d.cfg, d.q, qcodes)
     dist = torch.zeros((1, 1, d.max_len), dtype=torch.uint16, device="cuda")
@@ -943,9 +946,9 @@ def test_head_dim_extreme_distances(H, oracle, hd):
     (256, 3, 6, 2, [100, 64, 65], 128, False),
     (256, 1, 2, 2, [40000], 4096, True),
 ])
-def test_head_dim_decode_step_matches_oracle(H, oracle, hd, B, Hq, Hkv, lens, k, append):
+def test_head_dim_decode_step_matches_oracle(H, oracle, bound, hd, B, Hq, Hkv, lens, k, append):
     case = small_case(960 + hd + B + Hq, B, Hq, Hkv, lens, append=append, head_dim=hd)
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     out, idx = d.decode_step()
     ref = H.oracle_step(case, k, want_dist=False)
     assert out.shape[-1] == hd
@@ -961,13 +964,13 @@ def test_head_dim_decode_step_matches_oracle(H, oracle, hd, B, Hq, Hkv, lens, k,
 
 
 @pytest.mark.parametrize("hd", [64, 256])
-def test_head_dim_staged_entry_points_and_full_attention(H, oracle, hd):
+def test_head_dim_staged_entry_points_and_full_attention(H, oracle, bound, hd):
     """select_topk -> sparse_attn (the stand-alone kernels) reproduce the fused step, and the
     dense comparison kernel matches the oracle's full attention, at d = 64 / 256."""
     import paper_2510_18413_amd as A
     B, Hq, Hkv, lens, k = 2, 4, 2, [5000, 700], 96
     case = small_case(980 + hd, B, Hq, Hkv, lens, head_dim=hd)
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     out, idx = d.decode_step()
     qcodes = torch.zeros(B, Hq, hd // 4, dtype=torch.uint8, device="cuda")
     A.adamas_encode_query(d.cfg, d.q, qcodes)
@@ -1001,7 +1004,7 @@ def test_head_dim_staged_entry_points_and_full_attention(H, oracle, hd):
     (256, 2, 8, 2, [4097, 333], 128, 256, True),
     (256, 1, 3, 1, [20000], 1024, 1024, False),        # group 3
 ])
-def test_head_dim_paged_decode_step_matches_oracle(H, oracle, hd, B, Hq, Hkv, lens, k, page, append):
+def test_head_dim_paged_decode_step_matches_oracle(H, oracle, bound, hd, B, Hq, Hkv, lens, k, page, append):
     """The paged step at d = 64 / 256 against the oracle's paged step."""
     import paper_2510_18413_amd as A
     case = small_case(990 + hd + Hq, B, Hq, Hkv, lens, append=append, head_dim=hd)
@@ -1012,9 +1015,9 @@ def test_head_dim_paged_decode_step_matches_oracle(H, oracle, hd, B, Hq, Hkv, le
     vnd = None if case.v_new is None else H.dev_bf16(case.v_new)
     codes = torch.zeros(Hkv, pc.pool_tokens, hd // 4, dtype=torch.uint8, device="cuda")
     A.adamas_encode_keys(cfg, Kd, codes, 0, pc.pool_tokens)
-    table = torch.from_numpy(pc.page_table).cuda()
     seq_len = torch.from_numpy(case.seq_len).cuda()
-    max_len = max(case.max_seq_len, 1)
+    max_len = max(case.max_seq_len, 1, bound)
+    table = H.page_table(pc.page_table, page, max_len)
     ws = torch.full((A.adamas_workspace_bytes(cfg, B, max_len, k),), 0xA5, dtype=torch.uint8,
                     device="cuda")
     out = torch.full((B, Hq, hd), float("nan"), device="cuda")
@@ -1022,6 +1025,7 @@ def test_head_dim_paged_decode_step_matches_oracle(H, oracle, hd, B, Hq, Hkv, le
     A.adamas_decode_step_paged(cfg, qd, Kd, Vd, codes, table, page, seq_len, k, out, max_len, ws,
                                k_new=knd, v_new=vnd, idx_out=idx)
     torch.cuda.synchronize()
+    assert not bound or H.two_kernels(ws)
     Kr, Vr = pc.K.copy(), pc.V.copy()
     with oracle.head_dim(hd):
         _, rows = oracle.encode(Kr, case.thresholds)
@@ -1035,11 +1039,11 @@ def test_head_dim_paged_decode_step_matches_oracle(H, oracle, hd, B, Hq, Hkv, le
 
 
 @pytest.mark.parametrize("hd", [64, 256])
-def test_head_dim_without_hadamard(H, oracle, hd):
+def test_head_dim_without_hadamard(H, oracle, bound, hd):
     """The no-transform ablation is a run-time switch of the same kernels: also at d = 64 / 256."""
     import paper_2510_18413_amd as A
     case = small_case(995 + hd, 2, 4, 2, [3000, 4100], append=True, head_dim=hd)
-    d = H.DeviceCase(case, 96, variant=A.VARIANT_NO_HADAMARD)
+    d = H.DeviceCase(case, 96, variant=A.VARIANT_NO_HADAMARD, bound=bound)
     out, idx = d.decode_step()
     ref = H.oracle_step(case, 96, want_dist=False, variant=A.VARIANT_NO_HADAMARD)
     assert np.array_equal(idx, ref["idx"])
@@ -1055,7 +1059,7 @@ def test_head_dims_that_are_not_built_are_refused(H, oracle):
     assert A.adamas_workspace_bytes(A.Config.make(8, 1, 1024, head_dim=256), 1, 1024, 16) > 0
 
 
-def test_generation_loop_of_appending_steps(H, oracle):
+def test_generation_loop_of_appending_steps(H, oracle, bound):
     """Six consecutive decode steps on a growing cache (one sequence crosses a scan-tile
     boundary on the way), device lengths bumped in place, one workspace, no host round trip
     between the library calls of a step: every step's selection and output against the oracle,
@@ -1064,7 +1068,7 @@ def test_generation_loop_of_appending_steps(H, oracle):
     start_len = [700, 2046]
     case = small_case(1200, B, Hq, Hkv, [n + steps for n in start_len])   # pools sized for the end
     rng = np.random.default_rng(1201)
-    d = H.DeviceCase(case, k)          # encodes the whole pool: rows beyond the lengths are ignored
+    d = H.DeviceCase(case, k, bound=bound)          # encodes the whole pool: rows beyond the lengths are ignored
     K_ref, V_ref = case.K.copy(), case.V.copy()
     with oracle.head_dim(128):
         _, rows_ref = oracle.encode(K_ref, case.thresholds)
@@ -1092,7 +1096,7 @@ def test_generation_loop_of_appending_steps(H, oracle):
 
 @pytest.mark.parametrize("hd", [128, 64, 256])
 @pytest.mark.parametrize("far_share,k", [(0.02, 200), (0.5, 64), (0.9, 1500), (0.9, 4000), (1.0, 100)])
-def test_distances_above_255_in_some_tiles(H, oracle, hd, far_share, k):
+def test_distances_above_255_in_some_tiles(H, oracle, bound, hd, far_share, k):
     """Byte-sized distances carry a ninth bit only in tiles that need one.  Rows far from the
     query (every code 3 against every code 0: distance 3 * d) are sprinkled over some tiles or
     fill most of the cache, so that the threshold distance lies below 256 in one case and above
@@ -1112,7 +1116,7 @@ def test_distances_above_255_in_some_tiles(H, oracle, hd, far_share, k):
     rows = np.flatnonzero(far)
     case.K[:, rows] = 0
     case.K[:, rows, 0] = big                   # every coefficient +64 -> code 3
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     out, idx = d.decode_step()
     ref = H.oracle_step(case, k, want_dist=True)
     if hd >= 128:
@@ -1135,7 +1139,7 @@ def test_distances_above_255_in_some_tiles(H, oracle, hd, far_share, k):
 
 
 @pytest.mark.parametrize("k", [1, 64, 300])
-def test_ragged_batch_of_every_length_up_to_257(H, oracle, k):
+def test_ragged_batch_of_every_length_up_to_257(H, oracle, bound, k):
     """257 sequences of lengths 1, 2, ..., 257 in one call (one token of each appended in the
     same step), a query group of three: indices bit for bit, attention within tolerance, the
     appended K / V / code rows in place."""
@@ -1143,7 +1147,7 @@ def test_ragged_batch_of_every_length_up_to_257(H, oracle, k):
     case = synth.make_case("ragged257", 7100 + k, 257, 6, 2, lens, [0],
                            lambda b, L, h, rng: rng.choice(L, (3, min(1, L // 3)), replace=False),
                            append=True)
-    d = H.DeviceCase(case, k)
+    d = H.DeviceCase(case, k, bound=bound)
     out, idx = d.decode_step()
     ref = H.oracle_step(case, k, want_dist=False)
     assert np.array_equal(idx, ref["idx"])

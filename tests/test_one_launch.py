@@ -4,36 +4,15 @@ batch of four of them, what a thread looks at (4, 8 or 16 tokens) and a second p
 workgroups; ties, short lists, empty sequences."""
 
 import ctypes
-import functools
-import os
 import random
-import subprocess
-import tempfile
 
 import pytest
 import torch
 
 import paper_2510_18413_amd as A
-from paper_2510_18413_amd import build as B
+from plan_query import STEP, TOPK, one_launch_lib, waves
 
-HERE = os.path.dirname(os.path.abspath(__file__))
-STEP, TOPK = 0, 1
 THR = {1: (0.0,), 2: (-1.0, 0.0, 1.0), 3: (-1.5, -1.0, -0.5, 0.0, 0.5, 1.0, 1.5)}
-
-
-@functools.lru_cache(maxsize=1)
-def _lib():
-    with tempfile.TemporaryDirectory() as tmp:
-        so = os.path.join(tmp, "one_launch_plan.so")
-        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-fPIC", "-shared", "-I", str(B.ROOT / "include"),
-                        "-I", str(B.CSRC), os.path.join(HERE, "one_launch_plan.cpp"), "-o", so], check=True)
-        lib = ctypes.CDLL(so)
-        lib.one_launch_lds.restype = ctypes.c_int64
-        return lib
-
-
-def waves(cfg, batch, L, k, use=STEP, paged=False):
-    return _lib().one_launch_waves(ctypes.byref(cfg), batch, ctypes.c_int64(L), k, use, int(paged))
 
 
 def config(heads, kv, d=128, bits=2, variant=0, pool=1 << 20):
@@ -74,7 +53,7 @@ def test_the_rule_knows_how_many_waves_the_registers_leave_room_for():
         for d in (64, 96, 128, 160, 192, 256):
             for fused, paged in ((True, False), (True, True), (False, False)):
                 k = R.kernels()["one_launch_kernel<8, %s, %d, %s, %d>" % (str(fused).lower(), metric, str(paged).lower(), d)]
-                assert _lib().one_launch_waves_per_simd(int(fused), metric, d) <= R.waves_per_simd(k), (metric, d, fused, k)
+                assert one_launch_lib().one_launch_waves_per_simd(int(fused), metric, d) <= R.waves_per_simd(k), (metric, d, fused, k)
 
 
 def test_a_launch_never_asks_for_more_lds_than_it_may_have_or_a_grid_that_does_not_exist():
@@ -87,10 +66,23 @@ def test_a_launch_never_asks_for_more_lds_than_it_may_have_or_a_grid_that_does_n
                         for use, paged in ((STEP, False), (STEP, True), (TOPK, False)):
                             w = waves(c, batch, L, k, use, paged)
                             assert w in (0, 4, 8, 16)
-                            assert w == 0 or _lib().one_launch_lds(ctypes.byref(c), w, ctypes.c_int64(L), k, use, int(paged)) <= 65536
+                            assert w == 0 or one_launch_lib().one_launch_lds(ctypes.byref(c), w, ctypes.c_int64(L), k, use, int(paged)) <= 65536
     assert waves(config(64, 64), 65535, 100, 10) == 0                    # 4 Mi planes
     assert waves(config(32768, 32768), 16, 100, 10) == 0                 # a plane times the KV heads beyond 2^32
     assert waves(config(64, 64), 8191, 100, 10) == 4
+
+
+def test_no_call_of_32768_tokens_runs_as_one_launch():
+    """What tests of the two kernels give as max_seq_len when their sequences are shorter."""
+    for d in (64, 96, 128, 160, 192, 256):
+        for bits, variant in ((1, 0), (2, 0), (2, A.VARIANT_L2), (3, 0)):
+            for heads, kv in ((1, 1), (8, 1), (32, 8), (64, 64)):
+                for batch in (1, 9, 300):
+                    for k in (1, 4096):
+                        for use, paged in ((STEP, False), (STEP, True), (TOPK, False)):
+                            assert waves(config(heads, kv, d, bits, variant), batch, 32768, k, use, paged) == 0
+                for batch, L in ((1, 10240), (3, 10240)):           # top-k of a few heads
+                    assert batch * heads > 17 or waves(config(heads, kv, d, bits, variant), batch, L, 300, TOPK) == 0
 
 
 class Case:

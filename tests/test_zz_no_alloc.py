@@ -52,13 +52,16 @@ def _case(seed, B, Hq, Hkv, lens, append):
 def test_static_scratch_step_equals_workspace_step_twice_in_a_row(oracle):
     from gpu_harness import DeviceCase, attn_rel_err, oracle_step, ATTN_TOL
     # first a large input (9 scan tiles per head, 3 select segments), then a smaller one
-    for seed, B, Hq, Hkv, lens, k, append in [(501, 2, 8, 2, [9000, 4097], 96, True),
-                                              (502, 1, 4, 4, [700], 33, False)]:
+    # (and both again with a bound from which on they run as two kernels, in the array)
+    for seed, B, Hq, Hkv, lens, k, append, bound in [(501, 2, 8, 2, [9000, 4097], 96, True, 0),
+                                                     (502, 1, 4, 4, [700], 33, False, 0),
+                                                     (503, 2, 8, 2, [9000, 4097], 96, True, 32768),
+                                                     (504, 1, 4, 4, [700], 33, False, 32768)]:
         print("static-scratch step: seed", seed, "lens", lens, "k", k, flush=True)
         case = _case(seed, B, Hq, Hkv, lens, append)
-        ref = DeviceCase(case, k)
+        ref = DeviceCase(case, k, bound=bound)
         want_out, want_idx = ref.decode_step()
-        dev = DeviceCase(case, k)           # its own pools: an append writes them
+        dev = DeviceCase(case, k, bound=bound)           # its own pools: an append writes them
         assert A.adamas_workspace_bytes(dev.cfg, B, dev.max_len, k) <= A.STATIC_SCRATCH_BYTES
         A.adamas_decode_step_static(dev.cfg, dev.q, dev.K, dev.V, dev.codes, dev.seq_start,
                                     dev.seq_len, k, dev.out, dev.max_len, k_new=dev.k_new,
