@@ -235,6 +235,14 @@ int adamas_sparse_attn(const adamas_config *cfg, const void *q, const void *K,
  * is a candidate like any other (sequences with seq_len[b] == 0 append
  * nothing).  K, V, codes are therefore read AND written.
  * out fp32 [batch][Hq][128]; idx_out int32 [batch][Hq][k] or NULL.
+ *
+ * Short contexts run as one kernel, a workgroup per query head, that leaves the
+ * workspace alone (it is checked all the same); longer ones as a scan and a
+ * select kernel.  Which one a call gets follows from cfg, batch, max_seq_len and
+ * k.  Positions and cache rows are the same either way; out is summed in another
+ * order (fp32), so it may differ in the last bits, as it may between two values of
+ * max_seq_len.  The same holds for adamas_select_topk, whose results are whole
+ * numbers.
  */
 int adamas_decode_step(const adamas_config *cfg, const void *q,
                        const void *k_new, const void *v_new, void *K, void *V,
@@ -256,7 +264,9 @@ int adamas_decode_step(const adamas_config *cfg, const void *q,
  * adamas_workspace_bytes(cfg, batch, max_seq_len, k) <=
  * ADAMAS_STATIC_SCRATCH_BYTES fits, and some larger ones, for which the call
  * cuts the scan so that it needs the least scratch (the others cut it so that
- * it takes the least time).
+ * it takes the least time).  The check is the same for contexts that run as one
+ * kernel, which needs no scratch: a call is not refused or served by the form
+ * that it happens to take.
  * All calls on one GPU share that GPU's array: two calls whose work may overlap
  * on one GPU (different streams, different threads) race; calls on one stream
  * are ordered and safe.  The first call on each device looks the array's
@@ -272,9 +282,12 @@ int adamas_decode_step_static(const adamas_config *cfg, const void *q,
                               void *stream);
 
 /*
- * Profiling hook: adamas_decode_step cut at its one internal kernel
- * boundary.  `stages` is a bit mask; ADAMAS_STAGE_ALL is exactly
- * adamas_decode_step.  ADAMAS_STAGE_SCAN runs Alg. 1 up to the distance
+ * Profiling hook: the decode step cut between its scan and select kernels.
+ * `stages` is a bit mask; ADAMAS_STAGE_ALL is exactly adamas_decode_step, one
+ * kernel for short contexts.  The other values run the two kernels whatever the
+ * context: the same positions and rows, out to the last bits where adamas_decode_step
+ * runs as two kernels itself and within the rounding of fp32 sums elsewhere.
+ * ADAMAS_STAGE_SCAN runs Alg. 1 up to the distance
  * step (query encode, append, distance scan; leaves distances and
  * histograms in the workspace, writes neither out nor idx_out).
  * ADAMAS_STAGE_SELECT_ATTN runs the top-k, gather and attention steps on
@@ -298,7 +311,8 @@ int adamas_decode_step_stages(const adamas_config *cfg, const void *q,
  * Profiling hook, for libraries built with -DADAMAS_PHASE_TRACE only (an
  * ordinary build returns ADAMAS_ERR_UNSUPPORTED and has no stamping code in
  * its kernels).  After this call every workgroup of the two kernels of
- * adamas_decode_step / _stages / _paged leaves a record of ADAMAS_TRACE_SLOTS
+ * adamas_decode_step / _stages / _paged (which run as two whatever the context
+ * while stamps are on) leaves a record of ADAMAS_TRACE_SLOTS
  * uint64 in scan_records / select_records (device memory, n_records records
  * each, indexed by the workgroup's linear index in its grid; workgroups beyond
  * n_records leave nothing; either pointer may be NULL): the 100 MHz wall clock
