@@ -174,21 +174,22 @@ __device__ __forceinline__ uint32_t row_distance(const uint32_t (&row)[Dist<METR
   }
 }
 
+// Waves per SIMD that the registers of a workgroup have to leave room for, where the compiler takes a few more than that by
+// itself.  Fused scans of three-bit codes: at d = 256 130 vector registers, with which a compute unit holds one workgroup of eight
+// waves instead of two (16 sequences of 17000 tokens, groups of four: 121.6 us a layer, 102.8 with two); at d = 64, groups of two, 85
+// scalar ones, of which eight waves may have 80 (scan of 24 ragged sequences of 24000 tokens 24.5 us, 21.6 with them).  (Groups of
+// one and eight at d = 256 need more than a few.)  The scan of one-bit query codes at d = 192, groups of eight: 65, one workgroup of
+// sixteen waves instead of two (top-k of 24 sequences of 32000 tokens, 64 heads: 65.2 us, 57.3 with two).
+template <int G, bool FUSED, int WAVES, int METRIC, int D>
+constexpr int kScanWavesPerSimd = FUSED && METRIC == kMetricB3 && D == 64 && G == 2 && WAVES == 16          ? 8
+                                  : FUSED && METRIC == kMetricB3 && D == 256 && G > 1 && G < 8 && WAVES == 8 ? 4
+                                  : !FUSED && METRIC == kMetricB1 && D == 192 && G == 8 && WAVES == 16       ? 8
+                                                                                                             : WAVES / 4;
 // WAVES = wavefronts per workgroup (8 or 16, without the encode also 4): the tile is WAVES * 256 tokens.
 // D = head dimension: W = D / 32 words per code row.
-// Waves per SIMD that the registers of a fused workgroup of three-bit codes have to leave room for, where the compiler takes a few more
-// than that by itself: at d = 256 130 vector registers, with which a compute unit holds one workgroup of eight waves instead of two (16
-// sequences of 17000 tokens, groups of four: 121.6 us a layer, 102.8 with two); at d = 64, groups of two, 85 scalar ones, of which
-// eight waves may have 80 (scan of 24 ragged sequences of 24000 tokens 24.5 us, 21.6 with them).  (Groups of one and eight
-// at d = 256 need more than a few.)
-template <int G, int WAVES, int METRIC, int D>
-constexpr int kScanWavesPerSimd = METRIC != kMetricB3                       ? WAVES / 4
-                                  : D == 64 && G == 2 && WAVES == 16          ? 8
-                                  : D == 256 && G > 1 && G < 8 && WAVES == 8 ? 4
-                                                                             : WAVES / 4;
 template <int G, bool FUSED, int WAVES, int METRIC, bool PAGED, int D>
 __global__ __launch_bounds__(WAVES * kWave)
-__attribute__((amdgpu_waves_per_eu(FUSED ? kScanWavesPerSimd<G, WAVES, METRIC, D> : WAVES / 4)))
+__attribute__((amdgpu_waves_per_eu(kScanWavesPerSimd<G, FUSED, WAVES, METRIC, D>)))
 void scan_kernel(const ScanParams p) {
   static_assert(FUSED || !PAGED, "the paged layout is served by the fused step only");
   using Fmt = Dist<METRIC, D>;
@@ -403,9 +404,10 @@ void scan_kernel(const ScanParams p) {
   uint32_t one = 1;  // (opaque: otherwise written anew for every use)
   asm("" : "+v"(one));
   // Three-bit codes from d = 160 on spill in workgroups of sixteen waves: the tokens' numbers are made again at their use, not kept (d = 160,
-  // groups of three, 24 ragged sequences of 24000 tokens: 85.7 -> 81.4 us; of six 123.2 -> 115.4).
+  // groups of three, 24 ragged sequences of 24000 tokens: 85.7 -> 81.4 us; of six 123.2 -> 115.4).  So are those of the one-bit instance
+  // that would spill a register otherwise (kScanWavesPerSimd).
   int of_wave = lane;
-  if constexpr (FUSED && BITS == 3 && WAVES == 16 && D >= 160) asm("" : "+v"(of_wave));
+  if constexpr (WAVES == 16 && (FUSED ? BITS == 3 && D >= 160 : BITS == 1 && D == 192 && G == 8)) asm("" : "+v"(of_wave));
 #pragma unroll
   for (int g0 = 0; g0 < G; g0 += kPassHeads) {
 #pragma unroll

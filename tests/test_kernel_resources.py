@@ -45,6 +45,12 @@ def test_three_workgroups_of_the_scan_of_query_codes_fit_a_compute_unit(metric, 
         assert R.waves_per_simd(k) >= waves and k.scratch == 0, (name, k)
 
 
+def test_two_workgroups_of_the_one_bit_scan_of_query_codes_fit_a_compute_unit():
+    """Sixteen waves each, d = 192, groups of six to eight: 64 vector registers."""
+    for name, k in instances(r"scan_kernel<[678], false, 16, %d, false, 192>" % METRIC["one bit"]).items():
+        assert k.vgprs <= 64 and k.scratch == 0, (name, k)
+
+
 @pytest.mark.parametrize("group", range(2, 8))
 def test_two_workgroups_of_the_three_bit_scan_fit_a_compute_unit(group):
     """Eight waves each, d = 256: 128 vector registers.  And groups of two at d = 64: 80 scalar registers for eight waves per SIMD."""
