@@ -215,7 +215,7 @@ void scan_kernel(const ScanParams p) {
   constexpr int kScanRowWords = kScanTokPerThread * kRowWords, kHeadWords = QP * W + kScanRowWords;
   constexpr bool kScalarPlanes = !kAllTogether && (kHeadWords > 96 || (!FUSED && kHeadWords <= 68 && (BITS == 3 || kHeadWords >= 60)));
   constexpr int kTogether =
-      kAllTogether ? G : kScalarPlanes || kPassHeads * QP * W + kScanRowWords <= (BITS == 3 ? 44 : 48) ? kPassHeads : 1;
+      kAllTogether ? G : kScalarPlanes || WAVES == 4 || kPassHeads * QP * W + kScanRowWords <= (BITS == 3 ? 44 : 48) ? kPassHeads : 1;
   // per wave: its 256 distances to each query head of a pass, in token order
   __shared__ __align__(16) uint16_t s_dt[WAVES][kPassHeads][kScanTokPerThread * kWave];
 
@@ -393,6 +393,9 @@ void scan_kernel(const ScanParams p) {
   // (the method's group of one or two) at once; larger groups the heads of a pass at once where their planes and the rows leave a wave
   // within 64 registers, else one head after the other over the rows, which stay in registers.  (d = 96, groups of four: one by one
   // 27.4 us for 24 ragged sequences of 24000 tokens, two by two 25.8; d = 64, groups of eight 26.9 and 25.1.)
+  // Workgroups of four waves are those of calls that leave compute units idle, where registers to spare cost nothing and a wait for the
+  // planes of every head does: all heads of a pass at once (distances of 38 ragged sequences of 841 tokens, one bit, d = 256, groups of
+  // eight 7.4 us one by one, 6.8; of 19 of 872, squared differences at d = 128, groups of six 7.4 and 6.7).
   // Scalar registers hold them where they do not fit next to the rows, or cost a workgroup: three-bit codes at d = 256 (24 ragged
   // sequences of 10540 tokens, groups of six 33.9 us a layer, 44.1 in vector registers), and without the encode, which takes most, three-bit codes up to
   // d = 128 and two-bit ones at 192 (top-k of 8 sequences of 24000 tokens, three bits at d = 128, groups of three 31.8 us in vector

@@ -11,7 +11,6 @@ LARGEST = {"method": 3, "squared differences": 9, "one bit": 1, "three bits": 7}
 
 
 def instances(pattern):
-    import re
     found = {n: k for n, k in R.kernels().items() if re.fullmatch(pattern, n)}
     assert found, pattern
     return found
@@ -49,6 +48,12 @@ def test_two_workgroups_of_the_one_bit_scan_of_query_codes_fit_a_compute_unit():
     """Sixteen waves each, d = 192, groups of six to eight: 64 vector registers."""
     for name, k in instances(r"scan_kernel<[678], false, 16, %d, false, 192>" % METRIC["one bit"]).items():
         assert k.vgprs <= 64 and k.scratch == 0, (name, k)
+
+
+def test_four_workgroups_of_the_smallest_scans_fit_a_compute_unit():
+    """Four waves each, the planes of a pass's heads all at once (three at d = 256 with three-bit codes)."""
+    for name, k in instances(r"scan_kernel<\d, false, 4, \d, false, \d+>").items():
+        assert R.waves_per_simd(k) >= (3 if name.endswith(", 3, false, 256>") else 4) and k.scratch == 0, (name, k)
 
 
 @pytest.mark.parametrize("group", range(2, 8))
