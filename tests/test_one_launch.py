@@ -38,7 +38,10 @@ SLOWER = [((64, 1), (48, 8, 14, 26137, 491, 0, STEP), 57.4, 40.2), ((64, 1), (64
           ((128, 1), (16, 4, 41, 25530, 331, 64, STEP), 56.2, 45.0), ((96, 1), (112, 16, 12, 16330, 41, 0, TOPK), 44.7, 26.8),
           ((96, 3), (24, 8, 1, 8925, 18, 0, TOPK), 16.8, 10.6), ((256, 2), (48, 16, 2, 15190, 910, 0, TOPK), 25.6, 17.1),
           ((160, 1), (64, 8, 5, 17395, 819, 0, TOPK), 27.5, 18.5), ((96, 3), (32, 8, 44, 7100, 394, 0, TOPK), 72.2, 50.2),
-          ((96, 2), (7, 1, 408, 16330, 870, 0, TOPK), 98.4, 73.2), ((160, 2), (64, 8, 2, 13312, 36, 0, TOPK), 13.6, 10.9)]
+          ((96, 2), (7, 1, 408, 16330, 870, 0, TOPK), 98.4, 73.2), ((160, 2), (64, 8, 2, 13312, 36, 0, TOPK), 13.6, 10.9),
+          # rows of pieces of four bytes
+          ((160, 3), (4, 4, 26, 5791, 84, 0, TOPK), 21.0, 14.6), ((96, 3), (48, 8, 10, 13187, 339, 0, TOPK), 47.2, 35.1),
+          ((160, 1), (3, 1, 5, 8963, 39, 0, TOPK), 9.8, 7.4), ((160, 1), (8, 8, 8, 10363, 35, 0, TOPK), 10.3, 7.7)]
 
 
 @pytest.mark.parametrize("code,call,one,two", SLOWER)
